@@ -49,6 +49,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <limits.h>
 #include <math.h>
 #include <stdint.h>
 #include <string.h>
@@ -137,10 +138,13 @@ __device__ __forceinline__ void lse_add(float& m, float& s, float l) {
 }
 
 __device__ __forceinline__ void lse_merge(float& m, float& s, float m2, float s2) {
-  const float mm = fmaxf(m, m2);
-  if (mm == -INFINITY) { m = -INFINITY; s = 0.0f; return; }
-  s = s * exp2_fast(m - mm) + s2 * exp2_fast(m2 - mm);
-  m = mm;
+  // the same bits whichever state comes first (a tree of merges then does not
+  // depend on the lane that holds its result)
+  const bool first = m >= m2;
+  const float hi = first ? m : m2, lo = first ? m2 : m;
+  if (hi == -INFINITY) { m = -INFINITY; s = 0.0f; return; }
+  s = __fmaf_rn(first ? s2 : s, exp2_fast(lo - hi), first ? s : s2);
+  m = hi;
 }
 
 // Lane-state update of k_logz: the state starts at m = kEmpty (finite, below any
@@ -185,17 +189,17 @@ __device__ __forceinline__ void lse_add_e(float& m, float& s, float l) {
 }
 
 // ---------------------------------------------------------------- tiles
-// rows x D64 fp32 tile of x (rows [r0, r0+rows)) into LDS with row pitch D64+4;
-// rows >= nend and columns >= d are zero.
-template <int D64>
+// rows x D64 fp32 tile of x (row row_of(r), r < rows) into LDS with row pitch
+// D64+4; rows >= nend and columns >= d are zero.
+template <int D64, class Row>
 __device__ __forceinline__ void load_tile(const float* __restrict__ x, int64_t nend, int d,
-                                          int64_t r0, int rows, float* xs, bool vec4) {
+                                          Row&& row_of, int rows, float* xs, bool vec4) {
   constexpr int P = D64 + 4;
   if (vec4) {
     constexpr int Q4 = D64 / 4;
     for (int idx = threadIdx.x; idx < rows * Q4; idx += blockDim.x) {
       const int r = idx / Q4, c = (idx % Q4) * 4;
-      const int64_t nn = r0 + r;
+      const int64_t nn = row_of(r);
       float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
       if (nn < nend && c < d) v = *reinterpret_cast<const float4*>(x + nn * d + c);
       *reinterpret_cast<float4*>(xs + r * P + c) = v;
@@ -203,7 +207,7 @@ __device__ __forceinline__ void load_tile(const float* __restrict__ x, int64_t n
   } else {
     for (int idx = threadIdx.x; idx < rows * D64; idx += blockDim.x) {
       const int r = idx / D64, c = idx % D64;
-      const int64_t nn = r0 + r;
+      const int64_t nn = row_of(r);
       xs[r * P + c] = (nn < nend && c < d) ? x[nn * d + c] : 0.0f;
     }
   }
@@ -334,7 +338,19 @@ __device__ __forceinline__ double ill_logit_bounded_gr(const float* __restrict__
 
 // ---------------------------------------------------------------- prep
 // Workspace counters: [0] well components, [1] ill-conditioned components,
-// [2] well 32-blocks, [3] ill 32-blocks.
+// [2] well 32-blocks, [3] ill 32-blocks, then those of the one-product
+// screening: heavy points of its sample, "wild" parameters (weights near the
+// end of the float range: its error bound does not hold, every point is
+// heavy), and the number of heavy points (64 bits).
+constexpr int kCntSample = 4, kCntWild = 5, kCntHeavy = 6;
+constexpr double kWildWeight = 1e28;
+// The one-product screening is off (every point is heavy).
+__device__ __forceinline__ bool coarse_off(const int* __restrict__ counts, int sample_max) {
+  return counts[kCntWild] != 0 || counts[kCntSample] > sample_max;
+}
+__device__ __forceinline__ int64_t heavy_count(const int* __restrict__ counts) {
+  return (int64_t)*reinterpret_cast<const unsigned long long*>(counts + kCntHeavy);
+}
 
 __global__ __launch_bounds__(64) void k_prep_class(const float* __restrict__ w,
                                                    const float* __restrict__ mu,
@@ -345,22 +361,25 @@ __global__ __launch_bounds__(64) void k_prep_class(const float* __restrict__ w,
                                                    float2* __restrict__ cthr) {
   const int comp = blockIdx.x, lane = threadIdx.x;
   double e = 0.0, lg = 0.0;
+  bool tame = true;                             // every expanded-form weight below kWildWeight
   for (int j = lane; j < d; j += 64) {
     const double m = mu[(int64_t)comp * d + j], v = var[(int64_t)comp * d + j];
     e += m * m / v;
     lg += kLog2Pi + log(v);
+    tame = tame && fabs(m) / v < kWildWeight && 1.0 / v < kWildWeight;
   }
   for (int off = 32; off > 0; off >>= 1) {
     e += __shfl_xor(e, off);
     lg += __shfl_xor(lg, off);
   }
+  const bool wild = __ballot(!tame) != 0ull || !(fabs(lg) < kWildWeight) || !(e < kWildWeight);
   if (lane == 0) {
     const double wk = w[comp];
     int c;
     if (!(wk > 0.0)) c = 2;
     else if (e + d > kIllSum || !(e == e)) c = 1;
     else c = 0;
-    cls[comp] = c;
+    cls[comp] = c | (wild && c != 2 ? 4 : 0);
     const double lw = wk > 0.0 ? log(wk) : -INFINITY;
     cwell[comp] = kLog2e * (lw - 0.5 * (e + lg));
     cdir[comp] = kLog2e * (lw - 0.5 * lg);
@@ -384,11 +403,15 @@ __global__ __launch_bounds__(256) void k_prep_scan(const int* __restrict__ cls, 
   __shared__ int cw[256], ci[256];
   const int t = threadIdx.x;
   const int b = (int)((int64_t)k * t / 256), e = (int)((int64_t)k * (t + 1) / 256);
-  int nw = 0, ni = 0;
-  for (int c = b; c < e; ++c) { nw += cls[c] == 0; ni += cls[c] == 1; }
+  int nw = 0, ni = 0, wild = 0;
+  for (int c = b; c < e; ++c) {
+    nw += (cls[c] & 3) == 0;
+    ni += (cls[c] & 3) == 1;
+    wild |= cls[c] & 4;
+  }
   cw[t] = nw;
   ci[t] = ni;
-  __syncthreads();
+  wild = __syncthreads_or(wild);
   if (t == 0) {
     int aw = 0, ai = 0;
     for (int i = 0; i < 256; ++i) {
@@ -400,12 +423,15 @@ __global__ __launch_bounds__(256) void k_prep_scan(const int* __restrict__ cls, 
     counts[1] = ai;
     counts[2] = (aw + kBK - 1) / kBK;
     counts[3] = (ai + kBK - 1) / kBK;
+    counts[kCntSample] = 0;
+    counts[kCntWild] = wild != 0;
+    counts[kCntHeavy] = counts[kCntHeavy + 1] = 0;
   }
   __syncthreads();
   int pw = cw[t], pi = ci[t];
   for (int c = b; c < e; ++c) {
-    if (cls[c] == 0) well_idx[pw++] = c;
-    else if (cls[c] == 1) ill_idx[pi++] = c;
+    if ((cls[c] & 3) == 0) well_idx[pw++] = c;
+    else if ((cls[c] & 3) == 1) ill_idx[pi++] = c;
   }
 }
 
@@ -1063,6 +1089,7 @@ struct LogzPost {
   float rres[kRefCap];        // exact log-density relative to the screening log2 Z
   int rts[4][kT][PTS];        // per (wave, point): largest exact candidates
   float rtl[4][kT][PTS];
+  int64_t prow[PTS];          // row of each point (n past the last one)
 };
 
 // REFINE = false (the screened E-step): the candidates keep their screened
@@ -1075,9 +1102,9 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_logz(
     const int* __restrict__ well_idx, const int* __restrict__ ill_idx,
     const float* __restrict__ dmu, const double* __restrict__ dh, const double* __restrict__ cdir,
     const int* __restrict__ counts, double* __restrict__ logz2,
-    unsigned short* __restrict__ cslot, float* __restrict__ cr, double* __restrict__ ll_part,
+    unsigned short* __restrict__ cslot, float* __restrict__ cr,
     unsigned long long* __restrict__ bmask, unsigned char* __restrict__ iflag,
-    unsigned char* __restrict__ lflag) {
+    unsigned char* __restrict__ lflag, const int64_t* __restrict__ hlist, int sample_max) {
   constexpr int P = D64 + 4, NT = logz_tiles(D64), PTS = 32 * NT;
   constexpr bool B16 = screen_b16(D64);
   static_assert(!ISO || screen_split(D64), "the isotropic screening is a split-bf16 one");
@@ -1128,8 +1155,18 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_logz(
   auto& rres = post.rres;
   auto& rts = post.rts;
   auto& rtl = post.rtl;
+  auto& prow = post.prow;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, h = lane >> 5, col = lane & 31;
   const int64_t n0 = (int64_t)blockIdx.x * PTS;
+  // the points taken: the heavy ones of the one-product screening (hlist), or
+  // all of them; np of them in all, point p of this workgroup is row(p)
+  const bool whole = hlist == nullptr || coarse_off(counts, sample_max);
+  const int64_t np = whole ? n : heavy_count(counts);
+  if (n0 >= np) return;
+  auto row_of = [&](int p) -> int64_t {
+    if (n0 + p >= np) return n;
+    return whole ? n0 + p : hlist[n0 + p];
+  };
   if constexpr (B16) {
     // split tile: chunk c < D64/8 holds x of dims 8c .. 8c+7, chunk c + D64/8
     // x^2 of the same dims; rows >= n and dims >= d are zero
@@ -1144,7 +1181,7 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_logz(
 #pragma unroll
       for (int it = 0; it < NIT; ++it) {
         const int t = tid + 256 * it, p = t / NC8, c = t % NC8;
-        const int64_t row = n0 + p;
+        const int64_t row = row_of(p);
 #pragma unroll
         for (int hf = 0; hf < 2; ++hf) {
           const int j = 8 * c + 4 * hf;
@@ -1175,7 +1212,7 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_logz(
     } else {
       for (int t = tid; t < PTS * NC8; t += 256) {
         const int p = t / NC8, c = t % NC8;
-        const int64_t row = n0 + p;
+        const int64_t row = row_of(p);
         float v[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
@@ -1191,7 +1228,7 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_logz(
       if (tid < PTS) split_store_norm<D64>(xa, tid, csq + tid * NC8);
     }
   } else {
-    load_tile<D64>(x, n, d, n0, PTS, xs, vec4 != 0);
+    load_tile<D64>(x, n, d, row_of, PTS, xs, vec4 != 0);
   }
   __syncthreads();
   const int n_wkb = counts[2], n_ill = counts[1], n_well = counts[0];
@@ -1281,6 +1318,7 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_logz(
   }
   // the state below takes over the split tile's space
   if constexpr (B16) __syncthreads();
+  if (tid < PTS) prow[tid] = row_of(tid);
   // arg-max of every lane state, and the per-wave merged state of every point:
   // the LSE states and the two largest lane-state maxima (A >= B) of the 32
   // lanes of a lane half are merged by a transposing reduction (xpose_levels)
@@ -1359,7 +1397,7 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_logz(
     double mi = -INFINITY;
     float si = 0.0f;
     // rows >= n (zero rows of the fp32 tile) are skipped with the split tile
-    const int64_t row = n0 + lane;
+    const int64_t row = prow[lane];
     auto take = [&](double l) {
       if (l > mi) {
         si = __fmaf_rn(si, exp2_fast((float)(mi - l)), 1.0f);
@@ -1590,7 +1628,7 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_logz(
   // its entries in list order, so the result does not depend on the split.
   {
     const int p = lane, w2 = wave;
-    const bool owner = lane < PTS && n0 + lane < n;
+    const bool owner = lane < PTS && n0 + lane < np;
     unsigned cm = 0u, fm = 0u;
     int my_c = 0;
     // components of lane state (w2, b): slots 32 kb + b, kb = w2, w2 + 4, ... < n_wkb
@@ -1671,7 +1709,7 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_logz(
           for (int j = lo + tid / G; j < hi; j += 256 / G) {
             const int e = rlist[j - lo], pp = e >> 16;
             const int comp = widx[e & 0xFFFF];
-            const float* xr = x + (n0 + pp) * d;
+            const float* xr = x + prow[pp] * d;
             const float* mu = dmu + (size_t)comp * D64;
             const double* hh = dh + (size_t)comp * D64;
             const double cd = cdir[comp];
@@ -1716,7 +1754,7 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_logz(
             else comp = well_idx[e & 0xFFFF];
             const double ref = lzm[pp] > -INFINITY ? (double)lzm[pp] : 0.0;
             const double l =
-                B16 ? ill_logit_gr(x + (n0 + pp) * d, d, vec4, dmu + (size_t)comp * D64,
+                B16 ? ill_logit_gr(x + prow[pp] * d, d, vec4, dmu + (size_t)comp * D64,
                                    dh + (size_t)comp * D64, cdir[comp])
                     : ill_logit<D64>(xs + pp * P, dmu + (size_t)comp * D64,
                                      dh + (size_t)comp * D64, cdir[comp]);
@@ -1731,7 +1769,7 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_logz(
 #pragma unroll
           for (int blk = 0; blk < NT; ++blk) {
             const int pp = blk * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-            if (((cbits >> (16 * blk + v)) & 1u) && n0 + pp < n) {
+            if (((cbits >> (16 * blk + v)) & 1u) && n0 + pp < np) {
               const int pos = rcnt[pp * 4 + wave] + __popc(cmask[pp][wave] & ((1u << col) - 1u));
               if (pos >= lo && pos < hi) {
                 const float mv = blk ? m1[v] : m0[v];
@@ -1767,7 +1805,6 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_logz(
   __syncthreads();
   if (tid < 64) {
     const int p = tid;
-    double contrib = 0.0;
     if (p < PTS) {
       const float ref = lzm[p] > -INFINITY ? lzm[p] : 0.0f;
       // screened mass of everything that is not a candidate (ill states are exact)
@@ -1803,10 +1840,9 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_logz(
         if (mc > -INFINITY) stot += sc * exp2_fast(mc - mt);
       }
       const float lzr = mt + __log2f(stot);   // log2 Z - ref
-      const int64_t nn = n0 + p;
+      const int64_t nn = prow[p];
       if (nn < n) {
-        contrib = (double)ref + (double)lzr;
-        logz2[nn] = contrib;
+        logz2[nn] = (double)ref + (double)lzr;
 #pragma unroll
         for (int j = 0; j < kT; ++j) {
           cslot[nn * kT + j] = tsl[j] >= 0 ? (unsigned short)tsl[j] : kNoSlot;
@@ -1844,8 +1880,638 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_logz(
         }
       }
     }
-    for (int off = 32; off > 0; off >>= 1) contrib += __shfl_xor(contrib, off);
-    if (lane == 0) ll_part[blockIdx.x] = contrib;
+  }
+}
+
+// ---------------------------------------------------------------- Step 1: one-product screening
+// Almost every component of a point lies far below its largest one, so a
+// screening with a single bf16 product per log-density (a third of the matrix
+// work of the split screening) is enough to dismiss it, provided the dismissal
+// respects the error:
+//
+//   k_coarse  l~ = c + [x | x^2] . [W | P] on bf16 MFMA, every operand rounded
+//             once.  |l~ - l| <= eps M, M the sum of the products' magnitudes:
+//             with |x mu| <= (x^2 + mu^2) / 2 and x^2 <= 3 (x - mu)^2 + 1.5 mu^2,
+//             M <= KD (cdir - l) + KA (cdir - cwell), KD = 6, KA = 4 (the x
+//             products alone, for tied variances, whose ||x||^2 step carries
+//             three bf16 pieces of either factor: KD = 3, KA = 2.5); eps =
+//             coarse_eps: two roundings of 2^-8 and the fp32 accumulation.  With
+//             b = eps (KD cdir + KA (cdir - cwell)) per component and
+//             t = l~ + b (b is part of the bias),
+//               l <= t / (1 + KD eps),   l >= (t - 2 b) / (1 - KD eps).
+//             Every component with an upper bound above (best lower bound) -
+//             window is a candidate; a point with more than kCand candidates is
+//             heavy and goes to k_logz.
+//   k_refine  the candidates' log-densities in the direct form (fp64), log Z
+//             from them (the rest is below k 2^-window of it), the stored
+//             pairs and the dense blocks of the others.
+//
+// The components are those with a weight above 0: the well slots, then the
+// ill-conditioned ones (their bounds are wide, and hold just as well).
+// Weights whose magnitude nears the end of the float range switch the whole
+// pass off (kCntWild), and so does a sample of the points in which more than
+// sample_max are heavy.
+constexpr int kCand = 8;                // candidates held per point
+constexpr float kCoarseWindow = kDenseWindow;
+// Workgroups of the sample, taken when n is at least kSampleMin (below, the
+// pass costs no more than a round of workgroups).  The pass is switched off
+// when more than half of the sample is heavy: it costs about a third of k_logz
+// a point and the candidates' sums another sixth, so that with fewer than about
+// half of the points light it would not pay (the first E-step of a fit at
+// n = 1.18e6, d = 100, k = 1024, 64 % heavy: 8.64 ms with it, 8.2 without).
+constexpr int kSampleWG = 64;
+constexpr int64_t kSampleMin = (int64_t)1 << 18;
+// steps of 32 k: [x | x^2], or x and one step for ||x||^2
+template <int D64, bool ISO>
+__host__ __device__ constexpr int coarse_steps() {
+  return ISO ? D64 / 32 + 1 : D64 / 16;
+}
+__host__ __device__ constexpr double coarse_kd(bool iso) { return iso ? 3.0 : 6.0; }
+__host__ __device__ constexpr double coarse_ka(bool iso) { return iso ? 2.5 : 4.0; }
+// 2^-7 (1 + 2^-8) for the operands' roundings (two of 2^-8); five roundings of
+// 2^-22 of a running sum per MFMA for the accumulation
+__host__ __device__ constexpr double coarse_eps(int D64, bool iso) {
+  return 0x1p-7 * (1.0 + 0x1p-8) + (5.0 * (iso ? D64 / 32 : D64 / 16) + 16.0) * 0x1p-22;
+}
+// 16-point tiles per wave: the points' operands stay in registers, and two waves
+// share each SIMD
+__host__ __device__ constexpr int coarse_tiles(int D64) {
+  return D64 <= 128 ? 4 : (D64 <= 192 ? 3 : 2);
+}
+
+// Groups of 16 components per LDS block (two blocks and two workgroups fit a
+// compute unit's LDS); kpad, a multiple of 64, is a multiple of it.
+__host__ __device__ constexpr int coarse_groups(int D64) { return D64 <= 128 ? 4 : 2; }
+
+// Packed operand of k_coarse: wpc[(g * NS + s) * 64 + l] holds A[slot 16 g +
+// l % 16][k = 32 s + 8 (l / 16) + e], e = 0..7: W of dimension k for k < D64, P of
+// dimension k - D64 for k < 2 D64 (not ISO).  ISO: after the x steps one step
+// that meets the three bf16 pieces of ||x||^2 (lane group l / 16 = 0, places 0..2
+// and 3..5, group 1, places 0..2) with the three pieces of -1/2 log2(e) / var.
+// cbias[slot] = c + b, cb2[slot] = 2 b, cidx[slot] = the component; slots past the
+// last component have weights 0 and a bias far below everything.
+template <int D64, bool ISO>
+__global__ __launch_bounds__(256) void k_prep_pack_coarse(
+    const float* __restrict__ mu, const float* __restrict__ var, int d, int kpad,
+    const double* __restrict__ cwell, const double* __restrict__ cdir,
+    const int* __restrict__ counts, const int* __restrict__ well_idx,
+    const int* __restrict__ ill_idx, bf16x8* __restrict__ wpc, float* __restrict__ cbias,
+    float* __restrict__ cb2, int* __restrict__ cidx) {
+  constexpr int NS = coarse_steps<D64, ISO>(), NX = D64 / 32;
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= (int64_t)(kpad / 16) * NS * 64) return;
+  const int lane = (int)(t & 63), s = (int)((t >> 6) % NS), gr = (int)((t >> 6) / NS);
+  const int slot = gr * 16 + (lane & 15), k4 = lane >> 4;
+  const int n_well = counts[0], n_c = n_well + counts[1];
+  const int comp = slot < n_well ? well_idx[slot] : (slot < n_c ? ill_idx[slot - n_well] : -1);
+  bf16x8 w;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) w[e] = (__bf16)0.0f;
+  if (!ISO || s < NX) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int k = 32 * s + 8 * k4 + e, j = k < D64 ? k : k - D64;
+      if (comp >= 0 && j < d) {
+        const double m = mu[(int64_t)comp * d + j], s2 = var[(int64_t)comp * d + j];
+        w[e] = (__bf16)(float)(k < D64 ? kLog2e * m / s2 : -0.5 * kLog2e / s2);
+      }
+    }
+  } else if (comp >= 0) {
+    const double v = -0.5 * kLog2e / (double)var[(int64_t)comp * d];
+    const __bf16 p0 = (__bf16)(float)v;
+    const double r1 = v - (double)(float)p0;
+    const __bf16 p1 = (__bf16)(float)r1;
+    const __bf16 p2 = (__bf16)(float)(r1 - (double)(float)p1);
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+      if (k4 == 0) {
+        w[e] = p0;
+        w[3 + e] = p1;
+      } else if (k4 == 1) {
+        w[e] = p2;
+      }
+    }
+  }
+  wpc[t] = w;
+  if (s == 0 && k4 == 0) {
+    constexpr double kEps = coarse_eps(D64, ISO);
+    double bias = -3.0e38, b = 0.0;
+    if (comp >= 0) {
+      const double cd = cdir[comp], cwl = cwell[comp];
+      // the second term: fp32 roundings of the bias and of the bounds themselves
+      b = kEps * (coarse_kd(ISO) * cd + coarse_ka(ISO) * (cd - cwl)) +
+          0x1p-20 * (fabs(cd) + fabs(cwl) + 1.0);
+      bias = cwl + b;
+    }
+    cbias[slot] = (float)bias;
+    cb2[slot] = __double2float_ru(2.0 * b);
+    cidx[slot] = comp;
+  }
+}
+
+// Four values of a row from dimension j on, zero past d: one 16-byte load
+// where four are there (rows need no alignment beyond 4 bytes; the address is
+// a select, so that loads of several chunks stay in flight together).
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 load4_row(const float* __restrict__ xr, int j, int d,
+                                            const float* __restrict__ safe) {
+  const bool full = j + 4 <= d;
+  const f4u v = *reinterpret_cast<const f4u*>(full ? xr + j : safe);
+  float4 r = make_float4(v.x, v.y, v.z, v.w);
+  asm volatile("" : "+v"(r.x), "+v"(r.y), "+v"(r.z), "+v"(r.w));
+  if (!full) r = make_float4(0.f, 0.f, 0.f, 0.f);
+  return r;
+}
+// The row's last d % 4 values, where chunk j holds them (rows narrower than
+// four dimensions included).
+__device__ __forceinline__ void load4_tail(const float* __restrict__ xr, int j, int d,
+                                           float4& r) {
+  if (j < d && j + 4 > d) {
+    r.x = xr[j];
+    r.y = j + 1 < d ? xr[j + 1] : 0.0f;
+    r.z = j + 2 < d ? xr[j + 2] : 0.0f;
+    r.w = 0.0f;
+  }
+}
+
+// Inserts u into the descending triple m1 >= m2 >= m3 (a NaN leaves it as it
+// is), in place and in two halves, the first one first: left to the compiler,
+// the three updates are scheduled apart and the old values cost registers the
+// kernel does not have.
+__device__ __forceinline__ void top3_low(float m2, float& m3, float u) {
+  asm("v_med3_f32 %0, %1, %2, %0" : "+v"(m3) : "v"(u), "v"(m2));
+}
+__device__ __forceinline__ void top3_high(float& m1, float& m2, float u) {
+  asm("v_med3_f32 %1, %2, %0, %1\n\t"
+      "v_max_f32 %0, %2, %0"
+      : "+v"(m1), "+v"(m2)
+      : "v"(u));
+}
+
+typedef float f4v __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f4v mfma16b(bf16x8 a, bf16x8 b, f4v c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+// A wave takes 16 NT points (their operands, rounded to bf16, stay in registers
+// for the whole pass: lane l holds point l % 16 of each tile) against every
+// component, 16 at a time; the workgroup's four waves share blocks of 64 (above
+// 128 dimensions 32) components through a double-buffered LDS tile, loaded one block ahead (global
+// to LDS, no registers).  Accumulator register v of lane l is component 16 g +
+// 4 (l / 16) + v of point l % 16.  A lane state (point, lane group, register) thus
+// covers every 16th component; it keeps its three largest t, whose low mantissa
+// bits carry the group, so that an update is four instructions: mask-and-or, two
+// medians, one maximum.  The updates of a group fill the issue slots between
+// the MFMAs of the next one (two accumulator sets).
+template <int D64, bool ISO>
+__global__ __launch_bounds__(256, 2) void k_coarse(
+    const float* __restrict__ x, int64_t n, int d, const bf16x8* __restrict__ wpc,
+    const float* __restrict__ cbias, const float* __restrict__ cb2, int* __restrict__ counts,
+    float window, int64_t wg_step, int sample, int sample_max,
+    unsigned short* __restrict__ cand, int64_t* __restrict__ hlist) {
+  constexpr int NS = coarse_steps<D64, ISO>(), NT = coarse_tiles(D64), PTS = 16 * NT;
+  constexpr int NX = D64 / 32;                  // x steps
+  constexpr int GPB = coarse_groups(D64);       // groups of 16 components a block
+  constexpr int WB = GPB * NS;                  // 1 KB pieces of a block's operand
+  constexpr float kKE = (float)(coarse_kd(ISO) * coarse_eps(D64, ISO));
+  // two objects, so that reads of one do not wait for the loads into the other
+  __shared__ __align__(16) bf16x8 wbuf0[WB * 64];
+  __shared__ __align__(16) bf16x8 wbuf1[WB * 64];
+  __shared__ __align__(16) float bbuf0[64];     // biases, in the first 16 GPB
+  __shared__ __align__(16) float bbuf1[64];
+  __shared__ __align__(16) unsigned short clist[4 * PTS * kCand];
+  __shared__ int hcnt[4];
+  __shared__ unsigned long long hbase;
+  if (!sample && coarse_off(counts, sample_max)) return;
+  const int n_c = counts[0] + counts[1], nkb = (n_c + 16 * GPB - 1) / (16 * GPB);
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int k4 = lane >> 4, col = lane & 15;
+  const int64_t p0 = (int64_t)blockIdx.x * wg_step * (4 * PTS) + wave * PTS;
+  auto stage = [&](int kb, bf16x8* buf, float* bb) {
+#pragma unroll
+    for (int i = 0; i < (WB + 3) / 4; ++i) {
+      const int s = wave + 4 * i;
+      if (s < WB)
+        __builtin_amdgcn_global_load_lds(
+            (const __attribute__((address_space(1))) unsigned*)(wpc + ((size_t)kb * WB + s) * 64 +
+                                                                lane),
+            (__attribute__((address_space(3))) unsigned*)(buf + s * 64), 16, 0, 0);
+    }
+    if (wave == 0)
+      __builtin_amdgcn_global_load_lds(
+          (const __attribute__((address_space(1))) unsigned*)(cbias + (size_t)kb * 16 * GPB +
+                                                              (lane & (16 * GPB - 1))),
+          (__attribute__((address_space(3))) unsigned*)bb, 4, 0, 0);
+  };
+  if (nkb > 0) stage(0, wbuf0, bbuf0);
+  // the points' operands
+  bf16x8 xr[NT][NS];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int64_t row = p0 + 16 * t + col;
+    const float* xp = x + (row < n ? row : 0) * (int64_t)d;
+    const int dd = row < n ? d : 0;
+    float ssq = 0.0f;
+    float4 ld[NX][2];
+    if (d >= 4) {
+#pragma unroll
+      for (int s = 0; s < NX; ++s)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) ld[s][u] = load4_row(xp, 32 * s + 8 * k4 + 4 * u, dd, x);
+    } else {
+#pragma unroll
+      for (int s = 0; s < NX; ++s) ld[s][0] = ld[s][1] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    if (d & 3) {
+#pragma unroll
+      for (int s = 0; s < NX; ++s)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) load4_tail(xp, 32 * s + 8 * k4 + 4 * u, dd, ld[s][u]);
+    }
+#pragma unroll
+    for (int s = 0; s < NX; ++s) {
+      const float v[8] = {ld[s][0].x, ld[s][0].y, ld[s][0].z, ld[s][0].w,
+                          ld[s][1].x, ld[s][1].y, ld[s][1].z, ld[s][1].w};
+      float q8 = 0.0f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        xr[t][s][e] = (__bf16)v[e];
+        if constexpr (ISO) q8 = __fmaf_rn(v[e], v[e], q8);
+        else xr[t][NX + s][e] = (__bf16)(v[e] * v[e]);
+      }
+      ssq += q8;
+    }
+    if constexpr (ISO) {
+      float nrm = ssq + __shfl_xor(ssq, 16);
+      nrm += __shfl_xor(nrm, 32);
+      const __bf16 q0 = (__bf16)nrm;
+      const float r1 = nrm - (float)q0;
+      const __bf16 q1 = (__bf16)r1;
+      const __bf16 q2 = (__bf16)(r1 - (float)q1);
+      bf16x8 last;                              // the other groups meet weights 0
+      last[0] = last[3] = q0;
+      last[1] = last[4] = q1;
+      last[2] = last[5] = q2;
+      last[6] = last[7] = (__bf16)0.0f;
+      xr[t][NS - 1] = last;
+    }
+  }
+  int nbits = 0;                                // index bits: the group of 16
+  while ((GPB * nkb - 1) >> nbits) ++nbits;
+  const unsigned imask = (1u << nbits) - 1u;
+  unsigned keep = ~imask;
+  asm volatile("" : "+v"(keep));                // a vector register: the index is the scalar operand
+  float m1[NT][4], m2[NT][4], m3[NT][4];
+  f4v acc[2][NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      m1[t][v] = m2[t][v] = m3[t][v] = kEmpty;
+      acc[1][t][v] = kEmpty;
+    }
+  // a value is taken in by two half updates of two instructions each
+  float uh;
+  auto take = [&](int half, int t, int v, float l, int g) {
+    if (half == 0) {
+      uh = __uint_as_float((__float_as_uint(l) & keep) | (unsigned)g);
+      top3_low(m2[t][v], m3[t][v], uh);
+    } else {
+      top3_high(m1[t][v], m2[t][v], uh);
+    }
+  };
+  // The block's groups, group g's log-densities going into acc[g % 2] while
+  // group g - 1 (the other set) is taken in; operand pieces are read three
+  // steps ahead, across the groups.
+  auto block = [&](int kb, const bf16x8* cur, const float* cb, bf16x8* nxt, float* nb) {
+    constexpr int NV = 8 * NT, NM = NS * NT;    // half updates and MFMAs a group
+    // this wave's share of block kb has arrived (the barrier alone does not
+    // wait for loads into LDS), then everybody's; block kb - 1 is done with
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (kb + 1 < nkb) stage(kb + 1, nxt, nb);
+    const bf16x8* wl = cur + lane;
+    const float* bl = cb + 4 * k4;
+    constexpr int RW = 4;                       // ring: three steps ahead
+    static_assert(WB >= RW, "steps a block");
+    bf16x8 w[RW];
+#pragma unroll
+    for (int q = 0; q < RW - 1; ++q) w[q] = wl[64 * q];
+    f4v bias[2];
+    bias[0] = *reinterpret_cast<const f4v*>(bl);
+#pragma unroll
+    for (int q = 0; q < WB; ++q) {
+      const int gi = q / NS, s = q % NS, A = gi & 1;
+      if (q + RW - 1 < WB) w[(q + RW - 1) % RW] = wl[64 * (q + RW - 1)];
+      if (s == NS - 2 && gi + 1 < GPB)
+        bias[(gi + 1) & 1] = *reinterpret_cast<const f4v*>(bl + 16 * (gi + 1));
+      const int g = GPB * kb + gi;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        acc[A][t] = mfma16b(w[q % RW], xr[t][s], s == 0 ? bias[A] : acc[A][t]);
+#pragma unroll
+        for (int i = (s * NT + t) * NV / NM; i < (s * NT + t + 1) * NV / NM; ++i)
+          take(i & 1, i >> 3, (i >> 1) & 3, acc[1 - A][i >> 3][(i >> 1) & 3], g > 0 ? g - 1 : 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+  for (int kb = 0; kb + 1 < nkb; kb += 2) {
+    block(kb, wbuf0, bbuf0, wbuf1, bbuf1);
+    block(kb + 1, wbuf1, bbuf1, wbuf0, bbuf0);
+  }
+  if (nkb & 1) block(nkb - 1, wbuf0, bbuf0, wbuf1, bbuf1);
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      take(0, t, v, acc[1][t][v], nkb > 0 ? GPB * nkb - 1 : 0);
+      take(1, t, v, 0.0f, 0);
+    }
+  // per point (its four lanes agree on everything below): the best lower bound,
+  // the threshold, the candidates
+  const float dlt = __uint_as_float((unsigned)(127 - 22 + nbits) << 23);   // 2^(nbits - 22)
+  unsigned short* const cl = clist + wave * PTS * kCand;
+  auto slot_of = [&](float u, int v) {
+    return (int)(__float_as_uint(u) & imask) * 16 + 4 * k4 + v;
+  };
+  auto lower = [&](float u, int v) {
+    const int sl = slot_of(u, v);
+    return (u - dlt * fabsf(u) - cb2[sl < n_c ? sl : 0]) / (1.0f - kKE);
+  };
+  auto thresh = [&](float lo) {
+    const float T = (1.0f + kKE) * (lo - window);
+    return T - (dlt + 0x1p-18f) * (fabsf(T) + 1.0f);
+  };
+  unsigned long long hv[NT];                    // heavy points of each tile (lanes 0..15)
+  auto max4 = [&](float v) {
+    v = fmaxf(v, __shfl_xor(v, 16));
+    return fmaxf(v, __shfl_xor(v, 32));
+  };
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    float best = kEmpty;
+    int bv = 0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      if (m1[t][v] > best) {
+        best = m1[t][v];
+        bv = v;
+      }
+    }
+    float lo = best > -1e30f ? lower(best, bv) : -INFINITY;
+    lo = max4(lo);
+    float T = thresh(lo);
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      if (m1[t][v] >= T && v != bv) lo = fmaxf(lo, lower(m1[t][v], v));
+    lo = max4(lo);
+    T = thresh(lo);
+    int c = 0;
+    bool over = !(fabsf(lo) < 1e30f);           // nothing finite, or NaN
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      c += (m1[t][v] >= T ? 1 : 0) + (m2[t][v] >= T ? 1 : 0);
+      over = over || m3[t][v] >= T;
+    }
+    const int c1 = __shfl_xor(c, 16), cc = c + c1, c2 = __shfl_xor(cc, 32);
+    const bool live = p0 + 16 * t + col < n;
+    // (no candidate at all: bounds that contradict each other; the point is
+    // listed in one of the two places in every case)
+    over = over || cc + c2 > kCand || cc + c2 == 0;
+    // (every lane takes part in the exchange: a lane that skipped it would read as 0)
+    int ov = over ? 1 : 0;
+    ov |= __shfl_xor(ov, 16);
+    ov |= __shfl_xor(ov, 32);
+    over = ov != 0 && live;
+    hv[t] = __ballot(over && k4 == 0);
+    if (sample) continue;
+    unsigned short* const my = cl + (16 * t + col) * kCand;
+    // kNoSlot everywhere; a heavy point's list stays empty
+    if (k4 == 0) {
+#pragma unroll
+      for (int j = 0; j < kCand; ++j) my[j] = kNoSlot;
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (!over && live) {
+      int pos = ((k4 & 1) != 0 ? c1 : 0) + ((k4 & 2) != 0 ? c2 : 0);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        if (m1[t][v] >= T) my[pos++] = (unsigned short)slot_of(m1[t][v], v);
+        if (m2[t][v] >= T) my[pos++] = (unsigned short)slot_of(m2[t][v], v);
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (k4 == 0 && live) {
+      ushort4 o[2];
+      o[0] = make_ushort4(my[0], my[1], my[2], my[3]);
+      o[1] = make_ushort4(my[4], my[5], my[6], my[7]);
+      ushort4* const dst = reinterpret_cast<ushort4*>(cand + (p0 + 16 * t + col) * kCand);
+      dst[0] = o[0];
+      dst[1] = o[1];
+    }
+  }
+  // the workgroup's heavy points: one atomic for all of them (the order of the
+  // list does not matter: k_logz's result for a point is its own)
+  int mine = 0;
+#pragma unroll
+  for (int t = 0; t < NT; ++t) mine += __popcll(hv[t]);
+  if (lane == 0) hcnt[wave] = mine;
+  __syncthreads();
+  const int all = hcnt[0] + hcnt[1] + hcnt[2] + hcnt[3];
+  if (all == 0) return;
+  if (sample) {
+    if (tid == 0) atomicAdd(&counts[kCntSample], all);
+    return;
+  }
+  if (tid == 0)
+    hbase = atomicAdd(reinterpret_cast<unsigned long long*>(counts + kCntHeavy),
+                      (unsigned long long)all);
+  __syncthreads();
+  int64_t at = (int64_t)hbase;
+  for (int w = 0; w < wave; ++w) at += hcnt[w];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    if ((hv[t] >> lane) & 1ull)
+      hlist[at + __popcll(hv[t] & ((1ull << lane) - 1ull))] = p0 + 16 * t + col;
+    at += __popcll(hv[t]);
+  }
+}
+
+// Lanes that share a point in k_refine.
+__host__ __device__ constexpr int refine_lanes(int D64) {
+  return D64 <= 192 ? 8 : (D64 <= 384 ? 16 : 32);
+}
+
+// Butterfly sum over G lanes (a fixed order).
+template <int G>
+__device__ __forceinline__ double group_sum(double v) {
+  v += xshfl<1>(v);
+  v += xshfl<2>(v);
+  v += xshfl<4>(v);
+  if constexpr (G >= 16) v += xshfl<8>(v);
+  if constexpr (G >= 32) v += xshfl<16>(v);
+  return v;
+}
+
+// Direct-form log-densities (log2 units) of the candidates of one point,
+// G lanes per point: lane g sums the float4 chunks g, g + G, ... in fp64, the
+// lanes' sums are added in a fixed order.  my: the log-density of candidate g
+// (lanes g < kCand), -inf where there is none; slot: its slot.  The row is read
+// once for all candidates.  List: the point's candidate list (kNoSlot-terminated).
+template <int D64>
+__device__ __forceinline__ void refine_point(const float* __restrict__ x, int64_t row, int d,
+                                             const uint4 list, int g,
+                                             const int* __restrict__ cidx,
+                                             const float* __restrict__ dmu,
+                                             const double* __restrict__ dh,
+                                             const double* __restrict__ cdir, double& my,
+                                             int& slot) {
+  constexpr int G = refine_lanes(D64), NC = D64 / 4 / G;
+  static_assert(NC * 4 * G == D64, "chunks split evenly");
+  const unsigned lw[4] = {list.x, list.y, list.z, list.w};
+  // lane g looks candidate g's component up, all of them in one load
+  slot = kNoSlot;
+  if (g < kCand) slot = (int)((lw[g >> 1] >> (16 * (g & 1))) & 0xFFFFu);
+  const int mycomp = slot != kNoSlot ? cidx[slot] : 0;
+  my = -INFINITY;
+  double xv[NC][4];
+  {
+    float4 xf[NC];
+    const float* xp = x + row * (int64_t)d;
+    if (d >= 4) {
+#pragma unroll
+      for (int t = 0; t < NC; ++t) xf[t] = load4_row(xp, 4 * (g + G * t), d, x);
+    } else {
+#pragma unroll
+      for (int t = 0; t < NC; ++t) xf[t] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    if (d & 3) {
+#pragma unroll
+      for (int t = 0; t < NC; ++t) load4_tail(xp, 4 * (g + G * t), d, xf[t]);
+    }
+#pragma unroll
+    for (int t = 0; t < NC; ++t) {
+      xv[t][0] = (double)xf[t].x;
+      xv[t][1] = (double)xf[t].y;
+      xv[t][2] = (double)xf[t].z;
+      xv[t][3] = (double)xf[t].w;
+    }
+  }
+  const int g0 = (int)(threadIdx.x & 63) & ~(G - 1);
+#pragma unroll
+  for (int j = 0; j < kCand; ++j) {
+    const bool has = ((lw[j >> 1] >> (16 * (j & 1))) & 0xFFFFu) != kNoSlot;
+    if (__ballot(has) == 0ull) break;           // lists are filled from the front
+    const int comp = __shfl(mycomp, g0 + j);
+    double acc = 0.0, cd = 0.0;
+    if (has) {                                  // points without a j-th candidate load nothing
+      const float* mu = dmu + (size_t)comp * D64;
+      const double* hh = dh + (size_t)comp * D64;
+      cd = cdir[comp];
+#pragma unroll
+      for (int t = 0; t < NC; ++t) {
+        const int c4 = 4 * (g + G * t);
+        const float4 m = *reinterpret_cast<const float4*>(mu + c4);
+        const double2 h0 = *reinterpret_cast<const double2*>(hh + c4);
+        const double2 h1 = *reinterpret_cast<const double2*>(hh + c4 + 2);
+        double u;
+        u = xv[t][0] - (double)m.x; acc = fma(u * u, h0.x, acc);
+        u = xv[t][1] - (double)m.y; acc = fma(u * u, h0.y, acc);
+        u = xv[t][2] - (double)m.z; acc = fma(u * u, h1.x, acc);
+        u = xv[t][3] - (double)m.w; acc = fma(u * u, h1.y, acc);
+      }
+    }
+    acc = group_sum<G>(acc);
+    if (g == j && has) my = cd - acc;
+  }
+}
+
+// E-step outputs of the points whose candidates are listed (see k_logz for what
+// they mean): log2 Z, the kT largest exact responsibilities, the blocks of the
+// other well components above 2^-kDenseWindow, the routed components' flag.
+template <int D64>
+__global__ __launch_bounds__(256) void k_refine(
+    const float* __restrict__ x, int64_t n, int d, const unsigned short* __restrict__ cand,
+    const int* __restrict__ cidx, const float* __restrict__ dmu, const double* __restrict__ dh,
+    const double* __restrict__ cdir, const int* __restrict__ counts, int sample_max,
+    double* __restrict__ logz2, unsigned short* __restrict__ cslot, float* __restrict__ cr,
+    unsigned long long* __restrict__ bmask, unsigned char* __restrict__ iflag,
+    unsigned char* __restrict__ lflag) {
+  constexpr int G = refine_lanes(D64);
+  if (coarse_off(counts, sample_max)) return;
+  const int lane = threadIdx.x & 63, g = lane & (G - 1);
+  const int64_t nn = ((int64_t)blockIdx.x * 256 + threadIdx.x) / G;
+  uint4 list = make_uint4(~0u, ~0u, ~0u, ~0u);
+  if (nn < n) list = *reinterpret_cast<const uint4*>(cand + nn * kCand);
+  const bool light = (list.x & 0xFFFFu) != kNoSlot;
+  if (__ballot(light) == 0ull) return;
+  double my;
+  int slot;
+  refine_point<D64>(x, light ? nn : 0, d, list, g, cidx, dmu, dh, cdir, my, slot);
+  // the candidates sit in lanes g = 0..7: reductions over those eight lanes
+  double mx = my;
+  mx = fmax(mx, xshfl<1>(mx));
+  mx = fmax(mx, xshfl<2>(mx));
+  mx = fmax(mx, xshfl<4>(mx));
+  const float rel = (float)(my - mx);           // -inf where there is no candidate
+  float sum = exp2_fast(rel);
+  sum += xshfl<1>(sum);
+  sum += xshfl<2>(sum);
+  sum += xshfl<4>(sum);
+  const float lz = __log2f(sum);
+  const int n_well = counts[0];
+  const bool routed = slot != kNoSlot && slot >= n_well;
+  // rank among the well candidates above 2^-kDenseWindow (as in the dense pass,
+  // what is below is left out; routed ones and empty places last, each place a
+  // rank of its own)
+  const float key =
+      slot != kNoSlot && !routed && rel - lz > -kDenseWindow ? rel : -INFINITY;
+  int rank = 0;
+  auto count = [&](auto oc) {
+    constexpr int off = decltype(oc)::value;
+    // partner g ^ off: partners cover the other seven lanes
+    float ok = key;
+    if constexpr (off & 1) ok = xshfl<1>(ok);
+    if constexpr (off & 2) ok = xshfl<2>(ok);
+    if constexpr (off & 4) ok = xshfl<4>(ok);
+    rank += (ok > key || (ok == key && (g ^ off) < g)) ? 1 : 0;
+  };
+  count(std::integral_constant<int, 1>{});
+  count(std::integral_constant<int, 2>{});
+  count(std::integral_constant<int, 3>{});
+  count(std::integral_constant<int, 4>{});
+  count(std::integral_constant<int, 5>{});
+  count(std::integral_constant<int, 6>{});
+  count(std::integral_constant<int, 7>{});
+  const bool well = key > -INFINITY;
+  // blocks of the well candidates that are not stored
+  unsigned blo = 0u, bhi = 0u;
+  if (well && rank >= kT) {
+    const int b = slot >> 6;
+    if (b < 32) blo = 1u << b;
+    else if (b < 64) bhi = 1u << (b - 32);
+  }
+  int rt = routed && rel > -60.0f ? 1 : 0;
+  auto merge = [&](auto oc) {
+    constexpr int off = decltype(oc)::value;
+    blo |= (unsigned)xshfl_i<off>((int)blo);
+    bhi |= (unsigned)xshfl_i<off>((int)bhi);
+    rt |= xshfl_i<off>(rt);
+  };
+  merge(std::integral_constant<int, 1>{});
+  merge(std::integral_constant<int, 2>{});
+  merge(std::integral_constant<int, 4>{});
+  if (!light) return;
+  if (g < kCand && rank < kT) {
+    cslot[nn * kT + rank] = well ? (unsigned short)slot : kNoSlot;
+    cr[nn * kT + rank] = well ? exp2_fast(rel - lz) : 0.0f;
+  }
+  if (g == 0) {
+    logz2[nn] = mx + (double)lz;
+    iflag[nn] = (unsigned char)rt;
+    lflag[nn] = 0;
+    if (bmask != nullptr) bmask[nn] = ((unsigned long long)bhi << 32) | blo;
   }
 }
 
@@ -1877,7 +2543,6 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_logz(
 // Statistic column block c = 4g + e (x part; the x^2 part likewise) row i is
 // dimension 64g + 4i + e, so a lane reads the 4 blocks of a group with one
 // float4 too.
-typedef float f4v __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ f4v mfma16(float a, float b, f4v c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
@@ -2544,17 +3209,23 @@ constexpr int kSparseTab = 1 << 18;     // (bucket, unit) table entries at most
 constexpr int kSparseDepth = 3;
 static_assert(kSparseDepth <= 3, "records are stored four batches ahead");
 
+// logz2 given: also the unit's sum of log2 Z, each lane its points in order,
+// the lanes by a fixed butterfly.
 __global__ __launch_bounds__(64) void k_sparse_count(const unsigned short* __restrict__ cslot,
                                                      int64_t n, int64_t upts, int nb, int lcb,
-                                                     int nunit, int* __restrict__ gcnt) {
+                                                     int nunit, int* __restrict__ gcnt,
+                                                     const double* __restrict__ logz2,
+                                                     double* __restrict__ ll_part) {
   extern __shared__ int lc[];
   const int u = blockIdx.x, lane = threadIdx.x;
   for (int b = lane; b < nb; b += 64) lc[b] = 0;
   __syncthreads();
   const int64_t p0 = (int64_t)u * upts;
   const int64_t p1 = p0 + upts < n ? p0 + upts : n;
+  double ll = 0.0;
   for (int64_t p = p0 + lane; p < p1; p += 64) {
     const ushort4 s4 = *reinterpret_cast<const ushort4*>(cslot + p * kT);
+    if (logz2 != nullptr) ll += logz2[p];
     if (s4.x != kNoSlot) atomicAdd(&lc[s4.x >> lcb], 1);
     if (s4.y != kNoSlot) atomicAdd(&lc[s4.y >> lcb], 1);
     if (s4.z != kNoSlot) atomicAdd(&lc[s4.z >> lcb], 1);
@@ -2562,6 +3233,10 @@ __global__ __launch_bounds__(64) void k_sparse_count(const unsigned short* __res
   }
   __syncthreads();
   for (int b = lane; b < nb; b += 64) gcnt[(size_t)b * nunit + u] = lc[b];
+  if (logz2 != nullptr) {
+    for (int off = 32; off > 0; off >>= 1) ll += __shfl_xor(ll, off);
+    if (lane == 0) ll_part[u] = ll;
+  }
 }
 
 // Exclusive prefix of cnt[0 .. tot) into off[0 .. tot] (64-bit), off[tot] =
@@ -3336,7 +4011,7 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_assign_theta(
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, h = lane >> 5, col = lane & 31;
   const int64_t n0 = (int64_t)blockIdx.x * PTS;
   if constexpr (SPL) split_tile<D64>(x, n, d, vec4, n0, xa);
-  else load_tile<D64>(x, n, d, n0, PTS, xs, vec4 != 0);
+  else load_tile<D64>(x, n, d, [=](int r) { return n0 + r; }, PTS, xs, vec4 != 0);
   __syncthreads();
   float m0[16], m1[16];
   int a0[16], a1[16];
@@ -3469,7 +4144,7 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_assign_collect
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, h = lane >> 5, col = lane & 31;
   const int64_t n0 = (int64_t)blockIdx.x * PTS;
   if constexpr (SPL) split_tile<D64>(x, n, d, vec4, n0, xa);
-  else load_tile<D64>(x, n, d, n0, PTS, xs, vec4 != 0);
+  else load_tile<D64>(x, n, d, [=](int r) { return n0 + r; }, PTS, xs, vec4 != 0);
   if (tid < PTS) ccnt[tid] = 0;
   __syncthreads();
   const int n_wkb = counts[2], n_ill = counts[1];
@@ -4500,6 +5175,61 @@ inline bool phase_collect() {
   return true;
 }
 
+// Where the one-product screening keeps its operands (in the partials of the
+// dense statistics, which are written later: 16 D64 + 8 bytes a component are
+// there for the 4 D64 + 76 needed at most) and its per-point lists (in the exact
+// pairs' records, also written later: 24 of 64 bytes a point).
+struct CoarseView {
+  bf16x8* wpc;
+  float* cbias;
+  float* cb2;
+  int* cidx;
+  unsigned short* cand;
+  int64_t* hlist;
+};
+
+CoarseView coarse_view(const Layout& L, void* ws) {
+  CoarseView v;
+  size_t o = L.off_part_w;
+  v.cbias = at<float>(ws, o);
+  o += (size_t)L.kpad * sizeof(float);
+  v.cb2 = at<float>(ws, o);
+  o += (size_t)L.kpad * sizeof(float);
+  v.cidx = at<int>(ws, o);
+  o += (size_t)L.kpad * sizeof(int);
+  v.wpc = at<bf16x8>(ws, o);                    // kpad is a multiple of 64: 16-byte aligned
+  v.cand = at<unsigned short>(ws, L.off_slist);
+  v.hlist = at<int64_t>(ws, L.off_slist + (size_t)L.n * kCand * sizeof(unsigned short));
+  static_assert(kT * sizeof(SPair) >= kCand * sizeof(unsigned short) + sizeof(int64_t),
+                "the lists fit the exact pairs' records");
+  return v;
+}
+
+// Operands, sample (large n) and the screening itself.  *smax: the most heavy
+// points of the sample with which the pass stays on.
+template <int D64, bool ISO>
+void launch_coarse(const Layout& L, const float* x, const float* mu, const float* var, void* ws,
+                   float window, hipStream_t st, int* smax) {
+  const CoarseView cv = coarse_view(L, ws);
+  int* counts = at<int>(ws, L.off_counts);
+  constexpr int NS = coarse_steps<D64, ISO>(), WP = 4 * 16 * coarse_tiles(D64);
+  const int64_t tot = (int64_t)(L.kpad / 16) * NS * 64;
+  hipLaunchKernelGGL((k_prep_pack_coarse<D64, ISO>), dim3((unsigned)cdiv(tot, 256)), dim3(256), 0,
+                     st, mu, var, L.d, L.kpad, at<double>(ws, L.off_cwell),
+                     at<double>(ws, L.off_cdir), counts, at<int>(ws, L.off_well_idx),
+                     at<int>(ws, L.off_ill_idx), cv.wpc, cv.cbias, cv.cb2, cv.cidx);
+  const int64_t nwg = cdiv(L.n, WP);
+  *smax = INT_MAX;
+  if (L.n >= kSampleMin) {
+    hipLaunchKernelGGL((k_coarse<D64, ISO>), dim3(kSampleWG), dim3(256), 0, st, x, L.n, L.d,
+                       cv.wpc, cv.cbias, cv.cb2, counts, window, nwg / kSampleWG, 1, INT_MAX, cv.cand,
+                       cv.hlist);
+    *smax = kSampleWG * WP / 2;
+  }
+  hipLaunchKernelGGL((k_coarse<D64, ISO>), dim3((unsigned)nwg), dim3(256), 0, st, x, L.n, L.d,
+                     cv.wpc, cv.cbias, cv.cb2, counts, window, (int64_t)1, 0, *smax, cv.cand, cv.hlist);
+}
+
 template <int D64>
 int estep_impl(const Layout& L, const float* x, const float* w, const float* mu,
                const float* var, double* nk, double* s, double* q, double* loglik,
@@ -4575,12 +5305,23 @@ int estep_impl(const Layout& L, const float* x, const float* w, const float* mu,
                        st, mu, var, d, k, dmu, dh);
   }
   tm = phase_mark(1, st) && tm;
+  const int64_t* hlist = nullptr;
+  int smax = INT_MAX;
+  if constexpr (D64 <= 256) {
+    if (L.iso) launch_coarse<D64, true>(L, x, mu, var, ws, kCoarseWindow, st, &smax);
+    else launch_coarse<D64, false>(L, x, mu, var, ws, kCoarseWindow, st, &smax);
+    hlist = coarse_view(L, ws).hlist;
+    const CoarseView cv = coarse_view(L, ws);
+    hipLaunchKernelGGL(k_refine<D64>, dim3((unsigned)cdiv(n * refine_lanes(D64), 256)), dim3(256),
+                       0, st, x, n, d, cv.cand, cv.cidx, dmu, dh, cdir, counts, smax, logz2,
+                       cslot, cr, bmask, iflag, lflag);
+  }
   bool launched = false;
   if constexpr (screen_split(D64)) {
     if (L.iso && L.refine) {
       hipLaunchKernelGGL((k_logz<D64, true, true>), dim3((unsigned)L.n_wg_logz), dim3(256), 0, st,
                          x, n, d, vec4, wp, wpb, cw, thr, well_idx, ill_idx, dmu, dh, cdir, counts,
-                         logz2, cslot, cr, llpart, bmask, iflag, lflag);
+                         logz2, cslot, cr, bmask, iflag, lflag, hlist, smax);
       launched = true;
     }
   }
@@ -4588,11 +5329,11 @@ int estep_impl(const Layout& L, const float* x, const float* w, const float* mu,
     if (L.refine)
       hipLaunchKernelGGL((k_logz<D64, true, false>), dim3((unsigned)L.n_wg_logz), dim3(256), 0, st,
                          x, n, d, vec4, wp, wpb, cw, thr, well_idx, ill_idx, dmu, dh, cdir, counts,
-                         logz2, cslot, cr, llpart, bmask, iflag, lflag);
+                         logz2, cslot, cr, bmask, iflag, lflag, hlist, smax);
     else
       hipLaunchKernelGGL((k_logz<D64, false, false>), dim3((unsigned)L.n_wg_logz), dim3(256), 0,
                          st, x, n, d, vec4, wp, wpb, cw, thr, well_idx, ill_idx, dmu, dh, cdir,
-                         counts, logz2, cslot, cr, llpart, bmask, iflag, lflag);
+                         counts, logz2, cslot, cr, bmask, iflag, lflag, hlist, smax);
   }
   tm = phase_mark(2, st) && tm;
   {
@@ -4602,7 +5343,7 @@ int estep_impl(const Layout& L, const float* x, const float* w, const float* mu,
     SPair* slist = at<SPair>(ws, L.off_slist);
     const size_t lds = (size_t)L.nb * sizeof(int);
     hipLaunchKernelGGL(k_sparse_count, dim3((unsigned)L.nunit), dim3(64), lds, st, cslot, n,
-                       L.upts, L.nb, L.lsbk, L.nunit, scnt);
+                       L.upts, L.nb, L.lsbk, L.nunit, scnt, logz2, llpart);
     hipLaunchKernelGGL(k_sparse_scan, dim3(1), dim3(1024), 0, st, scnt, L.nb * L.nunit, soff);
     hipLaunchKernelGGL(k_sparse_scatter, dim3((unsigned)L.nunit), dim3(64), scatter_lds(L.nb), st,
                        cslot, cr, n, L.upts, L.nb, L.lsbk, L.nunit, soff, slist);
@@ -4659,7 +5400,7 @@ int estep_impl(const Layout& L, const float* x, const float* w, const float* mu,
                        part_s, part_i, counts, well_idx, ill_idx, L.nch, L.wbk, L.nparts, L.sbk,
                        L.grid_i, L.ibk, L.ipt, n, k, d, D64, spos, part_x, scnt2, nk, s, q);
   }
-  hipLaunchKernelGGL(k_reduce_ll, dim3(1), dim3(1024), 0, st, llpart, L.n_wg_logz, loglik,
+  hipLaunchKernelGGL(k_reduce_ll, dim3(1), dim3(1024), 0, st, llpart, (int64_t)L.nunit, loglik,
                      ll_accumulate);
   const int rc = launch_status();
   if (rc != GMM_OK) return rc;
@@ -4755,7 +5496,7 @@ int kmeans_impl(const Layout& L, const float* x, int n_iters, float var_floor, f
                        cslot, cr);
     const size_t lds = (size_t)L.nb * sizeof(int);
     hipLaunchKernelGGL(k_sparse_count, dim3((unsigned)L.nunit), dim3(64), lds, st, cslot, n,
-                       L.upts, L.nb, L.lsbk, L.nunit, scnt);
+                       L.upts, L.nb, L.lsbk, L.nunit, scnt, nullptr, nullptr);
     hipLaunchKernelGGL(k_sparse_scan, dim3(1), dim3(1024), 0, st, scnt, L.nb * L.nunit, soff);
     hipLaunchKernelGGL(k_sparse_scatter, dim3((unsigned)L.nunit), dim3(64), scatter_lds(L.nb), st,
                        cslot, cr, n, L.upts, L.nb, L.lsbk, L.nunit, soff, slist);
