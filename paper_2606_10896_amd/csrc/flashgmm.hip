@@ -1919,8 +1919,15 @@ constexpr float kCoarseWindow = kDenseWindow;
 // a point and the candidates' sums another sixth, so that with fewer than about
 // half of the points light it would not pay (the first E-step of a fit at
 // n = 1.18e6, d = 100, k = 1024, 64 % heavy: 8.64 ms with it, 8.2 without).
-constexpr int kSampleWG = 64;
+constexpr int kSampleWG = 256;
 constexpr int64_t kSampleMin = (int64_t)1 << 18;
+// Heavy points of an assignment up to which they are done over all components.
+constexpr int kFewHeavy = 512;
+// Candidate window of an assignment: what lies below is at most k 2^-40 of the
+// normaliser, and cannot be assigned to a rank j > 1 when tau >= 2^-40.
+constexpr float kAssignWindow = 40.0f;
+// Below this many points the waves of a workgroup share their points (SPLIT).
+constexpr int64_t kSplitMax = 65536;
 // steps of 32 k: [x | x^2], or x and one step for ||x||^2
 template <int D64, bool ISO>
 __host__ __device__ constexpr int coarse_steps() {
@@ -1933,15 +1940,28 @@ __host__ __device__ constexpr double coarse_ka(bool iso) { return iso ? 2.5 : 4.
 __host__ __device__ constexpr double coarse_eps(int D64, bool iso) {
   return 0x1p-7 * (1.0 + 0x1p-8) + (5.0 * (iso ? D64 / 32 : D64 / 16) + 16.0) * 0x1p-22;
 }
-// 16-point tiles per wave: the points' operands stay in registers, and two waves
-// share each SIMD
-__host__ __device__ constexpr int coarse_tiles(int D64) {
-  return D64 <= 128 ? 4 : (D64 <= 192 ? 3 : 2);
+// 16-point tiles per wave: the points' operands stay in registers; up to 256
+// dimensions two waves share each SIMD (256 registers each), above one has it
+// alone (512).
+__host__ __device__ constexpr int coarse_tiles(int D64, bool iso) {
+  return iso ? (D64 <= 128 ? 4
+                           : (D64 <= 192 ? 3 : (D64 <= 256 ? 2 : (D64 <= 512 ? 4 : (D64 <= 896 ? 3 : 2)))))
+             : (D64 <= 128 ? 4 : (D64 <= 192 ? 3 : (D64 <= 256 ? 2 : (D64 <= 384 ? 3 : (D64 <= 768 ? 2 : 1)))));
+}
+// Workgroups per compute unit.
+__host__ __device__ constexpr int coarse_wgs(int D64) { return D64 <= 256 ? 2 : 1; }
+// Operand pieces (steps) a wave of the SPLIT form reads ahead: a divisor of NS.
+__host__ __device__ constexpr int coarse_ring(int NS) {
+  for (int r = 8; r > 3; --r)
+    if (NS % r == 0) return r;
+  return NS;
 }
 
-// Groups of 16 components per LDS block (two blocks and two workgroups fit a
-// compute unit's LDS); kpad, a multiple of 64, is a multiple of it.
-__host__ __device__ constexpr int coarse_groups(int D64) { return D64 <= 128 ? 4 : 2; }
+// Groups of 16 components per LDS block (two blocks of every workgroup of a
+// compute unit fit its LDS); kpad, a multiple of 64, is a multiple of it.
+__host__ __device__ constexpr int coarse_groups(int D64) {
+  return D64 <= 128 ? 4 : (D64 <= 512 ? 2 : 1);
+}
 
 // Packed operand of k_coarse: wpc[(g * NS + s) * 64 + l] holds A[slot 16 g +
 // l % 16][k = 32 s + 8 (l / 16) + e], e = 0..7: W of dimension k for k < D64, P of
@@ -2063,30 +2083,40 @@ __device__ __forceinline__ f4v mfma16b(bf16x8 a, bf16x8 b, f4v c) {
 // bits carry the group, so that an update is four instructions: mask-and-or, two
 // medians, one maximum.  The updates of a group fill the issue slots between
 // the MFMAs of the next one (two accumulator sets).
-template <int D64, bool ISO>
-__global__ __launch_bounds__(256, 2) void k_coarse(
+// SPLIT (few points): the workgroup's waves share its 32 points instead and take
+// every fourth group each, reading the operand from L2 one group ahead; their
+// states meet in LDS at the end.  With 256 points a workgroup, n below about
+// 65536 would leave compute units without one.
+template <int D64, bool ISO, bool SPLIT>
+__global__ __launch_bounds__(256, SPLIT ? 1 : coarse_wgs(D64)) void k_coarse(
     const float* __restrict__ x, int64_t n, int d, const bf16x8* __restrict__ wpc,
     const float* __restrict__ cbias, const float* __restrict__ cb2, int* __restrict__ counts,
     float window, int64_t wg_step, int sample, int sample_max,
     unsigned short* __restrict__ cand, int64_t* __restrict__ hlist) {
-  constexpr int NS = coarse_steps<D64, ISO>(), NT = coarse_tiles(D64), PTS = 16 * NT;
+  constexpr int NS = coarse_steps<D64, ISO>(), NTF = coarse_tiles(D64, ISO);
+  constexpr int NT = SPLIT && NTF > 2 ? 2 : NTF;
+  constexpr int PTS = 16 * NT;                  // points a wave takes
   constexpr int NX = D64 / 32;                  // x steps
   constexpr int GPB = coarse_groups(D64);       // groups of 16 components a block
   constexpr int WB = GPB * NS;                  // 1 KB pieces of a block's operand
   constexpr float kKE = (float)(coarse_kd(ISO) * coarse_eps(D64, ISO));
   // two objects, so that reads of one do not wait for the loads into the other
-  __shared__ __align__(16) bf16x8 wbuf0[WB * 64];
-  __shared__ __align__(16) bf16x8 wbuf1[WB * 64];
+  __shared__ __align__(16) bf16x8 wbuf0[SPLIT ? 1 : WB * 64];
+  __shared__ __align__(16) bf16x8 wbuf1[SPLIT ? 1 : WB * 64];
   __shared__ __align__(16) float bbuf0[64];     // biases, in the first 16 GPB
   __shared__ __align__(16) float bbuf1[64];
-  __shared__ __align__(16) unsigned short clist[4 * PTS * kCand];
+  __shared__ __align__(16) unsigned short clist[(SPLIT ? 1 : 4) * PTS * kCand];
+  __shared__ float xlo[SPLIT ? 4 : 1][PTS];     // SPLIT: the waves' bounds, then their counts
   __shared__ int hcnt[4];
   __shared__ unsigned long long hbase;
   if (!sample && coarse_off(counts, sample_max)) return;
   const int n_c = counts[0] + counts[1], nkb = (n_c + 16 * GPB - 1) / (16 * GPB);
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int k4 = lane >> 4, col = lane & 15;
-  const int64_t p0 = (int64_t)blockIdx.x * wg_step * (4 * PTS) + wave * PTS;
+  const int64_t p0 =
+      SPLIT ? (int64_t)blockIdx.x * wg_step * PTS
+            : (int64_t)blockIdx.x * wg_step * (4 * PTS) + wave * PTS;
+  static_assert(!SPLIT || (PTS & (PTS - 1)) == 0, "tiles");
   auto stage = [&](int kb, bf16x8* buf, float* bb) {
 #pragma unroll
     for (int i = 0; i < (WB + 3) / 4; ++i) {
@@ -2103,7 +2133,7 @@ __global__ __launch_bounds__(256, 2) void k_coarse(
                                                               (lane & (16 * GPB - 1))),
           (__attribute__((address_space(3))) unsigned*)bb, 4, 0, 0);
   };
-  if (nkb > 0) stage(0, wbuf0, bbuf0);
+  if (!SPLIT && nkb > 0) stage(0, wbuf0, bbuf0);
   // the points' operands
   bf16x8 xr[NT][NS];
 #pragma unroll
@@ -2112,34 +2142,41 @@ __global__ __launch_bounds__(256, 2) void k_coarse(
     const float* xp = x + (row < n ? row : 0) * (int64_t)d;
     const int dd = row < n ? d : 0;
     float ssq = 0.0f;
-    float4 ld[NX][2];
-    if (d >= 4) {
+    constexpr int GS = NX < 8 ? NX : (NX % 8 == 0 ? 8 : 4);   // steps whose loads fly together
+    static_assert(NX % GS == 0, "load groups");
 #pragma unroll
-      for (int s = 0; s < NX; ++s)
+    for (int s0 = 0; s0 < NX; s0 += GS) {
+      float4 ld[GS][2];
+      if (d >= 4) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u) ld[s][u] = load4_row(xp, 32 * s + 8 * k4 + 4 * u, dd, x);
-    } else {
+        for (int s = 0; s < GS; ++s)
 #pragma unroll
-      for (int s = 0; s < NX; ++s) ld[s][0] = ld[s][1] = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    if (d & 3) {
+          for (int u = 0; u < 2; ++u)
+            ld[s][u] = load4_row(xp, 32 * (s0 + s) + 8 * k4 + 4 * u, dd, x);
+      } else {
 #pragma unroll
-      for (int s = 0; s < NX; ++s)
-#pragma unroll
-        for (int u = 0; u < 2; ++u) load4_tail(xp, 32 * s + 8 * k4 + 4 * u, dd, ld[s][u]);
-    }
-#pragma unroll
-    for (int s = 0; s < NX; ++s) {
-      const float v[8] = {ld[s][0].x, ld[s][0].y, ld[s][0].z, ld[s][0].w,
-                          ld[s][1].x, ld[s][1].y, ld[s][1].z, ld[s][1].w};
-      float q8 = 0.0f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        xr[t][s][e] = (__bf16)v[e];
-        if constexpr (ISO) q8 = __fmaf_rn(v[e], v[e], q8);
-        else xr[t][NX + s][e] = (__bf16)(v[e] * v[e]);
+        for (int s = 0; s < GS; ++s) ld[s][0] = ld[s][1] = make_float4(0.f, 0.f, 0.f, 0.f);
       }
-      ssq += q8;
+      if (d & 3) {
+#pragma unroll
+        for (int s = 0; s < GS; ++s)
+#pragma unroll
+          for (int u = 0; u < 2; ++u)
+            load4_tail(xp, 32 * (s0 + s) + 8 * k4 + 4 * u, dd, ld[s][u]);
+      }
+#pragma unroll
+      for (int s = 0; s < GS; ++s) {
+        const float v[8] = {ld[s][0].x, ld[s][0].y, ld[s][0].z, ld[s][0].w,
+                            ld[s][1].x, ld[s][1].y, ld[s][1].z, ld[s][1].w};
+        float q8 = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          xr[t][s0 + s][e] = (__bf16)v[e];
+          if constexpr (ISO) q8 = __fmaf_rn(v[e], v[e], q8);
+          else xr[t][NX + s0 + s][e] = (__bf16)(v[e] * v[e]);
+        }
+        ssq += q8;
+      }
     }
     if constexpr (ISO) {
       float nrm = ssq + __shfl_xor(ssq, 16);
@@ -2183,7 +2220,9 @@ __global__ __launch_bounds__(256, 2) void k_coarse(
   // The block's groups, group g's log-densities going into acc[g % 2] while
   // group g - 1 (the other set) is taken in; operand pieces are read three
   // steps ahead, across the groups.
-  auto block = [&](int kb, const bf16x8* cur, const float* cb, bf16x8* nxt, float* nb) {
+  auto block = [&](auto pc, int kb, const bf16x8* cur, const float* cb, bf16x8* nxt,
+                   float* nb) {
+    constexpr int PAR = decltype(pc)::value;    // parity of the block's first group
     constexpr int NV = 8 * NT, NM = NS * NT;    // half updates and MFMAs a group
     // this wave's share of block kb has arrived (the barrier alone does not
     // wait for loads into LDS), then everybody's; block kb - 1 is done with
@@ -2198,13 +2237,13 @@ __global__ __launch_bounds__(256, 2) void k_coarse(
 #pragma unroll
     for (int q = 0; q < RW - 1; ++q) w[q] = wl[64 * q];
     f4v bias[2];
-    bias[0] = *reinterpret_cast<const f4v*>(bl);
+    bias[PAR] = *reinterpret_cast<const f4v*>(bl);
 #pragma unroll
     for (int q = 0; q < WB; ++q) {
-      const int gi = q / NS, s = q % NS, A = gi & 1;
+      const int gi = q / NS, s = q % NS, A = (gi + PAR) & 1;
       if (q + RW - 1 < WB) w[(q + RW - 1) % RW] = wl[64 * (q + RW - 1)];
       if (s == NS - 2 && gi + 1 < GPB)
-        bias[(gi + 1) & 1] = *reinterpret_cast<const f4v*>(bl + 16 * (gi + 1));
+        bias[(gi + 1 + PAR) & 1] = *reinterpret_cast<const f4v*>(bl + 16 * (gi + 1));
       const int g = GPB * kb + gi;
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
@@ -2216,22 +2255,56 @@ __global__ __launch_bounds__(256, 2) void k_coarse(
       }
     }
   };
-  for (int kb = 0; kb + 1 < nkb; kb += 2) {
-    block(kb, wbuf0, bbuf0, wbuf1, bbuf1);
-    block(kb + 1, wbuf1, bbuf1, wbuf0, bbuf0);
-  }
-  if (nkb & 1) block(nkb - 1, wbuf0, bbuf0, wbuf1, bbuf1);
+  if constexpr (SPLIT) {
+    const int ng = GPB * nkb;
+    constexpr int RS = coarse_ring(NS);
+    bf16x8 w[RS];
+    for (int g = wave; g < ng; g += 4) {
+      const bf16x8* wl = wpc + (size_t)g * NS * 64 + lane;
+      const bf16x8* wn = g + 4 < ng ? wl + (size_t)4 * NS * 64 : wl;
+      const f4v bias = *reinterpret_cast<const f4v*>(cbias + (size_t)g * 16 + 4 * k4);
+      if (g == wave) {
 #pragma unroll
-  for (int t = 0; t < NT; ++t)
+        for (int q = 0; q < RS; ++q) w[q] = wl[64 * q];
+      }
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      take(0, t, v, acc[1][t][v], nkb > 0 ? GPB * nkb - 1 : 0);
-      take(1, t, v, 0.0f, 0);
+      for (int q = 0; q < NS; ++q) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+          acc[0][t] = mfma16b(w[q % RS], xr[t][q], q == 0 ? bias : acc[0][t]);
+        w[q % RS] = q + RS < NS ? wl[64 * (q + RS)] : wn[64 * (q + RS - NS)];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          take(0, t, v, acc[0][t][v], g);
+          take(1, t, v, 0.0f, 0);
+        }
     }
+  } else {
+    constexpr std::integral_constant<int, 0> even{};
+    constexpr std::integral_constant<int, GPB & 1> odd{};
+    for (int kb = 0; kb + 1 < nkb; kb += 2) {
+      block(even, kb, wbuf0, bbuf0, wbuf1, bbuf1);
+      block(odd, kb + 1, wbuf1, bbuf1, wbuf0, bbuf0);
+    }
+    if (nkb & 1) block(even, nkb - 1, wbuf0, bbuf0, wbuf1, bbuf1);
+    // the last group: in acc[0] after an odd number of groups
+    const bool last0 = (GPB & 1) != 0 && (nkb & 1) != 0;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        take(0, t, v, last0 ? acc[0][t][v] : acc[1][t][v], nkb > 0 ? GPB * nkb - 1 : 0);
+        take(1, t, v, 0.0f, 0);
+      }
+  }
   // per point (its four lanes agree on everything below): the best lower bound,
   // the threshold, the candidates
   const float dlt = __uint_as_float((unsigned)(127 - 22 + nbits) << 23);   // 2^(nbits - 22)
-  unsigned short* const cl = clist + wave * PTS * kCand;
+  unsigned short* const cl = clist + (SPLIT ? 0 : wave * PTS * kCand);
   auto slot_of = [&](float u, int v) {
     return (int)(__float_as_uint(u) & imask) * 16 + 4 * k4 + v;
   };
@@ -2248,61 +2321,109 @@ __global__ __launch_bounds__(256, 2) void k_coarse(
     v = fmaxf(v, __shfl_xor(v, 16));
     return fmaxf(v, __shfl_xor(v, 32));
   };
+  // SPLIT: the largest of the four waves' values per point
+  auto meet = [&](float (&v)[NT]) {
+    if constexpr (SPLIT) {
+      __syncthreads();
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        if (k4 == 0) xlo[wave][16 * t + col] = v[t];
+      __syncthreads();
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        v[t] = fmaxf(fmaxf(xlo[0][16 * t + col], xlo[1][16 * t + col]),
+                     fmaxf(xlo[2][16 * t + col], xlo[3][16 * t + col]));
+    }
+  };
+  float lo[NT];
+  int bv[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
     float best = kEmpty;
-    int bv = 0;
+    bv[t] = 0;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       if (m1[t][v] > best) {
         best = m1[t][v];
-        bv = v;
+        bv[t] = v;
       }
     }
-    float lo = best > -1e30f ? lower(best, bv) : -INFINITY;
-    lo = max4(lo);
-    float T = thresh(lo);
+    lo[t] = max4(best > -1e30f ? lower(best, bv[t]) : -INFINITY);
+  }
+  meet(lo);
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const float T = thresh(lo[t]);
 #pragma unroll
     for (int v = 0; v < 4; ++v)
-      if (m1[t][v] >= T && v != bv) lo = fmaxf(lo, lower(m1[t][v], v));
-    lo = max4(lo);
-    T = thresh(lo);
+      if (m1[t][v] >= T && v != bv[t]) lo[t] = fmaxf(lo[t], lower(m1[t][v], v));
+    lo[t] = max4(lo[t]);
+  }
+  meet(lo);
+  int cpos[NT], ctot[NT];                       // this lane's first place, candidates in all
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const float T = thresh(lo[t]);
     int c = 0;
-    bool over = !(fabsf(lo) < 1e30f);           // nothing finite, or NaN
+    bool over = false;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       c += (m1[t][v] >= T ? 1 : 0) + (m2[t][v] >= T ? 1 : 0);
       over = over || m3[t][v] >= T;
     }
+    // a full lane state counts as too many (the exchanges are made by every
+    // lane: one that skipped them would read as 0)
+    c += over ? 64 : 0;
     const int c1 = __shfl_xor(c, 16), cc = c + c1, c2 = __shfl_xor(cc, 32);
+    cpos[t] = ((k4 & 1) != 0 ? c1 : 0) + ((k4 & 2) != 0 ? c2 : 0);
+    ctot[t] = cc + c2;
+  }
+  if constexpr (SPLIT) {
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+      if (k4 == 0) xlo[wave][16 * t + col] = (float)ctot[t];
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      ctot[t] = 0;
+      for (int w = 0; w < 4; ++w) {
+        const int cw = (int)xlo[w][16 * t + col];
+        if (w < wave) cpos[t] += cw;
+        ctot[t] += cw;
+      }
+    }
+  }
+  const bool writer = !SPLIT || wave == 0;      // the wave that writes its points' lists
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
     const bool live = p0 + 16 * t + col < n;
-    // (no candidate at all: bounds that contradict each other; the point is
-    // listed in one of the two places in every case)
-    over = over || cc + c2 > kCand || cc + c2 == 0;
-    // (every lane takes part in the exchange: a lane that skipped it would read as 0)
-    int ov = over ? 1 : 0;
-    ov |= __shfl_xor(ov, 16);
-    ov |= __shfl_xor(ov, 32);
-    over = ov != 0 && live;
-    hv[t] = __ballot(over && k4 == 0);
+    // heavy: too many, bounds that are not finite, or no candidate at all (bounds
+    // that contradict each other); every point is listed in one of the two places
+    const bool over =
+        live && (ctot[t] > kCand || ctot[t] == 0 || !(fabsf(lo[t]) < 1e30f));
+    hv[t] = writer ? __ballot(over && k4 == 0) : 0ull;
     if (sample) continue;
     unsigned short* const my = cl + (16 * t + col) * kCand;
     // kNoSlot everywhere; a heavy point's list stays empty
-    if (k4 == 0) {
+    if (writer && k4 == 0) {
 #pragma unroll
       for (int j = 0; j < kCand; ++j) my[j] = kNoSlot;
     }
-    __builtin_amdgcn_wave_barrier();
+    if constexpr (SPLIT) __syncthreads();
+    else __builtin_amdgcn_wave_barrier();
     if (!over && live) {
-      int pos = ((k4 & 1) != 0 ? c1 : 0) + ((k4 & 2) != 0 ? c2 : 0);
+      const float T = thresh(lo[t]);
+      int pos = cpos[t];
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         if (m1[t][v] >= T) my[pos++] = (unsigned short)slot_of(m1[t][v], v);
         if (m2[t][v] >= T) my[pos++] = (unsigned short)slot_of(m2[t][v], v);
       }
     }
-    __builtin_amdgcn_wave_barrier();
-    if (k4 == 0 && live) {
+    if constexpr (SPLIT) __syncthreads();
+    else __builtin_amdgcn_wave_barrier();
+    if (writer && k4 == 0 && live) {
       ushort4 o[2];
       o[0] = make_ushort4(my[0], my[1], my[2], my[3]);
       o[1] = make_ushort4(my[4], my[5], my[6], my[7]);
@@ -2513,6 +2634,68 @@ __global__ __launch_bounds__(256) void k_refine(
     lflag[nn] = 0;
     if (bmask != nullptr) bmask[nn] = ((unsigned long long)bhi << 32) | blo;
   }
+}
+
+// Assignment outputs of the points whose candidates are listed (window >= 40
+// log2 units, or m = 1): the candidates ranked by their exact log-densities
+// (ties to the lower index), the normaliser their sum (the others are below k
+// 2^-window of it).  Rank j > 1 needs r > tau >= 2^-40, so that every
+// component that can be assigned is a candidate.
+template <int D64>
+__global__ __launch_bounds__(256) void k_assign_refine(
+    const float* __restrict__ x, int64_t n, int d, const unsigned short* __restrict__ cand,
+    const int* __restrict__ cidx, const float* __restrict__ dmu, const double* __restrict__ dh,
+    const double* __restrict__ cdir, const int* __restrict__ counts, int sample_max, int m,
+    float tau, int* __restrict__ idx, float* __restrict__ resp, int* __restrict__ ovf) {
+  constexpr int G = refine_lanes(D64);
+  if (coarse_off(counts, sample_max)) return;
+  const int lane = threadIdx.x & 63, g = lane & (G - 1);
+  const int64_t nn = ((int64_t)blockIdx.x * 256 + threadIdx.x) / G;
+  uint4 list = make_uint4(~0u, ~0u, ~0u, ~0u);
+  if (nn < n) list = *reinterpret_cast<const uint4*>(cand + nn * kCand);
+  const bool light = (list.x & 0xFFFFu) != kNoSlot;
+  if (__ballot(light) == 0ull) return;
+  double my;
+  int slot;
+  refine_point<D64>(x, light ? nn : 0, d, list, g, cidx, dmu, dh, cdir, my, slot);
+  // the candidates sit in lanes g = 0..7
+  double mx = my;
+  mx = fmax(mx, xshfl<1>(mx));
+  mx = fmax(mx, xshfl<2>(mx));
+  mx = fmax(mx, xshfl<4>(mx));
+  const bool has = slot != kNoSlot;
+  const double e = has ? exp2(my - mx) : 0.0;
+  double sum = e;
+  sum += xshfl<1>(sum);
+  sum += xshfl<2>(sum);
+  sum += xshfl<4>(sum);
+  const int comp = has ? cidx[slot] : INT_MAX;  // empty places rank last, by place
+  int rank = 0;
+  auto count = [&](auto oc) {
+    constexpr int off = decltype(oc)::value;
+    double ol = my;
+    int ocmp = comp;
+    if constexpr (off & 1) { ol = xshfl<1>(ol); ocmp = xshfl_i<1>(ocmp); }
+    if constexpr (off & 2) { ol = xshfl<2>(ol); ocmp = xshfl_i<2>(ocmp); }
+    if constexpr (off & 4) { ol = xshfl<4>(ol); ocmp = xshfl_i<4>(ocmp); }
+    const bool tie = ol == my && (ocmp < comp || (ocmp == comp && (g ^ off) < g));
+    rank += (ol > my || tie) ? 1 : 0;
+  };
+  count(std::integral_constant<int, 1>{});
+  count(std::integral_constant<int, 2>{});
+  count(std::integral_constant<int, 3>{});
+  count(std::integral_constant<int, 4>{});
+  count(std::integral_constant<int, 5>{});
+  count(std::integral_constant<int, 6>{});
+  count(std::integral_constant<int, 7>{});
+  if (!light) return;
+  if (g < kCand && rank < m) {
+    const double r = e / sum;
+    const bool take = has && (rank == 0 || r > (double)tau);
+    idx[nn * m + rank] = take ? comp : -1;
+    resp[nn * m + rank] = take ? (float)r : 0.0f;
+  }
+  if (g == 0) ovf[nn] = 0;
 }
 
 // ---------------------------------------------------------------- Step 2: statistics, well set
@@ -3820,19 +4003,6 @@ __host__ __device__ constexpr float split_eps(int D64) {
   return 2.0f * (3.0f * 0x1p-16f + (3.0f * D64 / 8.0f + 8.0f) * 0x1p-24f);
 }
 
-// fp64 direct-form log-density (natural log) of component comp at point xr
-// (fp32 row, LDS or global memory), from the caller's fp32 parameters and the
-// fp64 constant cdir (log2 units).
-__device__ __forceinline__ double ell64(const float* xr, const float* __restrict__ mu,
-                                        const float* __restrict__ var, double cdir_k, int d) {
-  double acc = 0.0;
-  for (int j = 0; j < d; ++j) {
-    const double t = (double)xr[j] - (double)mu[j];
-    acc += t * t / (double)var[j];
-  }
-  return cdir_k * kLn2 - 0.5 * acc;
-}
-
 // Per well slot, the terms of its error bound: (cdir_j, A_j) in log2 units;
 // (-inf, 0) for the padding slots.
 __global__ __launch_bounds__(256) void k_assign_slots(const double* __restrict__ cwell,
@@ -3853,12 +4023,12 @@ __global__ __launch_bounds__(256) void k_assign_slots(const double* __restrict__
 }
 
 // Split X tile of the bf16 screening (the [x | x^2] layout of k_logz) from
-// rows n0 .. n0 + 63; rows >= n and dimensions >= d are zero.  The whole
+// rows row_of(0) .. row_of(63); rows >= n and dimensions >= d are zero.  The whole
 // chunks of every thread are loaded first (one memory round trip), the
 // partial ones value by value.
-template <int D64>
+template <int D64, class Row>
 __device__ __forceinline__ void split_tile(const float* __restrict__ x, int64_t n, int d,
-                                           int vec4, int64_t n0, bf16x8* xa) {
+                                           int vec4, Row&& row_of, bf16x8* xa) {
   constexpr int NC8 = D64 / 8, PTS = 64, NIT = (PTS * NC8 + 255) / 256;
   const int tid = threadIdx.x;
   float4 ld[NIT][2];
@@ -3866,7 +4036,7 @@ __device__ __forceinline__ void split_tile(const float* __restrict__ x, int64_t 
 #pragma unroll
   for (int it = 0; it < NIT; ++it) {
     const int t = tid + 256 * it, p = t / NC8, c = t % NC8;
-    const int64_t row = n0 + p;
+    const int64_t row = row_of(p);
     whole[it] = vec4 && t < PTS * NC8 && row < n && 8 * c + 8 <= d;
     if (whole[it]) {
       ld[it][0] = *reinterpret_cast<const float4*>(x + row * d + 8 * c);
@@ -3877,7 +4047,7 @@ __device__ __forceinline__ void split_tile(const float* __restrict__ x, int64_t 
   for (int it = 0; it < NIT; ++it) {
     const int t = tid + 256 * it, p = t / NC8, c = t % NC8;
     if (t >= PTS * NC8) continue;
-    const int64_t row = n0 + p;
+    const int64_t row = row_of(p);
     float v[8];
     if (whole[it]) {
       v[0] = ld[it][0].x; v[1] = ld[it][0].y; v[2] = ld[it][0].z; v[3] = ld[it][0].w;
@@ -3990,7 +4160,7 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_assign_theta(
     const float* __restrict__ x, int64_t n, int d, int vec4, const float4* __restrict__ wp,
     const bf16x8* __restrict__ wpb, const float* __restrict__ cw,
     const float2* __restrict__ ca, const int* __restrict__ counts, int tsel,
-    float2* __restrict__ theta) {
+    const int64_t* __restrict__ hlist, int sample_max, float2* __restrict__ theta) {
   constexpr int P = D64 + 4, NT = logz_tiles(D64), PTS = 32 * NT;
   // SPL: split tile in LDS; SPB: split-bf16 screening (from the split tile or,
   // D64 > 256, from the fp32 tile), whose thresholds need the arg-max slots
@@ -4010,8 +4180,16 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_assign_theta(
   float2* const lma = reinterpret_cast<float2*>(smem);                     // [PTS][129]
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, h = lane >> 5, col = lane & 31;
   const int64_t n0 = (int64_t)blockIdx.x * PTS;
-  if constexpr (SPL) split_tile<D64>(x, n, d, vec4, n0, xa);
-  else load_tile<D64>(x, n, d, [=](int r) { return n0 + r; }, PTS, xs, vec4 != 0);
+  // the points taken: the heavy ones of the one-product screening, or all
+  const bool whole = hlist == nullptr || coarse_off(counts, sample_max);
+  const int64_t np = whole ? n : heavy_count(counts);
+  if (n0 >= np || (!whole && np <= kFewHeavy)) return;
+  auto row_of = [&](int p) -> int64_t {
+    if (n0 + p >= np) return n;
+    return whole ? n0 + p : hlist[n0 + p];
+  };
+  if constexpr (SPL) split_tile<D64>(x, n, d, vec4, row_of, xa);
+  else load_tile<D64>(x, n, d, row_of, PTS, xs, vec4 != 0);
   __syncthreads();
   float m0[16], m1[16];
   int a0[16], a1[16];
@@ -4088,7 +4266,7 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_assign_theta(
       for (int j = 0; j < TL; ++j)
         if (ol[j] > tl[TL - 1]) insert(ol[j], oa[j]);
     }
-    if (r != 0 || n0 + p >= n) return;
+    if (r != 0 || n0 + p >= np) return;
     float st = -INFINITY;
 #pragma unroll
     for (int j = 0; j < TL; ++j)
@@ -4110,7 +4288,7 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_assign_theta(
     } else {
       out = make_float2(st - 2.0f * kScreenSlack, st - 2.0f * kScreenSlack);
     }
-    theta[n0 + p] = out;
+    theta[row_of(p)] = out;
   }
 }
 
@@ -4123,7 +4301,8 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_assign_collect
     const double* __restrict__ dh, const int* __restrict__ counts,
     const float2* __restrict__ theta, const float* __restrict__ mu,
     const float* __restrict__ var, const double* __restrict__ cdir, int m, float tau,
-    int* __restrict__ idx, float* __restrict__ resp, int* __restrict__ ovf) {
+    const int64_t* __restrict__ hlist, int sample_max, int* __restrict__ idx,
+    float* __restrict__ resp, int* __restrict__ ovf) {
   constexpr int P = D64 + 4, NT = logz_tiles(D64), PTS = 32 * NT;
   constexpr bool SPL = screen_b16(D64);
   constexpr int RPV = 4 * screen_steps<D64, false>() + 1;
@@ -4138,22 +4317,35 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_assign_collect
   __shared__ int cand[PTS][kACap];         // well slot s >= 0, or -(ill component + 1)
   __shared__ float2 stw[4][PTS];
   __shared__ float2 sti[4][PTS];
+  __shared__ int64_t prow[PTS];            // row of each point (n past the last one)
   float* const xs = reinterpret_cast<float*>(smem);
   bf16x8* const xa = reinterpret_cast<bf16x8*>(smem);
   double* const cl = reinterpret_cast<double*>(smem + (SPL ? 0 : XB));    // [PTS][kACap]
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, h = lane >> 5, col = lane & 31;
   const int64_t n0 = (int64_t)blockIdx.x * PTS;
-  if constexpr (SPL) split_tile<D64>(x, n, d, vec4, n0, xa);
-  else load_tile<D64>(x, n, d, [=](int r) { return n0 + r; }, PTS, xs, vec4 != 0);
-  if (tid < PTS) ccnt[tid] = 0;
+  // the points taken: the heavy ones of the one-product screening, or all
+  const bool whole = hlist == nullptr || coarse_off(counts, sample_max);
+  const int64_t np = whole ? n : heavy_count(counts);
+  if (n0 >= np || (!whole && np <= kFewHeavy)) return;
+  auto row_of = [&](int p) -> int64_t {
+    if (n0 + p >= np) return n;
+    return whole ? n0 + p : hlist[n0 + p];
+  };
+  if constexpr (SPL) split_tile<D64>(x, n, d, vec4, row_of, xa);
+  else load_tile<D64>(x, n, d, row_of, PTS, xs, vec4 != 0);
+  if (tid < PTS) {
+    ccnt[tid] = 0;
+    prow[tid] = row_of(tid);
+  }
   __syncthreads();
   const int n_wkb = counts[2], n_ill = counts[1];
   float th0[16], th1[16], m0[16], s0[16], m1[16], s1[16];
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
     const int p = 8 * (v >> 2) + 4 * h + (v & 3);
-    th0[v] = n0 + p < n ? theta[n0 + p].x : INFINITY;
-    th1[v] = (NT == 2 && n0 + 32 + p < n) ? theta[n0 + 32 + p].x : INFINITY;
+    th0[v] = prow[p] < n ? theta[prow[p]].x : INFINITY;
+    th1[v] = INFINITY;
+    if constexpr (NT == 2) th1[v] = prow[32 + p] < n ? theta[prow[32 + p]].x : INFINITY;
     m0[v] = m1[v] = kEmpty;
     s0[v] = s1[v] = 0.0f;
   }
@@ -4216,7 +4408,7 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_assign_collect
     // than 64 log2 units below the point's threshold (so below 2^-62 of its
     // mass) is left out of the normaliser: its sum stops early (most of them
     // after 16 dimensions), as in k_logz.
-    const int64_t row = n0 + lane;
+    const int64_t row = prow[lane];
     const float thl = row < n ? theta[row].y : INFINITY;
     const float* xr = SPL ? x + (row < n ? row : 0) * d : xs + lane * P;
     float mi = kEmpty, si = 0.0f;
@@ -4265,7 +4457,7 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_assign_collect
     for (int p = 0; p < PTS; ++p) {
       eoff[p] = acc;
       const int c = ccnt[p];
-      acc += (c <= kACap && n0 + p < n) ? c : 0;
+      acc += (c <= kACap && prow[p] < n) ? c : 0;
     }
     eoff[PTS] = acc;
   }
@@ -4287,7 +4479,7 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_assign_collect
       const int j = e - eoff[p];
       const int code = cand[p][j];
       const int comp = code >= 0 ? well_idx[code] : -code - 1;
-      const float* xr = SPL ? x + (n0 + p) * d : xs + p * P;
+      const float* xr = SPL ? x + prow[p] * d : xs + p * P;
       const float* mu = dmu + (size_t)comp * D64;
       const double* hh = dh + (size_t)comp * D64;
       const bool v4 = !SPL || vec4;
@@ -4316,9 +4508,9 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_assign_collect
     }
   }
   __syncthreads();
-  if (tid < PTS && n0 + tid < n) {
+  if (tid < PTS && prow[tid] < n) {
     const int p = tid;
-    const int64_t nn = n0 + p;
+    const int64_t nn = prow[p];
     const int cnt = ccnt[p];
     if (cnt > kACap) {
       ovf[nn] = 1;
@@ -4373,85 +4565,151 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_assign_collect
   }
 }
 
-// Points whose candidate list overflowed: every component's log-density in
-// fp64, thread t taking components t, t + 256, ...; per-thread top-m lists and
-// log-sum-exp states merged by one thread in thread order.
+// Points done exactly over every component in fp64: those whose candidate list
+// overflowed, and the heavy points of the one-product screening when there are
+// at most kFewHeavy of them (one workgroup a point, which takes less time than
+// one workgroup of the two screening passes).  Eight lanes share a component's
+// direct-form sum (coalesced parameter rows: one thread a component took 1.1 ms
+// for 30 points of 128 dimensions at k = 1024), kFbBatch components at a time so
+// that their loads fly together; every group keeps a top-m list and a log-sum-exp
+// state of its components in ascending order, and the groups' are merged by
+// m block-wide arg-max rounds and fixed-order sums.
+constexpr int kFbBatch = 4;
 __global__ __launch_bounds__(256) void k_assign_fallback(
-    const float* __restrict__ x, int64_t n, int d, int k, const float* __restrict__ mu,
-    const float* __restrict__ var, const double* __restrict__ cdir, int m, float tau,
-    const int* __restrict__ ovf, int* __restrict__ idx, float* __restrict__ resp) {
-  __shared__ float xr[GMM_MAX_D];
+    const float* __restrict__ x, int64_t n, int d, int D64, int k, const float* __restrict__ dmu,
+    const double* __restrict__ dh, const double* __restrict__ cdir, int m, float tau,
+    const int* __restrict__ ovf, const int* __restrict__ counts,
+    const int64_t* __restrict__ hlist, int sample_max, int* __restrict__ idx,
+    float* __restrict__ resp) {
+  constexpr int G = 8, NGR = 256 / G;
+  __shared__ __align__(16) float xr[GMM_MAX_D];
   __shared__ int plist[1024];
   __shared__ int pcnt;
-  __shared__ double lm[256], ls[256];
-  __shared__ double ltl[256][GMM_MAX_M];
-  __shared__ int lti[256][GMM_MAX_M];
-  const int tid = threadIdx.x;
+  __shared__ double wl[2][4];
+  __shared__ int wc[2][4];
+  __shared__ double wz[4];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = tid & (G - 1);
+  const int grp = tid / G;
   const int64_t b0 = (int64_t)blockIdx.x * 1024;
+  const bool off = coarse_off(counts, sample_max);
+  // every point of a call that small (the two passes were not launched)
+  const bool each = hlist != nullptr && off && n <= kFewHeavy;
+  const bool few = each || (hlist != nullptr && !off && heavy_count(counts) <= kFewHeavy);
+  if (!few && b0 >= n) return;
   if (tid == 0) pcnt = 0;
   __syncthreads();
   // the order of the list does not matter: every point's result is its own
-  for (int i = tid; i < 1024; i += 256)
-    if (b0 + i < n && ovf[b0 + i]) plist[atomicAdd(&pcnt, 1)] = i;
+  if (few) {
+    // the light points' lists never overflow; entries blockIdx.x, + gridDim.x, ...
+    const int hc = each ? (int)n : (int)heavy_count(counts);
+    if (tid == 0) pcnt = hc > (int)blockIdx.x ? (hc - 1 - (int)blockIdx.x) / (int)gridDim.x + 1 : 0;
+  } else {
+    for (int i = tid; i < 1024; i += 256)
+      if (b0 + i < n && ovf[b0 + i]) plist[atomicAdd(&pcnt, 1)] = i;
+  }
   __syncthreads();
   const int np = pcnt;
   for (int ip = 0; ip < np; ++ip) {
-    const int64_t nn = b0 + plist[ip];
-    for (int j = tid; j < d; j += 256) xr[j] = x[nn * d + j];
+    const int64_t i = blockIdx.x + (int64_t)ip * gridDim.x;
+    const int64_t nn = each ? i : (few ? hlist[i] : b0 + plist[ip]);
+    for (int j = tid; j < D64; j += 256) xr[j] = j < d ? x[nn * d + j] : 0.0f;
     __syncthreads();
     double tl[GMM_MAX_M];
     int ti[GMM_MAX_M];
 #pragma unroll
-    for (int j = 0; j < GMM_MAX_M; ++j) { tl[j] = -INFINITY; ti[j] = -1; }
-    double mx = -INFINITY, sm = 0.0;
-    for (int comp = tid; comp < k; comp += 256) {
-      const double l = ell64(xr, mu + (size_t)comp * d, var + (size_t)comp * d, cdir[comp], d);
-      if (!(l > -INFINITY)) continue;
-      if (l > mx) { sm = sm * exp(mx - l) + 1.0; mx = l; }
-      else sm += exp(l - mx);
+    for (int j = 0; j < GMM_MAX_M; ++j) { tl[j] = -INFINITY; ti[j] = INT_MAX; }
+    double mx = -INFINITY, sm = 0.0;            // natural log
+    for (int c0 = grp; c0 < k; c0 += kFbBatch * NGR) {
+      double acc[kFbBatch];
 #pragma unroll
-      for (int q = GMM_MAX_M - 1; q >= 0; --q) {
-        // components arrive in increasing index order: ties keep the earlier
-        const bool above = ti[q] < 0 || l > tl[q];
-        const bool above_prev = q > 0 && (ti[q - 1] < 0 || l > tl[q - 1]);
-        if (above_prev) { tl[q] = tl[q - 1]; ti[q] = ti[q - 1]; }
-        else if (above) { tl[q] = l; ti[q] = comp; }
+      for (int u = 0; u < kFbBatch; ++u) acc[u] = 0.0;
+      for (int c4 = 4 * g; c4 < D64; c4 += 4 * G) {
+        const float4 xv = *reinterpret_cast<const float4*>(xr + c4);
+        float4 mv[kFbBatch];
+        double2 h0[kFbBatch], h1[kFbBatch];
+#pragma unroll
+        for (int u = 0; u < kFbBatch; ++u) {
+          const int comp = c0 + u * NGR < k ? c0 + u * NGR : c0;
+          mv[u] = *reinterpret_cast<const float4*>(dmu + (size_t)comp * D64 + c4);
+          h0[u] = *reinterpret_cast<const double2*>(dh + (size_t)comp * D64 + c4);
+          h1[u] = *reinterpret_cast<const double2*>(dh + (size_t)comp * D64 + c4 + 2);
+        }
+#pragma unroll
+        for (int u = 0; u < kFbBatch; ++u) {
+          double t;
+          t = (double)xv.x - (double)mv[u].x; acc[u] = fma(t * t, h0[u].x, acc[u]);
+          t = (double)xv.y - (double)mv[u].y; acc[u] = fma(t * t, h0[u].y, acc[u]);
+          t = (double)xv.z - (double)mv[u].z; acc[u] = fma(t * t, h1[u].x, acc[u]);
+          t = (double)xv.w - (double)mv[u].w; acc[u] = fma(t * t, h1[u].y, acc[u]);
+        }
       }
-    }
-    lm[tid] = mx;
-    ls[tid] = sm;
 #pragma unroll
-    for (int j = 0; j < GMM_MAX_M; ++j) { ltl[tid][j] = tl[j]; lti[tid][j] = ti[j]; }
-    __syncthreads();
-    if (tid == 0) {
-      double M = -INFINITY;
-      for (int t = 0; t < 256; ++t) M = fmax(M, lm[t]);
-      double z = 0.0;
-      for (int t = 0; t < 256; ++t)
-        if (lm[t] > -INFINITY) z += ls[t] * exp(lm[t] - M);
-      const double lz = M + log(z);
-      double bl[GMM_MAX_M];
-      int bi[GMM_MAX_M];
-      for (int j = 0; j < GMM_MAX_M; ++j) { bl[j] = -INFINITY; bi[j] = -1; }
-      for (int t = 0; t < 256; ++t)
-        for (int j2 = 0; j2 < GMM_MAX_M; ++j2) {
-          const int c = lti[t][j2];
-          if (c < 0) break;
-          const double l = ltl[t][j2];
+      for (int u = 0; u < kFbBatch; ++u) {
+        const int comp = c0 + u * NGR;
+        const double a = group_sum<G>(acc[u]);
+        if (comp >= k) continue;                // the same for the group's lanes
+        const double l = kLn2 * (cdir[comp] - a);
+        if (!(l > -INFINITY)) continue;
+        if (l > mx) { sm = sm * exp(mx - l) + 1.0; mx = l; }
+        else sm += exp(l - mx);
+        // components arrive in increasing index order: ties keep the earlier
+        if (l > tl[GMM_MAX_M - 1] || ti[GMM_MAX_M - 1] == INT_MAX) {
+#pragma unroll
           for (int q = GMM_MAX_M - 1; q >= 0; --q) {
-            const bool above = bi[q] < 0 || l > bl[q] || (l == bl[q] && c < bi[q]);
-            const bool above_prev =
-                q > 0 && (bi[q - 1] < 0 || l > bl[q - 1] || (l == bl[q - 1] && c < bi[q - 1]));
-            if (above_prev) { bl[q] = bl[q - 1]; bi[q] = bi[q - 1]; }
-            else if (above) { bl[q] = l; bi[q] = c; }
+            const bool above = ti[q] == INT_MAX || l > tl[q];
+            const bool above_prev = q > 0 && (ti[q - 1] == INT_MAX || l > tl[q - 1]);
+            if (above_prev) { tl[q] = tl[q - 1]; ti[q] = ti[q - 1]; }
+            else if (above) { tl[q] = l; ti[q] = comp; }
           }
         }
-      for (int j = 0; j < m; ++j) {
+      }
+    }
+    // rank j: the largest list head (ties to the lower component), whose group
+    // drops it; the normaliser after the first round
+    double lz = 0.0;
+    for (int j = 0; j < m; ++j) {
+      double bl = tl[0];
+      int bc = ti[0];
+      auto pick = [&](double ol, int oc) {
+        const bool o = oc != INT_MAX && (bc == INT_MAX || ol > bl || (ol == bl && oc < bc));
+        bl = o ? ol : bl;
+        bc = o ? oc : bc;
+      };
+      pick(xshfl<8>(bl), xshfl_i<8>(bc));
+      pick(xshfl<16>(bl), xshfl_i<16>(bc));
+      pick(__shfl_xor(bl, 32), __shfl_xor(bc, 32));
+      if (lane == 0) {
+        wl[j & 1][wave] = bl;
+        wc[j & 1][wave] = bc;
+      }
+      __syncthreads();
+      bl = wl[j & 1][0];
+      bc = wc[j & 1][0];
+      for (int w = 1; w < 4; ++w) pick(wl[j & 1][w], wc[j & 1][w]);
+      if (j == 0) {
+        double z = mx > -INFINITY ? sm * exp(mx - bl) : 0.0;
+        z += xshfl<8>(z);
+        z += xshfl<16>(z);
+        z += __shfl_xor(z, 32);
+        if (lane == 0) wz[wave] = z;
+        __syncthreads();
+        lz = bl + log(((wz[0] + wz[1]) + wz[2]) + wz[3]);
+      }
+      if (bc != INT_MAX && ti[0] == bc) {
+#pragma unroll
+        for (int q = 0; q + 1 < GMM_MAX_M; ++q) {
+          tl[q] = tl[q + 1];
+          ti[q] = ti[q + 1];
+        }
+        tl[GMM_MAX_M - 1] = -INFINITY;
+        ti[GMM_MAX_M - 1] = INT_MAX;
+      }
+      if (tid == 0) {
         int oi = -1;
         float orr = 0.0f;
-        if (bi[j] >= 0) {
-          const double r = exp(bl[j] - lz);
-          if (j == 0 || r > (double)tau) { oi = bi[j]; orr = (float)r; }
+        if (bc != INT_MAX) {
+          const double r = exp(bl - lz);
+          if (j == 0 || r > (double)tau) { oi = bc; orr = (float)r; }
         }
         idx[nn * m + j] = oi;
         resp[nn * m + j] = orr;
@@ -5212,22 +5470,30 @@ void launch_coarse(const Layout& L, const float* x, const float* mu, const float
                    float window, hipStream_t st, int* smax) {
   const CoarseView cv = coarse_view(L, ws);
   int* counts = at<int>(ws, L.off_counts);
-  constexpr int NS = coarse_steps<D64, ISO>(), WP = 4 * 16 * coarse_tiles(D64);
+  constexpr int NS = coarse_steps<D64, ISO>(), WP = 4 * 16 * coarse_tiles(D64, ISO);
+  constexpr int SP = 16 * (coarse_tiles(D64, ISO) > 2 ? 2 : coarse_tiles(D64, ISO));
   const int64_t tot = (int64_t)(L.kpad / 16) * NS * 64;
   hipLaunchKernelGGL((k_prep_pack_coarse<D64, ISO>), dim3((unsigned)cdiv(tot, 256)), dim3(256), 0,
                      st, mu, var, L.d, L.kpad, at<double>(ws, L.off_cwell),
                      at<double>(ws, L.off_cdir), counts, at<int>(ws, L.off_well_idx),
                      at<int>(ws, L.off_ill_idx), cv.wpc, cv.cbias, cv.cb2, cv.cidx);
-  const int64_t nwg = cdiv(L.n, WP);
   *smax = INT_MAX;
-  if (L.n >= kSampleMin) {
-    hipLaunchKernelGGL((k_coarse<D64, ISO>), dim3(kSampleWG), dim3(256), 0, st, x, L.n, L.d,
-                       cv.wpc, cv.cbias, cv.cb2, counts, window, nwg / kSampleWG, 1, INT_MAX, cv.cand,
-                       cv.hlist);
-    *smax = kSampleWG * WP / 2;
+  if (L.n < kSplitMax) {
+    hipLaunchKernelGGL((k_coarse<D64, ISO, true>), dim3((unsigned)cdiv(L.n, SP)), dim3(256), 0, st,
+                       x, L.n, L.d, cv.wpc, cv.cbias, cv.cb2, counts, window, (int64_t)1, 0,
+                       INT_MAX, cv.cand, cv.hlist);
+    return;
   }
-  hipLaunchKernelGGL((k_coarse<D64, ISO>), dim3((unsigned)nwg), dim3(256), 0, st, x, L.n, L.d,
-                     cv.wpc, cv.cbias, cv.cb2, counts, window, (int64_t)1, 0, *smax, cv.cand, cv.hlist);
+  const int64_t nwg = cdiv(L.n, WP);
+  if (L.n >= kSampleMin) {
+    hipLaunchKernelGGL((k_coarse<D64, ISO, true>), dim3(kSampleWG), dim3(256), 0, st, x, L.n, L.d,
+                       cv.wpc, cv.cbias, cv.cb2, counts, window, L.n / (kSampleWG * SP), 1,
+                       INT_MAX, cv.cand, cv.hlist);
+    *smax = kSampleWG * SP / 2;
+  }
+  hipLaunchKernelGGL((k_coarse<D64, ISO, false>), dim3((unsigned)nwg), dim3(256), 0, st, x, L.n,
+                     L.d, cv.wpc, cv.cbias, cv.cb2, counts, window, (int64_t)1, 0, *smax, cv.cand,
+                     cv.hlist);
 }
 
 template <int D64>
@@ -5307,7 +5573,7 @@ int estep_impl(const Layout& L, const float* x, const float* w, const float* mu,
   tm = phase_mark(1, st) && tm;
   const int64_t* hlist = nullptr;
   int smax = INT_MAX;
-  if constexpr (D64 <= 256) {
+  {
     if (L.iso) launch_coarse<D64, true>(L, x, mu, var, ws, kCoarseWindow, st, &smax);
     else launch_coarse<D64, false>(L, x, mu, var, ws, kCoarseWindow, st, &smax);
     hlist = coarse_view(L, ws).hlist;
@@ -5410,8 +5676,8 @@ int estep_impl(const Layout& L, const float* x, const float* w, const float* mu,
 
 template <int D64>
 int assign_impl(const Layout& L, const float* x, const float* w, const float* mu,
-                const float* var, int m, float tau, int* idx, float* resp, void* ws,
-                hipStream_t st) {
+                const float* var, int m, float tau, float window, int* idx, float* resp,
+                void* ws, hipStream_t st) {
   const int64_t n = L.n;
   const int d = L.d, k = L.k, kpad = L.kpad;
   int* counts = at<int>(ws, L.off_counts);
@@ -5449,17 +5715,38 @@ int assign_impl(const Layout& L, const float* x, const float* w, const float* mu
                          cwell, cdir, counts, well_idx, kpad, ca);
     }
   }
-  if (m + 2 <= 4)
-    hipLaunchKernelGGL((k_assign_theta<D64, 4>), dim3((unsigned)L.n_wg_logz), dim3(256), 0, st, x,
-                       n, d, vec4, wp, wpb, cw, ca, counts, m + 2, theta);
-  else
-    hipLaunchKernelGGL((k_assign_theta<D64, kTMax>), dim3((unsigned)L.n_wg_logz), dim3(256), 0, st,
-                       x, n, d, vec4, wp, wpb, cw, ca, counts, m + 2, theta);
-  hipLaunchKernelGGL(k_assign_collect<D64>, dim3((unsigned)L.n_wg_logz), dim3(256), 0, st, x, n,
-                     d, vec4, wp, wpb, cw, ca, well_idx, ill_idx, dmu, dh, counts, theta, mu, var,
-                     cdir, m, tau, idx, resp, ovf);
-  hipLaunchKernelGGL(k_assign_fallback, dim3((unsigned)cdiv(n, 1024)), dim3(256), 0, st, x, n, d,
-                     k, mu, var, cdir, m, tau, ovf, idx, resp);
+  // the one-product screening and the exact ranking of its candidates, where
+  // the window holds every component that can be assigned; then, for the
+  // heavy points (or all), the two-pass screening
+  const int64_t* hlist = nullptr;
+  int smax = INT_MAX;
+  if (m == 1 || tau >= 0x1p-40f) {
+    if (L.iso) launch_coarse<D64, true>(L, x, mu, var, ws, window, st, &smax);
+    else launch_coarse<D64, false>(L, x, mu, var, ws, window, st, &smax);
+    const CoarseView cv = coarse_view(L, ws);
+    hlist = cv.hlist;
+    hipLaunchKernelGGL(k_assign_refine<D64>, dim3((unsigned)cdiv(n * refine_lanes(D64), 256)),
+                       dim3(256), 0, st, x, n, d, cv.cand, cv.cidx, dmu, dh, cdir, counts, smax,
+                       m, tau, idx, resp, ovf);
+  }
+  // up to kFewHeavy points, all of them heavy at most: nothing for the two passes
+  if (hlist == nullptr || n > kFewHeavy) {
+    if (m + 2 <= 4)
+      hipLaunchKernelGGL((k_assign_theta<D64, 4>), dim3((unsigned)L.n_wg_logz), dim3(256), 0, st,
+                         x, n, d, vec4, wp, wpb, cw, ca, counts, m + 2, hlist, smax, theta);
+    else
+      hipLaunchKernelGGL((k_assign_theta<D64, kTMax>), dim3((unsigned)L.n_wg_logz), dim3(256), 0,
+                         st, x, n, d, vec4, wp, wpb, cw, ca, counts, m + 2, hlist, smax, theta);
+    hipLaunchKernelGGL(k_assign_collect<D64>, dim3((unsigned)L.n_wg_logz), dim3(256), 0, st, x, n,
+                       d, vec4, wp, wpb, cw, ca, well_idx, ill_idx, dmu, dh, counts, theta, mu,
+                       var, cdir, m, tau, hlist, smax, idx, resp, ovf);
+  }
+  {
+    int64_t wg = cdiv(n, 1024);
+    if (hlist != nullptr && wg < kFewHeavy) wg = n < kFewHeavy ? n : kFewHeavy;
+    hipLaunchKernelGGL(k_assign_fallback, dim3((unsigned)wg), dim3(256), 0, st, x, n, d, D64, k,
+                       dmu, dh, cdir, m, tau, ovf, counts, hlist, smax, idx, resp);
+  }
   return launch_status();
 }
 
@@ -5490,7 +5777,7 @@ int kmeans_impl(const Layout& L, const float* x, int n_iters, float var_floor, f
   for (int it = 0; it <= n_iters; ++it) {
     // nearest centre; the top-1 responsibility goes to the cr region, which the
     // pairs overwrite below
-    int rc = assign_impl<D64>(L, x, weq, means, ones, 1, 0.0f, assign, cr, ws, st);
+    int rc = assign_impl<D64>(L, x, weq, means, ones, 1, 0.0f, 0.0f, assign, cr, ws, st);
     if (rc != GMM_OK) return rc;
     hipLaunchKernelGGL(k_km_pairs, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, assign, n,
                        cslot, cr);
@@ -5976,6 +6263,7 @@ int gmm_kmeans(const float* x, int64_t n, int32_t d, int32_t k, int32_t n_iters,
     return GMM_ERR_INVALID_ARG;
   Layout L;
   if (!make_layout(n, d, k, 1, &L)) return GMM_ERR_UNSUPPORTED;
+  L.iso = true;             // unit variances
   rc = check_ws(L, ws, ws_bytes);
   if (rc != GMM_OK) return rc;
   switch (L.D64) {
@@ -6030,7 +6318,7 @@ int gmm_assign_topk(const float* x, int64_t n, int32_t d, int32_t k, const float
   if (rc != GMM_OK) return rc;
   switch (L.D64) {
 #define GMM_CASE(D) \
-  case D: return assign_impl<D>(L, x, weights, means, vars, m, tau, idx, resp, ws, stream);
+  case D: return assign_impl<D>(L, x, weights, means, vars, m, tau, kAssignWindow, idx, resp, ws, stream);
     GMM_FOR_EACH_D64(GMM_CASE)
 #undef GMM_CASE
     default: return GMM_ERR_UNSUPPORTED;

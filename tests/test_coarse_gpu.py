@@ -1,5 +1,5 @@
-"""The one-product screening of the E-step (k_coarse, k_refine and the points it hands to
-k_logz) against the fp64 checker, at the edges of its tiles and of its rules: workgroups of
+"""The one-product screening of the E-step and of the assignment (k_coarse, k_refine,
+k_assign_refine and the points they hand to the two- or three-product passes) against the fp64 checker, at the edges of its tiles and of its rules: workgroups of
 128 and 256 points, blocks of 32 components, widths with and without a remainder, points with
 more components in reach than a list or a lane state holds, the sample that switches the pass
 off, and weights near the end of the float range.  The workspace starts as garbage, so a point
@@ -8,9 +8,10 @@ import numpy as np
 import pytest
 
 import gmm_synth as g
+import gmmcheck
 import oracle
-from gmmcheck import (check_params, check_params_iso, check_stats, gpu_estep, gpu_estep_iso,
-                      gpu_mstep, gpu_mstep_iso)
+from gmmcheck import (check_assign, check_params, check_params_iso, check_stats, gpu_assign,
+                      gpu_estep, gpu_estep_iso, gpu_mstep, gpu_mstep_iso)
 
 pytestmark = pytest.mark.gpu
 
@@ -19,6 +20,15 @@ def _dirty_ws(n, d, k):
     import torch
     import paper_2606_10896_amd as gmm
     ws = gmm.workspace(n, d, k)
+    ws.fill_(0xEE)
+    torch.cuda.synchronize()
+    return ws
+
+
+def _dirty_ws_m(n, d, k):
+    import torch
+    import paper_2606_10896_amd as gmm
+    ws = gmm.workspace(n, d, k, 1)
     ws.fill_(0xEE)
     torch.cuda.synchronize()
     return ws
@@ -37,7 +47,11 @@ def _check(x, th, label):
 @pytest.mark.parametrize("n,d,k", [
     (255, 64, 31), (256, 63, 32), (257, 65, 33), (513, 128, 64), (700, 127, 97),
     (128, 129, 32), (129, 192, 65), (385, 193, 40), (300, 256, 33), (1000, 7, 130),
-    (300, 2, 9), (64, 1, 3), (2000, 100, 257)])
+    (300, 2, 9), (64, 1, 3), (2000, 100, 257), (129, 257, 33), (200, 384, 40), (130, 512, 17),
+    (65, 640, 33), (129, 768, 64), (90, 895, 20), (70, 1024, 33),
+    # whole workgroups of points (n >= 65536) instead of shared ones
+    (65613, 20, 40), (65536, 128, 70), (65600, 130, 33), (65700, 250, 20), (65599, 385, 9),
+    (65601, 700, 7), (65600, 1000, 5)])
 def test_tile_edges(n, d, k):
     w = g.custom(f"c{n}_{d}_{k}", n, d, max(2, k // 2), k, data_seed=n * 3 + d, init_seed=k)
     x, th0 = g.make(w)
@@ -46,7 +60,9 @@ def test_tile_edges(n, d, k):
 
 
 @pytest.mark.parametrize("n,d,k", [(255, 64, 33), (257, 100, 64), (700, 128, 97),
-                                   (300, 190, 40), (129, 250, 32)])
+                                   (300, 190, 40), (129, 250, 32), (70, 500, 20), (40, 800, 9),
+                                   (65601, 30, 20), (65600, 200, 9), (65537, 600, 5),
+                                   (65540, 1000, 4)])
 def test_tile_edges_isotropic(n, d, k):
     w = g.custom(f"ci{n}_{d}_{k}", n, d, max(2, k // 2), k, data_seed=n * 5 + d, init_seed=k)
     x, (wt, mu, var) = g.make(w)
@@ -59,10 +75,8 @@ def test_tile_edges_isotropic(n, d, k):
         wt, mu, v = (ref[a].astype(np.float32) for a in ("weights", "means", "vars"))
 
 
-@pytest.mark.parametrize("d,seed", [(16, 1), (96, 2), (128, 3), (200, 4)])
-def test_many_components_in_reach(d, seed):
-    """Clusters of 1 to 14 near-identical components, scattered over the slots: points whose
-    candidates overflow the list, or one lane state of either lane half only."""
+def _reach(d, seed, n):
+    """Clusters of 1 to 14 near-identical components, scattered over the slots."""
     rng = np.random.default_rng(seed)
     sizes = np.tile(np.arange(1, 15), 6)
     k = int(sizes.sum())
@@ -70,11 +84,81 @@ def test_many_components_in_reach(d, seed):
     order = rng.permutation(k)
     centre = rng.normal(0.0, 4.0, (sizes.size, d))
     mu = (centre[cl] + rng.normal(0.0, 0.02, (k, d)))[order].astype(np.float32)
-    var = rng.uniform(0.5, 1.5, (k, d)).astype(np.float32) * 0 + np.float32(1.0)
+    var = np.ones((k, d), np.float32)
     wt = rng.dirichlet(np.full(k, 5.0)).astype(np.float32)
-    n = 6000
     x = (centre[rng.integers(0, sizes.size, n)] + rng.normal(0.0, 1.0, (n, d))).astype(np.float32)
-    _check(x, (wt, mu, var), f"reach d{d}")
+    return x, (wt, mu, var)
+
+
+@pytest.mark.parametrize("d,seed", [(16, 1), (96, 2), (128, 3), (200, 4), (300, 5), (770, 6)])
+def test_many_components_in_reach(d, seed):
+    """Points whose candidates overflow the list, or one lane state of one lane group only."""
+    x, th = _reach(d, seed, 6000)
+    _check(x, th, f"reach d{d}")
+
+
+def _check_assign(x, th, m, tau, label, min_checked=0.9):
+    import torch
+    import paper_2606_10896_amd as gmm
+    n, d = x.shape
+    k = th[0].shape[0]
+    ws = gmm.workspace(n, d, k, m)
+    ws.fill_(0xEE)
+    torch.cuda.synchronize()
+    ref = oracle.assign_topk(x, *th, m, tau, mr=m + 1)
+    gidx, gresp = gpu_assign(x, *th, m, tau, ws=ws)
+    print(f"  {label}: {check_assign(gidx, gresp, ref, m, tau, label, min_checked):.4f}", flush=True)
+
+
+@pytest.mark.parametrize("n,d,k,m,tau", [
+    (300, 24, 40, 2, 1 / 40), (65600, 24, 40, 3, 1 / 40), (65537, 130, 20, 8, 1e-6),
+    (2000, 24, 40, 2, 1e-13), (2000, 24, 40, 1, 0.0), (65600, 260, 9, 2, 0.1),
+    (700, 900, 33, 4, 1e-3), (1, 128, 9, 2, 0.1)])
+def test_assignment_routes(n, d, k, m, tau):
+    """Shared and whole workgroups, tau below the candidate window (2^-40), m = 1."""
+    w = g.custom(f"ca{n}_{d}_{k}", max(n, k), d, k, k, data_seed=n + d, init_seed=k + 1)
+    x, th0 = g.make(w)
+    th = oracle.fit(x, *th0, 2, keep_thetas=True)["thetas"][-1]
+    _check_assign(x[:n], th, m, tau, f"assign n{n} d{d} k{k} m{m} tau{tau}")
+
+
+@pytest.mark.parametrize("n,d", [(400, 64), (6000, 64), (6000, 200), (500, 400)])
+def test_assignment_of_heavy_points(n, d, monkeypatch):
+    """Few heavy points (every component in fp64) and many (the two-pass screening).  There
+    the normaliser keeps the screening error of the components that are no candidates, and
+    with 14 near-identical ones they carry most of it: a screened responsibility is within
+    2^-21 (S + d) relative, S = sum mu^2 / var of the components (the bound stated for the
+    split-bf16 screening)."""
+    x, th = _reach(d, 11, n)
+    s = float((th[1].astype(np.float64) ** 2 / th[2]).sum(1).max())
+    monkeypatch.setattr(gmmcheck, "TOL_RESP", max(gmmcheck.TOL_RESP, 2.0 ** -21 * (s + d)))
+    _check_assign(x, th, 4, 1e-4, f"assign heavy n{n} d{d}", min_checked=0.5)
+
+
+@pytest.mark.parametrize("n", [300, 3000])
+def test_assignment_with_weights_near_the_end_of_the_float_range(n):
+    w = g.custom("cx", 3000, 24, 10, 40, data_seed=8, init_seed=9)
+    x, (wt, mu, var) = g.make(w)
+    var = var.copy()
+    var[7] = 1e-29
+    _check_assign(x[:n], (wt, mu, var), 2, 1 / 40, f"assign wild n{n}")
+
+
+@pytest.mark.parametrize("n,d,k", [(65600, 20, 33), (900, 300, 20)])
+def test_kmeans_through_the_screening(n, d, k):
+    import torch
+    import paper_2606_10896_amd as gmm
+    w = g.custom(f"ck{n}", n, d, k, k, data_seed=n, init_seed=k)
+    x, (wt, mu, var) = g.make(w)
+    ref = oracle.kmeans(x, mu, var, 3)
+    xd, wd, md, vd = (torch.from_numpy(a.copy()).cuda() for a in (x, wt, mu, var))
+    assign = torch.empty(n, dtype=torch.int32, device="cuda")
+    gmm.gmm_kmeans(xd, wd, md, vd, 3, assign, _dirty_ws_m(n, d, k))
+    same = (assign.cpu().numpy() == ref["assign"]).mean()
+    print(f"  k-means n{n}: assignment equal {same:.6f}", flush=True)
+    assert same >= 0.9999
+    np.testing.assert_allclose(md.cpu().numpy(), ref["means"], rtol=1e-4, atol=1e-4)
+    np.testing.assert_allclose(wd.cpu().numpy(), ref["weights"], rtol=1e-3, atol=2.0 / n)
 
 
 @pytest.mark.parametrize("spread", [0.0, 1.0])
