@@ -64,7 +64,7 @@
 namespace {
 
 constexpr int kBK = 32;                 // components per MFMA block of the screening pass
-constexpr int kWB = 64;                 // components per workgroup of k_stats_well
+constexpr int kWB = 64;                 // well slots are padded to a multiple of this
 constexpr double kLog2e = 1.4426950408889634073599246810019;
 constexpr double kLn2 = 0.69314718055994530941723212145818;
 constexpr double kLog2Pi = 1.8378770664093454835606594728112;  // log(2 pi)
@@ -72,8 +72,8 @@ constexpr double kLog2Pi = 1.8378770664093454835606594728112;  // log(2 pi)
 // the fp32 expanded form is good to ~1e-2 in log2 units, plenty for screening
 constexpr double kIllSum = 2.0e5;
 constexpr int kT = 4;                   // exact responsibilities stored per point
-constexpr int kFlush = 128;             // k_stats_well: fp32 -> fp64 every 128 iterations
-constexpr int kStatsWin = 4096;         // k_stats_well: points scanned per queue window
+constexpr int kFlush = 256;             // k_stats_well: fp32 -> fp64 every 256 tiles of 16 points
+constexpr int kStatsWin = 1024;         // k_stats_well: list entries scanned per queue window
 // Refined lists store component slots as 16-bit values; kNoSlot marks an
 // empty entry (slots are < k <= GMM_MAX_K = 65535).
 constexpr unsigned short kNoSlot = 0xFFFF;
@@ -148,14 +148,17 @@ __device__ __forceinline__ void lse_merge(float& m, float& s, float m2, float s2
 }
 
 // Lane-state update of k_logz: the state starts at m = kEmpty (finite, below any
-// log-density), s = 0, a = -1, so l = -inf (a dead or padded component) adds
-// exactly 0 and no NaN can arise.  a tracks the arg-max slot.
+// log-density), o = 0, a = -1, so l = -inf (a dead or padded component) adds
+// exactly 0 and no NaN can arise.  a tracks the arg-max slot, o the sum of the
+// other components' 2^(l - m): apart from the arg-max's 1, in which what is
+// below 2^-24 of it would be lost, and with it the marks of its pairs for the
+// dense statistics.
 constexpr float kEmpty = -3.0e38f;
-__device__ __forceinline__ void lse_add_arg(float& m, float& s, int& a, float l, int slot) {
+__device__ __forceinline__ void lse_add_arg(float& m, float& o, int& a, float l, int slot) {
   const float dl = l - m;
   const float e = exp2_fast(-fabsf(dl));
   const bool gt = dl > 0.0f;
-  s = gt ? __fmaf_rn(s, e, 1.0f) : s + e;
+  o = gt ? __fmaf_rn(o, e, e) : o + e;
   m = gt ? l : m;
   a = gt ? slot : a;
 }
@@ -342,11 +345,33 @@ __device__ __forceinline__ double ill_logit_bounded_gr(const float* __restrict__
 // screening: heavy points of its sample, "wild" parameters (weights near the
 // end of the float range: its error bound does not hold, every point is
 // heavy), and the number of heavy points (64 bits).
-constexpr int kCntSample = 4, kCntWild = 5, kCntHeavy = 6;
+// Then the entries of the dense list (64 bits, k_sparse_offsets).
+constexpr int kCntSample = 4, kCntWild = 5, kCntHeavy = 6, kCntDense = 8;
 constexpr double kWildWeight = 1e28;
 // The one-product screening is off (every point is heavy).
 __device__ __forceinline__ bool coarse_off(const int* __restrict__ counts, int sample_max) {
   return counts[kCntWild] != 0 || counts[kCntSample] > sample_max;
+}
+// Components per bit of a point's 64-bit mask of the dense statistics, as a
+// shift: 16 (a group of the dense passes) while 64 bits cover the slots, then
+// 32 or 64.
+__host__ __device__ __forceinline__ int mask_shift(int kpad) {
+  return kpad <= 1024 ? 4 : (kpad <= 2048 ? 5 : 6);
+}
+// Points the dense statistics look at: those of the dense list, or all n.
+__device__ __forceinline__ int64_t dense_points(const int* __restrict__ counts, bool listed,
+                                                int64_t n) {
+  return listed ? *reinterpret_cast<const int64_t*>(counts + kCntDense) : n;
+}
+// Chunks they are split into: at most nch, and for a short list no more than
+// keep 256 points a chunk (a chunk's partial sums are written and read again;
+// 1024 and 4096 left too few workgroups at n = 1e5: 312 us against 206 with the
+// chunks of the whole range).  The same in the dense passes and
+// k_reduce_stats.
+__device__ __forceinline__ int dense_chunks(int64_t np, bool listed, int nch) {
+  if (!listed) return nch;
+  const int64_t c = (np + 255) / 256;
+  return c < 1 ? 1 : (c > nch ? nch : (int)c);
 }
 __device__ __forceinline__ int64_t heavy_count(const int* __restrict__ counts) {
   return (int64_t)*reinterpret_cast<const unsigned long long*>(counts + kCntHeavy);
@@ -1104,7 +1129,8 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_logz(
     const int* __restrict__ counts, double* __restrict__ logz2,
     unsigned short* __restrict__ cslot, float* __restrict__ cr,
     unsigned long long* __restrict__ bmask, unsigned char* __restrict__ iflag,
-    unsigned char* __restrict__ lflag, const int64_t* __restrict__ hlist, int sample_max) {
+    unsigned char* __restrict__ lflag, const int64_t* __restrict__ hlist, int sample_max,
+    int gsh) {
   constexpr int P = D64 + 4, NT = logz_tiles(D64), PTS = 32 * NT;
   constexpr bool B16 = screen_b16(D64);
   static_assert(!ISO || screen_split(D64), "the isotropic screening is a split-bf16 one");
@@ -1233,7 +1259,7 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_logz(
   __syncthreads();
   const int n_wkb = counts[2], n_ill = counts[1], n_well = counts[0];
 
-  float m0[16], s0[16], m1[16], s1[16];
+  float m0[16], s0[16], m1[16], s1[16];       // s: the others' sum (lse_add_arg)
   int a0[16], a1[16];
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
@@ -1334,12 +1360,12 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_logz(
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       XM[v] = m0[v];
-      XS[v] = s0[v];
+      XS[v] = a0[v] >= 0 ? 1.0f + s0[v] : 0.0f;
       XA[v] = m0[v];
       XB[v] = kEmpty;
       if constexpr (NT == 2) {
         XM[16 + v] = m1[v];
-        XS[16 + v] = s1[v];
+        XS[16 + v] = a1[v] >= 0 ? 1.0f + s1[v] : 0.0f;
         XA[16 + v] = m1[v];
         XB[16 + v] = kEmpty;
       }
@@ -1542,7 +1568,7 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_logz(
       for (int blk = 0; blk < NT; ++blk) {
         const int pp = blk * 32 + p;
         const float mv = blk ? m1[v] : m0[v];
-        const float sv = blk ? s1[v] : s0[v];
+        const float ov = blk ? s1[v] : s0[v];
         const int av = blk ? a1[v] : a0[v];
         const bool valid = av >= 0;
         // refined: within the component's window, or among the point's four
@@ -1556,13 +1582,13 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_logz(
         const float2 tr = tsrc[valid ? av : 0];
         const float2 tf = valid ? tr : make_float2(0.0f, 0.0f);
         const float er = exp2_fast(rel), ex = exp2_fast(mv - swx);
-        const bool full = REFINE & valid & ((sv - 1.0f) * er * tf.y > kFullErr);
+        const bool full = REFINE & valid & (ov * er * tf.y > kFullErr);
         const bool cand =
             valid & (full | (rel > tf.x) | ((mv >= s4) & (rel > -(float)kWideWindow)));
         if (cand) cbits |= 1u << (16 * blk + v);
-        XT[16 * blk + v] = cand ? (full ? sv : 1.0f) * ex : 0.0f;
+        XT[16 * blk + v] = cand ? (full ? 1.0f + ov : 1.0f) * ex : 0.0f;
         const bool sig = (bmask != nullptr) & valid & (rel > -kDenseWindow);
-        const bool oth = sig & ((sv - 1.0f) * er > kDenseMass);
+        const bool oth = sig & (ov * er > kDenseMass);
         if constexpr (B16) {
           // one flag byte per lane state (IllStage's space is free now); the
           // (point, wave) masks are assembled from them below
@@ -1860,11 +1886,12 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_logz(
           lflag[nn] = 0;
         }
         if (bmask != nullptr) {
-          // 64-component blocks the dense statistics pass takes for this point
+          // granules of components the dense statistics pass takes for this point
           unsigned long long bm = 0ull;
           for (int w2 = 0; w2 < 4; ++w2) {
             if (omask[p][w2] != 0u)
-              for (int kb = w2; kb < n_wkb; kb += 4) bm |= 1ull << (kb >> 1);
+              for (int kb = w2; kb < n_wkb; kb += 4)
+                bm |= (gsh == 4 ? 3ull : 1ull) << ((kb * kBK) >> gsh);
             unsigned sm = smask[p][w2];
             while (sm) {
               const int b = __ffs(sm) - 1;
@@ -1873,7 +1900,7 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_logz(
               bool stored = false;
 #pragma unroll
               for (int j = 0; j < kT; ++j) stored = stored || tsl[j] == slot;
-              if (!stored) bm |= 1ull << (slot >> 6);
+              if (!stored) bm |= 1ull << (slot >> gsh);
             }
           }
           bmask[nn] = bm;
@@ -2558,7 +2585,7 @@ __global__ __launch_bounds__(256) void k_refine(
     const double* __restrict__ cdir, const int* __restrict__ counts, int sample_max,
     double* __restrict__ logz2, unsigned short* __restrict__ cslot, float* __restrict__ cr,
     unsigned long long* __restrict__ bmask, unsigned char* __restrict__ iflag,
-    unsigned char* __restrict__ lflag) {
+    unsigned char* __restrict__ lflag, int gsh) {
   constexpr int G = refine_lanes(D64);
   if (coarse_off(counts, sample_max)) return;
   const int lane = threadIdx.x & 63, g = lane & (G - 1);
@@ -2609,7 +2636,7 @@ __global__ __launch_bounds__(256) void k_refine(
   // blocks of the well candidates that are not stored
   unsigned blo = 0u, bhi = 0u;
   if (well && rank >= kT) {
-    const int b = slot >> 6;
+    const int b = slot >> gsh;
     if (b < 32) blo = 1u << b;
     else if (b < 64) bhi = 1u << (b - 32);
   }
@@ -2699,20 +2726,21 @@ __global__ __launch_bounds__(256) void k_assign_refine(
 }
 
 // ---------------------------------------------------------------- Step 2: statistics, well set
-// Grid: (64-component block, point chunk), 16x16x4 fp32 MFMA.  Wave w owns the
-// 16 components 16w .. 16w+15 of the block and works on its own: its
-// log-density operand (W and P of its components, 2 * D64 values per lane in
-// the MFMA B-operand order of the packed array wq) stays in registers for the
-// whole chunk; for every 16-point tile it forms the log-densities of its
-// components, takes r = 2^(l - log2 Z) with the refined pairs set to 0
-// (k_stats_sparse sums those exactly), and
-// contracts r^T [x | x^2] into fp32 accumulators (its 16 components x 2 D64
-// columns) that are folded into the workgroup's fp64 partial every kFlush
-// iterations; N_k is summed on the vector ALU.  The log-density accumulator
-// layout (point 4(l/16)+v, component l%16) is the B-operand layout of the
-// statistic MFMA, so r stays in registers.  The waves share only the X tile:
-// 32 points per iteration, double-buffered in LDS and loaded one iteration
-// ahead, one barrier per iteration.
+// Grid: (16-component group, chunk of the dense list), one wave a workgroup,
+// 16x16x4 fp32 MFMA.  The wave's log-density operand (W and P of its components,
+// 2 * D64 values per lane in the MFMA B-operand order of the packed array wq)
+// stays in registers for the whole chunk.  It queues the chunk's points that
+// need its group (mask granule), in point order, and for every 16 of them forms
+// the log-densities, takes r = 2^(l - log2 Z) with the refined pairs set to 0
+// (k_stats_sparse sums those exactly), and contracts r^T [x | x^2] into fp32
+// accumulators (its 16 components x 2 D64 columns) that are folded into the
+// workgroup's fp64 partial every kFlush tiles; N_k is summed on the vector ALU.
+// The log-density accumulator layout (point 4(l/16)+v, component l%16) is the
+// B-operand layout of the statistic MFMA, so r stays in registers.  The rows
+// of the next 16 points are loaded into registers while the current ones, in
+// LDS, are worked on; the wave meets no barrier.  (Four waves sharing the tiles
+// of a 64-component queue did four groups' work for every point that needed
+// one: in the course of a fit most need one or two.)
 //
 // The log-density chain yields l - log2 Z directly: for every group of 32
 // dimensions its x steps, its x^2 steps, then one step that adds the group's
@@ -2737,13 +2765,12 @@ __device__ __forceinline__ f4v mfma16(float a, float b, f4v c) {
 // ALU, written into dimension 0 of Q (the isotropic Q is the sum over the
 // dimensions).
 template <int D64, bool ISO>
-__global__ __launch_bounds__(256, D64 <= 128 ? 2 : 1) void k_stats_well(
+__global__ __launch_bounds__(64, D64 <= 128 ? 2 : 1) void k_stats_well(
     const float* __restrict__ x, int64_t n, int d, int vec4, const float* __restrict__ wq,
-    const float* __restrict__ cw, const int* __restrict__ counts,
-    const double* __restrict__ logz2, const unsigned short* __restrict__ cslot,
-    const unsigned long long* __restrict__ bmask, int nch, int64_t chunk_pts,
-    const unsigned char* __restrict__ sflag, unsigned char* __restrict__ lflag,
-    double* __restrict__ part) {
+    const int* __restrict__ counts, const double* __restrict__ logz2,
+    const unsigned short* __restrict__ cslot, const ulonglong2* __restrict__ dlist, int nch,
+    int gsh, const unsigned char* __restrict__ sflag, unsigned char* __restrict__ lflag,
+    unsigned long long* __restrict__ lmask, double* __restrict__ part) {
   constexpr int P = D64 + 4;
   constexpr int NS = D64 / 4;                   // MFMA steps per chain
   constexpr int NG = D64 / 64;                  // float4 column groups per part
@@ -2752,59 +2779,56 @@ __global__ __launch_bounds__(256, D64 <= 128 ? 2 : 1) void k_stats_well(
   constexpr int WQS = ISO ? wq_steps_iso(D64) : wq_steps(D64);
   constexpr int SB = ISO ? NS + NGB : 2 * NS;   // first bias step
   constexpr int NACC = ISO ? NB : 2 * NB;       // accumulator blocks
-  constexpr int PTS = 32;                       // points per iteration (two tiles)
+  constexpr int PTS = 16;                       // points per tile
   constexpr int Q4 = D64 / 4;
-  constexpr int LD = PTS * Q4 / 256;            // float4 per thread per X tile
+  constexpr int LD = PTS * Q4 / 64;             // float4 per lane per X tile
   constexpr int STRIDE = 1 + 2 * D64;
-  static_assert(kT == 4, "refined lists are loaded as int4");
-  static_assert(LD >= 1 && PTS * Q4 % 256 == 0, "tile split");
-  __shared__ __align__(16) float xs[2][PTS * P];
-  __shared__ float2 lzb[2][PTS];                // -log2 Z / NGB as a (hi, lo) pair
-  __shared__ unsigned long long rbb[2][PTS];
-  __shared__ unsigned pqo[2][PTS];              // the tile's points (offsets from p0, ~0u: none)
-  __shared__ unsigned long long lbits;          // light slots of this block
-  __shared__ unsigned qpt[kStatsWin + PTS];     // queued points (offsets from the chunk start)
-  static_assert(kStatsWin == 16 * 256, "a window is 16 points per thread");
-  __shared__ int qsum[4];
-  const int kb = blockIdx.x / nch, chunk = blockIdx.x % nch;
-  if (2 * kb >= counts[2]) return;              // counts[2]: well blocks of 32
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int i16 = lane & 15, k4 = lane >> 4;
+  static_assert(kT == 4, "refined lists are loaded as ushort4");
+  __shared__ __align__(16) float xs[PTS * P];
+  __shared__ unsigned qpt[kStatsWin + PTS];     // queued points (offsets from pb)
+  const int grp = blockIdx.x / nch, chunk = blockIdx.x % nch;
+  const int n_well = counts[0];
+  if (16 * grp >= n_well) return;               // no well component in this group
+  const int lane = threadIdx.x, i16 = lane & 15, k4 = lane >> 4;
+  // entries of the dense list (or points), split into ech chunks
+  const int64_t ne = dense_points(counts, dlist != nullptr, n);
+  const int ech = dense_chunks(ne, dlist != nullptr, nch);
+  if (chunk >= ech) return;
+  const int64_t chunk_pts = (ne + ech - 1) / ech;
   const int64_t p0 = (int64_t)chunk * chunk_pts;
-  const int64_t p1 = p0 + chunk_pts < n ? p0 + chunk_pts : n;
-  double* pw = part + (size_t)blockIdx.x * kWB * STRIDE;
+  const int64_t p1 = p0 + chunk_pts < ne ? p0 + chunk_pts : ne;
+  double* pw = part + (size_t)blockIdx.x * 16 * STRIDE;
   if (p0 >= p1) {
-    for (int i = tid; i < kWB * STRIDE; i += 256) pw[i] = 0.0;
+    for (int i = lane; i < 16 * STRIDE; i += 64) pw[i] = 0.0;
     return;
   }
-  const int grp = kb * 4 + wave;                // 16-component group
-  if (wave == 0) {
-    const int sl = kb * kWB + lane;
-    const unsigned long long lb =
-        __ballot(sflag != nullptr && sl < counts[0] && sflag[sl] != 0);
-    if (lane == 0) lbits = lb;
-  }
+  const int64_t pb = dlist != nullptr ? (int64_t)dlist[p0].x : p0;   // first point
+  // this lane's component; a light one is left out here and recomputed exactly:
+  // the points where it comes within 2^-72 of log2 Z are flagged for that
+  const int myslot = 16 * grp + i16;
+  const bool mylight = sflag != nullptr && myslot < n_well && sflag[myslot] != 0;
+  const bool anylight = __ballot(mylight) != 0ull;
   float wb[WQS];
 #pragma unroll
   for (int s2 = 0; s2 < WQS; ++s2) wb[s2] = wq[((size_t)grp * WQS + s2) * 64 + lane];
 
-  // ---- X tile: global -> registers -> LDS
+  // ---- X tile: global -> registers -> LDS; lanes 0..15 also hold the tile's
+  // -log2 Z / NGB (as a hi, lo pair), refined slots of this group and points
   float4 px[LD];
   float2 plz = make_float2(-INFINITY, 0.0f);
-  unsigned long long prb = 0ull;
-  unsigned ppo = ~0u;
+  unsigned prb = 0u, ppo = ~0u;
   // tile i holds queue entries PTS i .. PTS i + PTS - 1 (rows past qn are zero)
   int qn = 0;                                   // queued points (uniform)
   auto load_regs = [&](int i) {
 #pragma unroll
     for (int j = 0; j < LD; ++j) {
-      const int idx = tid + 256 * j, r = idx / Q4, c = (idx % Q4) * 4;
+      const int idx = lane + 64 * j, r = idx / Q4, c = (idx % Q4) * 4;
       const int e = PTS * i + r;
-      const int64_t nn = e < qn ? p0 + qpt[e] : p1;
+      const int64_t nn = e < qn ? pb + qpt[e] : -1;
       float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
       if (vec4) {
-        if (nn < p1 && c < d) v = *reinterpret_cast<const float4*>(x + nn * d + c);
-      } else if (nn < p1) {
+        if (nn >= 0 && c < d) v = *reinterpret_cast<const float4*>(x + nn * d + c);
+      } else if (nn >= 0) {
         const float* xr = x + nn * d;
         v.x = c < d ? xr[c] : 0.f;
         v.y = c + 1 < d ? xr[c + 1] : 0.f;
@@ -2813,13 +2837,14 @@ __global__ __launch_bounds__(256, D64 <= 128 ? 2 : 1) void k_stats_well(
       }
       px[j] = v;
     }
-    if (tid < PTS) {
-      const int e = PTS * i + tid;
-      const int64_t nn = e < qn ? p0 + qpt[e] : p1;
+    if (lane < PTS) {
+      const int e = PTS * i + lane;
       plz = make_float2(-INFINITY, 0.0f);
-      prb = 0ull;
-      ppo = nn < p1 ? (unsigned)(nn - p0) : ~0u;
-      if (nn < p1) {
+      prb = 0u;
+      ppo = ~0u;
+      if (e < qn) {
+        ppo = qpt[e];
+        const int64_t nn = pb + ppo;
         const double b64 = -logz2[nn] / NGB;
         const float bh = (float)b64;
         plz = make_float2(bh, (float)(b64 - (double)bh));
@@ -2827,20 +2852,8 @@ __global__ __launch_bounds__(256, D64 <= 128 ? 2 : 1) void k_stats_well(
         const int v4[4] = {sl.x, sl.y, sl.z, sl.w};
 #pragma unroll
         for (int j = 0; j < kT; ++j)
-          if (v4[j] != kNoSlot && v4[j] / kWB == kb) prb |= 1ull << (v4[j] % kWB);
+          if (v4[j] != kNoSlot && (v4[j] >> 4) == grp) prb |= 1u << (v4[j] & 15);
       }
-    }
-  };
-  auto store_regs = [&](int buf) {
-#pragma unroll
-    for (int j = 0; j < LD; ++j) {
-      const int idx = tid + 256 * j, r = idx / Q4, c = (idx % Q4) * 4;
-      *reinterpret_cast<float4*>(&xs[buf][r * P + c]) = px[j];
-    }
-    if (tid < PTS) {
-      lzb[buf][tid] = plz;
-      rbb[buf][tid] = prb;
-      pqo[buf][tid] = ppo;
     }
   };
 
@@ -2850,11 +2863,6 @@ __global__ __launch_bounds__(256, D64 <= 128 ? 2 : 1) void k_stats_well(
   float nkacc = 0.0f;
   float qacc = 0.0f;                            // ISO: sum of r ||x||^2
   bool first = true;
-  const int myc = wave * 16 + i16;              // this lane's component in the block
-  __syncthreads();                              // lbits
-  // a light component is left out here and recomputed exactly; the points
-  // where it comes within 2^-72 of log2 Z are flagged for that
-  const bool mylight = ((lbits >> myc) & 1ull) != 0ull;
 
   // fp32 accumulators -> fp64 partial.  Register v of block c at lane l is
   // column 4(l/16) + v of the block: dimension 64 (c/4 % NG) + 4 (4 k4 + v) + c % 4.
@@ -2866,7 +2874,7 @@ __global__ __launch_bounds__(256, D64 <= 128 ? 2 : 1) void k_stats_well(
       q2 = qacc + __shfl_xor(qacc, 16);
       q2 += __shfl_xor(q2, 32);
     }
-    double* row = pw + (size_t)myc * STRIDE;
+    double* row = pw + (size_t)i16 * STRIDE;
     if (k4 == 0) row[0] = first ? (double)nk2 : row[0] + (double)nk2;
 #pragma unroll
     for (int part2 = 0; part2 < 2; ++part2) {
@@ -2901,62 +2909,57 @@ __global__ __launch_bounds__(256, D64 <= 128 ? 2 : 1) void k_stats_well(
     first = false;
   };
 
-  // The chunk is taken in windows of kStatsWin points: the points of a window
-  // that need this block (every point when bmask is null) are appended to the
-  // queue in point order, the full tiles of the queue are processed (at the
-  // chunk's end also the partial one) and the rest moves to the queue's front.
-  const unsigned long long kbit = 1ull << (kb & 63);
+  // Windows of kStatsWin entries: those that need this group (every point when
+  // dlist is null) are appended to the queue in order, the full tiles of the
+  // queue are processed (at the chunk's end also the partial one) and the rest
+  // moves to the queue's front.
+  const unsigned long long kbit = 1ull << (((16 * grp) >> gsh) & 63);
+  const unsigned long long below = (1ull << lane) - 1ull;
   int tiles = 0;                                // tiles processed (flush schedule)
   for (int64_t wb0 = p0; wb0 < p1; wb0 += kStatsWin) {
     const int64_t we = wb0 + kStatsWin < p1 ? wb0 + kStatsWin : p1;
-    {
-      // thread t takes points wb0 + 16 t .. wb0 + 16 t + 15
-      const int64_t a = wb0 + 16 * tid;
-      unsigned sel = 0u;
+    for (int64_t a = wb0; a < we; a += 512) {
+      unsigned long long mk[8];
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int64_t pt = a + e;
-        if (pt < we && (bmask == nullptr || (bmask[pt] & kbit) != 0ull)) sel |= 1u << e;
+      for (int j = 0; j < 8; ++j) {
+        const int64_t e = a + 64 * j + lane;
+        mk[j] = e < we ? (dlist != nullptr ? dlist[e].y : ~0ull) : 0ull;
       }
-      const int c = __popc(sel);
-      int inc = c;
-      for (int o = 1; o < 64; o <<= 1) {
-        const int t2 = __shfl_up(inc, o);
-        if (lane >= o) inc += t2;
-      }
-      if (lane == 63) qsum[wave] = inc;
-      __syncthreads();
-      int pos = qn + inc - c, all = 0;
 #pragma unroll
-      for (int w2 = 0; w2 < 4; ++w2) {
-        if (w2 < wave) pos += qsum[w2];
-        all += qsum[w2];
+      for (int j = 0; j < 8; ++j) {
+        const int64_t e = a + 64 * j + lane;
+        const bool need = (mk[j] & kbit) != 0ull;
+        const unsigned long long bal = __ballot(need);
+        if (need)
+          qpt[qn + __popcll(bal & below)] =
+              (unsigned)((dlist != nullptr ? (int64_t)dlist[e].x : e) - pb);
+        qn += __popcll(bal);
       }
-      while (sel) {
-        const int e = __ffs(sel) - 1;
-        sel &= sel - 1;
-        qpt[pos++] = (unsigned)(a + e - p0);
-      }
-      qn += all;
-      __syncthreads();                          // queue complete, qsum free
     }
+    __builtin_amdgcn_wave_barrier();
     const int nt = we >= p1 ? (qn + PTS - 1) / PTS : qn / PTS;
-    if (nt > 0) {
-  load_regs(0);
-  store_regs(0);
-  for (int i = 0; i < nt; ++i) {
-    const int cur = i & 1;
-    __syncthreads();                            // tile i in xs[cur]; xs[cur ^ 1] free
-    if (i + 1 < nt) load_regs(i + 1);
+    if (nt > 0) load_regs(0);
+    for (int i = 0; i < nt; ++i) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      // log-densities of points t*16 .. t*16+15 against this wave's components
-      f4v la = {0.f, 0.f, 0.f, 0.f};
-      const float* xr = &xs[cur][(t * 16 + i16) * P + 4 * k4];
+      for (int j = 0; j < LD; ++j) {
+        const int idx = lane + 64 * j, r = idx / Q4, c = (idx % Q4) * 4;
+        *reinterpret_cast<float4*>(&xs[r * P + c]) = px[j];
+      }
       // A operand of the bias steps: -log2 Z / NGB of row point i16 as a
       // (hi, lo) pair in lane groups 0 and 2, 1 in lane group 1, 0 in group 3
-      const float2 bz = lzb[cur][t * 16 + i16];
-      const float ab = k4 == 0 ? bz.x : (k4 == 1 ? 1.0f : (k4 == 2 ? bz.y : 0.0f));
+      const float bzx = __shfl(plz.x, i16), bzy = __shfl(plz.y, i16);
+      const float ab = k4 == 0 ? bzx : (k4 == 1 ? 1.0f : (k4 == 2 ? bzy : 0.0f));
+      unsigned rbv[4], pov[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        rbv[v] = __shfl(prb, 4 * k4 + v);
+        pov[v] = __shfl(ppo, 4 * k4 + v);
+      }
+      __builtin_amdgcn_wave_barrier();
+      if (i + 1 < nt) load_regs(i + 1);
+      // log-densities of the tile's points against this wave's components
+      f4v la = {0.f, 0.f, 0.f, 0.f};
+      const float* xr = &xs[i16 * P + 4 * k4];
       // wide D: keep each group's operand loads in their group (hoisting all
       // of them exhausts the registers)
       constexpr bool kPin = D64 > 128;
@@ -3002,20 +3005,25 @@ __global__ __launch_bounds__(256, D64 <= 128 ? 2 : 1) void k_stats_well(
       float r[4];
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int pt = t * 16 + 4 * k4 + v;
         const float e = exp2_fast(la[v]);
-        r[v] = (((rbb[cur][pt] >> myc) & 1ull) || mylight) ? 0.0f : e;
-        if (mylight && e > 0x1p-72f) {
-          const unsigned po = pqo[cur][pt];
-          if (po != ~0u) lflag[p0 + po] = 1;
-        }
+        r[v] = (((rbv[v] >> i16) & 1u) || mylight) ? 0.0f : e;
         nkacc += r[v];
         if constexpr (ISO) qacc += r[v] * __shfl(nfull, 4 * k4 + v);
       }
-      // statistics: step v contracts points t*16 + 4k + v (k = 0..3)
+      if (anylight) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          if (mylight && pov[v] != ~0u && exp2_fast(la[v]) > 0x1p-72f) {
+            const int64_t nn = pb + pov[v];
+            lflag[nn] = 1;
+            if (lmask != nullptr) atomicOr(lmask + nn, kbit);
+          }
+        }
+      }
+      // statistics: step v contracts points 4k + v (k = 0..3)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const float* yr = &xs[cur][(t * 16 + 4 * k4 + v) * P + 4 * i16];
+        const float* yr = &xs[(4 * k4 + v) * P + 4 * i16];
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
           const float4 y = *reinterpret_cast<const float4*>(yr + 64 * g);
@@ -3032,22 +3040,20 @@ __global__ __launch_bounds__(256, D64 <= 128 ? 2 : 1) void k_stats_well(
           if constexpr (kPin) __builtin_amdgcn_sched_barrier(0);
         }
       }
-    }
-    if (i + 1 < nt) store_regs(cur ^ 1);
-    if ((tiles % kFlush) == kFlush - 1) flush();
-    ++tiles;
-  }
+      __builtin_amdgcn_wave_barrier();          // this tile's LDS reads before the next writes
+      if ((tiles % kFlush) == kFlush - 1) flush();
+      ++tiles;
     }
     // the entries not taken move to the front of the queue
     const int used = PTS * nt < qn ? PTS * nt : qn;
     const int left = qn - used;
-    __syncthreads();                            // every read of the queue and the tiles done
-    const unsigned keep = tid < left ? qpt[used + tid] : 0u;
-    __syncthreads();
-    if (tid < left) qpt[tid] = keep;
+    const unsigned keep = lane < left ? qpt[used + lane] : 0u;
+    __builtin_amdgcn_wave_barrier();
+    if (lane < left) qpt[lane] = keep;
+    __builtin_amdgcn_wave_barrier();
     qn = left;
   }
-  // the last partial sums (zeros when no point of the chunk needs this block)
+  // the last partial sums (zeros when no point of the chunk needs this group)
   if (first || (tiles % kFlush) != 0) flush();
 }
 
@@ -3080,9 +3086,9 @@ __global__ __launch_bounds__(64 * (DW / 128)) void k_stats_wide(
     const float* __restrict__ x, int64_t n, int d, int vec4, const float* __restrict__ wq,
     const double* __restrict__ cwell, const int* __restrict__ well_idx,
     const int* __restrict__ counts, const double* __restrict__ logz2,
-    const unsigned short* __restrict__ cslot, const unsigned long long* __restrict__ bmask,
-    int nch, int64_t chunk_pts, const unsigned char* __restrict__ sflag,
-    unsigned char* __restrict__ lflag, double* __restrict__ part) {
+    const unsigned short* __restrict__ cslot, const ulonglong2* __restrict__ dlist, int nch,
+    int gsh, const unsigned char* __restrict__ sflag, unsigned char* __restrict__ lflag,
+    unsigned long long* __restrict__ lmask, double* __restrict__ part) {
   constexpr int NW = DW / 128, DQ = 128, P = DQ + 4;
   constexpr int NS = DW / 4, WQS = wq_steps(DW);
   constexpr int SW = DQ / 4, NBQ = DQ / 16, NG = DQ / 64;
@@ -3099,8 +3105,14 @@ __global__ __launch_bounds__(64 * (DW / 128)) void k_stats_wide(
   if (16 * g >= n_well) return;                // no well component in this group
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int i16 = lane & 15, k4 = lane >> 4;
+  // entries of the dense list (or points), split into ech chunks
+  const int64_t ne = dense_points(counts, dlist != nullptr, n);
+  const int ech = dense_chunks(ne, dlist != nullptr, nch);
+  if (chunk >= ech) return;
+  const int64_t chunk_pts = (ne + ech - 1) / ech;
   const int64_t p0 = (int64_t)chunk * chunk_pts;
-  const int64_t p1 = p0 + chunk_pts < n ? p0 + chunk_pts : n;
+  const int64_t p1 = p0 + chunk_pts < ne ? p0 + chunk_pts : ne;
+  const int64_t pb = dlist != nullptr && p0 < p1 ? (int64_t)dlist[p0].x : p0;   // first point
   double* pw = part + (size_t)blockIdx.x * 16 * STRIDE;
   if (p0 >= p1) {
     for (int i = tid; i < 16 * STRIDE; i += 64 * NW) pw[i] = 0.0;
@@ -3125,7 +3137,7 @@ __global__ __launch_bounds__(64 * (DW / 128)) void k_stats_wide(
   float4 px[LD];
   double plz = INFINITY;
   unsigned prb = 0u;
-  unsigned ppo = ~0u;
+  int64_t ppo = -1;
   // tile i holds queue entries 16 i .. 16 i + 15 (rows past qn are zero)
   int qn = 0;                                   // queued points (uniform)
   auto load_regs = [&](int i) {
@@ -3133,11 +3145,11 @@ __global__ __launch_bounds__(64 * (DW / 128)) void k_stats_wide(
     for (int j = 0; j < LD; ++j) {
       const int idx = lane + 64 * j, r = idx / (DQ / 4), c = dq0 + (idx % (DQ / 4)) * 4;
       const int e = 16 * i + r;
-      const int64_t nn = e < qn ? p0 + qpt[e] : p1;
+      const int64_t nn = e < qn ? pb + qpt[e] : -1;
       float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
       if (vec4) {
-        if (nn < p1 && c < d) v = *reinterpret_cast<const float4*>(x + nn * d + c);
-      } else if (nn < p1) {
+        if (nn >= 0 && c < d) v = *reinterpret_cast<const float4*>(x + nn * d + c);
+      } else if (nn >= 0) {
         const float* xr = x + nn * d;
         v.x = c < d ? xr[c] : 0.f;
         v.y = c + 1 < d ? xr[c + 1] : 0.f;
@@ -3148,11 +3160,11 @@ __global__ __launch_bounds__(64 * (DW / 128)) void k_stats_wide(
     }
     if (lane < 16) {
       const int e = 16 * i + lane;
-      const int64_t nn = e < qn ? p0 + qpt[e] : p1;
+      const int64_t nn = e < qn ? pb + qpt[e] : -1;
       plz = INFINITY;
       prb = 0u;
-      ppo = nn < p1 ? (unsigned)(nn - p0) : ~0u;
-      if (nn < p1) {
+      ppo = nn;
+      if (nn >= 0) {
         plz = logz2[nn];
         const ushort4 sl = *reinterpret_cast<const ushort4*>(cslot + nn * kT);
         const int v4[4] = {sl.x, sl.y, sl.z, sl.w};
@@ -3216,10 +3228,10 @@ __global__ __launch_bounds__(64 * (DW / 128)) void k_stats_wide(
   };
 
   // Windows of WIN points: the points that need this group's 64-component
-  // block (every point when bmask is null) are queued in point order, the
+  // block (every point when dlist is null) are queued in point order, the
   // full 16-point tiles of the queue are processed (at the chunk's end also
   // the partial one) and the rest moves to the queue's front.
-  const unsigned long long kbit = 1ull << ((g >> 2) & 63);
+  const unsigned long long kbit = 1ull << (((16 * g) >> gsh) & 63);
   int tiles = 0;                                // tiles processed (flush schedule)
   for (int64_t wb0 = p0; wb0 < p1; wb0 += WIN) {
     const int64_t we = wb0 + WIN < p1 ? wb0 + WIN : p1;
@@ -3229,7 +3241,11 @@ __global__ __launch_bounds__(64 * (DW / 128)) void k_stats_wide(
 #pragma unroll
       for (int e = 0; e < WPT; ++e) {
         const int64_t pt = a + e;
-        if (pt < we && (bmask == nullptr || (bmask[pt] & kbit) != 0ull)) sel |= 1u << e;
+        if (dlist == nullptr) {
+          if (pt < we) sel |= 1u << e;
+        } else if (pt < we && (dlist[pt].y & kbit) != 0ull) {
+          sel |= 1u << e;
+        }
       }
       const int c = __popc(sel);
       int inc = c;
@@ -3248,7 +3264,7 @@ __global__ __launch_bounds__(64 * (DW / 128)) void k_stats_wide(
       while (sel) {
         const int e = __ffs(sel) - 1;
         sel &= sel - 1;
-        qpt[pos++] = (unsigned)(a + e - p0);
+        qpt[pos++] = (unsigned)((dlist != nullptr ? (int64_t)dlist[a + e].x : a + e) - pb);
       }
       qn += all;
       __syncthreads();                          // queue complete, qsum free
@@ -3258,7 +3274,8 @@ __global__ __launch_bounds__(64 * (DW / 128)) void k_stats_wide(
   load_regs(0);
   for (int i = 0; i < nt; ++i) {
     store_regs();
-    unsigned rbv[4], pov[4];
+    unsigned rbv[4];
+    int64_t pov[4];
     double lzv[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -3318,7 +3335,10 @@ __global__ __launch_bounds__(64 * (DW / 128)) void k_stats_wide(
       tot += cst - lzv[v];
       const float e = exp2_fast((float)tot);
       r[v] = (((rbv[v] >> i16) & 1u) || mylight) ? 0.0f : e;
-      if (mylight && wave == 0 && e > 0x1p-72f && pov[v] != ~0u) lflag[p0 + pov[v]] = 1;
+      if (mylight && wave == 0 && e > 0x1p-72f && pov[v] >= 0) {
+        lflag[pov[v]] = 1;
+        if (lmask != nullptr) atomicOr(lmask + pov[v], kbit);
+      }
       nkacc += r[v];
     }
     // statistics over this wave's dimensions: step v contracts points 4k + v
@@ -3365,7 +3385,8 @@ __global__ __launch_bounds__(64 * (DW / 128)) void k_stats_wide(
 // sparse_cb(D64) consecutive well slots.  Three light passes put the pairs of
 // every bucket into one contiguous list, in a fixed order:
 //   k_sparse_count    per unit (a contiguous range of points): pairs per bucket
-//   k_sparse_scan     exclusive prefix over (bucket, unit), bucket-major
+//   k_sparse_total,   exclusive prefix over (bucket, unit), bucket-major
+//   k_sparse_offsets
 //   k_sparse_scatter  per unit: every pair to its bucket's segment, the unit's
 //                     points taken 64 at a time, slot rank j outer, lanes inner
 // and k_stats_sparse sums each bucket's list, split into parts, in list order.
@@ -3393,12 +3414,15 @@ constexpr int kSparseDepth = 3;
 static_assert(kSparseDepth <= 3, "records are stored four batches ahead");
 
 // logz2 given: also the unit's sum of log2 Z, each lane its points in order,
-// the lanes by a fixed butterfly.
+// the lanes by a fixed butterfly; bmask given: the unit's points with a block
+// for the dense statistics.
 __global__ __launch_bounds__(64) void k_sparse_count(const unsigned short* __restrict__ cslot,
                                                      int64_t n, int64_t upts, int nb, int lcb,
                                                      int nunit, int* __restrict__ gcnt,
                                                      const double* __restrict__ logz2,
-                                                     double* __restrict__ ll_part) {
+                                                     double* __restrict__ ll_part,
+                                                     const unsigned long long* __restrict__ bmask,
+                                                     int* __restrict__ dcnt) {
   extern __shared__ int lc[];
   const int u = blockIdx.x, lane = threadIdx.x;
   for (int b = lane; b < nb; b += 64) lc[b] = 0;
@@ -3406,9 +3430,11 @@ __global__ __launch_bounds__(64) void k_sparse_count(const unsigned short* __res
   const int64_t p0 = (int64_t)u * upts;
   const int64_t p1 = p0 + upts < n ? p0 + upts : n;
   double ll = 0.0;
+  int dc = 0;
   for (int64_t p = p0 + lane; p < p1; p += 64) {
     const ushort4 s4 = *reinterpret_cast<const ushort4*>(cslot + p * kT);
     if (logz2 != nullptr) ll += logz2[p];
+    if (bmask != nullptr) dc += bmask[p] != 0ull ? 1 : 0;
     if (s4.x != kNoSlot) atomicAdd(&lc[s4.x >> lcb], 1);
     if (s4.y != kNoSlot) atomicAdd(&lc[s4.y >> lcb], 1);
     if (s4.z != kNoSlot) atomicAdd(&lc[s4.z >> lcb], 1);
@@ -3420,49 +3446,96 @@ __global__ __launch_bounds__(64) void k_sparse_count(const unsigned short* __res
     for (int off = 32; off > 0; off >>= 1) ll += __shfl_xor(ll, off);
     if (lane == 0) ll_part[u] = ll;
   }
+  if (bmask != nullptr) {
+    for (int off = 32; off > 0; off >>= 1) dc += __shfl_xor(dc, off);
+    if (lane == 0) dcnt[u] = dc;
+  }
 }
 
-// Exclusive prefix of cnt[0 .. tot) into off[0 .. tot] (64-bit), off[tot] =
-// total.  One workgroup of 1024 threads, 4096 entries per round.
-__global__ __launch_bounds__(1024) void k_sparse_scan(const int* __restrict__ cnt, int tot,
-                                                      int64_t* __restrict__ off) {
-  __shared__ int64_t wsum[16];
-  __shared__ int64_t carry_s;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid == 0) carry_s = 0;
+// Pairs per bucket: tot[b] = the sum of row b of cnt [nb][nunit].
+__global__ __launch_bounds__(256) void k_sparse_total(const int* __restrict__ cnt, int nunit,
+                                                      int64_t* __restrict__ tot) {
+  __shared__ int64_t ws[4];
+  const int* row = cnt + (size_t)blockIdx.x * nunit;
+  int64_t v = 0;
+  for (int u = threadIdx.x; u < nunit; u += 256) v += row[u];
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = v;
   __syncthreads();
-  for (int base = 0; base < tot; base += 4096) {
-    int64_t v[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int i = base + 4 * tid + j;
-      v[j] = i < tot ? (int64_t)(unsigned)cnt[i] : 0;
-    }
-    const int64_t own = v[0] + v[1] + v[2] + v[3];
+  if (threadIdx.x == 0) tot[blockIdx.x] = ws[0] + ws[1] + ws[2] + ws[3];
+}
+
+// Exclusive prefix of cnt [nb][nunit] (bucket-major) into off, off[nb nunit] = the
+// total: workgroup b adds the buckets before it up and scans its own row (one
+// workgroup over all of it took 85 to 170 us of 2^18 entries).  Workgroup nb
+// (dcnt given): the same for the units' dense points, doff[nunit] and
+// *dtotal = their number.
+__global__ __launch_bounds__(256) void k_sparse_offsets(
+    const int* __restrict__ cnt, int nb, int nunit, const int64_t* __restrict__ tot,
+    int64_t* __restrict__ off, const int* __restrict__ dcnt, int64_t* __restrict__ doff,
+    int64_t* __restrict__ dtotal) {
+  __shared__ int64_t ws[4];
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const bool dense = b == nb;
+  const int* row = dense ? dcnt : cnt + (size_t)b * nunit;
+  int64_t* out = dense ? doff : off + (size_t)b * nunit;
+  int64_t run = 0;
+  if (!dense) {
+    for (int c = tid; c < b; c += 256) run += tot[c];
+    for (int o = 32; o > 0; o >>= 1) run += __shfl_xor(run, o);
+    if (lane == 0) ws[wave] = run;
+    __syncthreads();
+    run = ws[0] + ws[1] + ws[2] + ws[3];
+    __syncthreads();
+  }
+  for (int u0 = 0; u0 < nunit; u0 += 256) {
+    const int u = u0 + tid;
+    const int64_t own = u < nunit ? row[u] : 0;
     int64_t inc = own;
     for (int o = 1; o < 64; o <<= 1) {
       const int64_t t = __shfl_up(inc, o);
       if (lane >= o) inc += t;
     }
-    if (lane == 63) wsum[wave] = inc;
+    if (lane == 63) ws[wave] = inc;
     __syncthreads();
-    int64_t before = carry_s, all = 0;
-    for (int w = 0; w < 16; ++w) {
-      if (w < wave) before += wsum[w];
-      all += wsum[w];
-    }
-    int64_t run = before + inc - own;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int i = base + 4 * tid + j;
-      if (i < tot) off[i] = run;
-      run += v[j];
-    }
-    __syncthreads();                            // wsum and carry_s read by all
-    if (tid == 0) carry_s += all;
+    int64_t before = run;
+    for (int w = 0; w < wave; ++w) before += ws[w];
+    if (u < nunit) out[u] = before + inc - own;
+    run += ws[0] + ws[1] + ws[2] + ws[3];
     __syncthreads();
   }
-  if (tid == 0) off[tot] = carry_s;
+  if (tid == 0) {
+    if (dense) {
+      out[nunit] = run;
+      *dtotal = run;
+    } else if (b == nb - 1) {
+      off[(size_t)nb * nunit] = run;
+    }
+  }
+}
+
+// The dense list: (point, blocks) of every point with a block for the dense
+// statistics, in point order (unit u from doff[u] on).  The points' masks
+// become those of the light components (none yet).
+__global__ __launch_bounds__(64) void k_dense_list(unsigned long long* __restrict__ bmask,
+                                                   int64_t n, int64_t upts,
+                                                   const int64_t* __restrict__ doff,
+                                                   ulonglong2* __restrict__ dlist) {
+  const int u = blockIdx.x, lane = threadIdx.x;
+  const int64_t p0 = (int64_t)u * upts;
+  const int64_t p1 = p0 + upts < n ? p0 + upts : n;
+  int64_t pos = doff[u];
+  for (int64_t pb = p0; pb < p1; pb += 64) {
+    const int64_t p = pb + lane;
+    const unsigned long long m = p < p1 ? bmask[p] : 0ull;
+    const unsigned long long has = __ballot(m != 0ull);
+    if (m != 0ull) {
+      dlist[pos + __popcll(has & ((1ull << lane) - 1ull))] =
+          make_ulonglong2((unsigned long long)p, m);
+      bmask[p] = 0ull;
+    }
+    pos += __popcll(has);
+  }
 }
 
 // Buckets up to which k_sparse_scatter keeps its unit's list positions in LDS
@@ -3782,8 +3855,9 @@ __global__ __launch_bounds__(256) void k_stats_ill(
     const float* __restrict__ dmu, const double* __restrict__ dh,
     const double* __restrict__ cdir, const int* __restrict__ counts,
     const double* __restrict__ logz2, const unsigned char* __restrict__ iflag,
-    const unsigned char* __restrict__ lflag, const unsigned short* __restrict__ cslot,
-    const int* __restrict__ small_pos, double* __restrict__ part) {
+    const unsigned char* __restrict__ lflag, const unsigned long long* __restrict__ lmask,
+    const unsigned short* __restrict__ cslot, const int* __restrict__ small_pos,
+    const int* __restrict__ small_slot, int gsh, double* __restrict__ part) {
   constexpr int P = D64 + 4, NJ = D64 / 64, STRIDE = 1 + 2 * D64;
   constexpr int PT = ill_pt(D64), CW = ill_cw(D64), ICB = 4 * CW;
   constexpr int WIN = 16 * 256;                 // points scanned per queue window
@@ -3819,7 +3893,16 @@ __global__ __launch_bounds__(256) void k_stats_ill(
   // log-density there came within 2^-72 of log2 Z), and the point's stored
   // exact pairs are left out there: the exact-pair pass has summed them.  At
   // every other point each light component is either stored or has
-  // r < 2^-64.
+  // r < 2^-64.  lmask holds the 64-component blocks in which that happened:
+  // a point is taken only for the light components of those blocks (the list is
+  // in slot order, so this workgroup's lie in the blocks from its first one's to
+  // its last one's).
+  unsigned long long want = ~0ull;
+  if (small_pos != nullptr && lmask != nullptr) {
+    const int last = (kb + 1) * ICB < n_ill ? (kb + 1) * ICB - 1 : n_ill - 1;
+    const int b0 = small_slot[kb * ICB] >> gsh, b1 = small_slot[last] >> gsh;
+    want = (~0ull << b0) & (~0ull >> (63 - b1));
+  }
   int qn = 0;
   for (int64_t wb0 = p0; wb0 < p1; wb0 += WIN) {
     const int64_t we = wb0 + WIN < p1 ? wb0 + WIN : p1;
@@ -3832,6 +3915,7 @@ __global__ __launch_bounds__(256) void k_stats_ill(
         bool take = pt < we;
         if (take && iflag != nullptr) take = iflag[pt] != 0;
         if (take && small_pos != nullptr) take = lflag[pt] != 0;
+        if (take && small_pos != nullptr && lmask != nullptr) take = (lmask[pt] & want) != 0ull;
         if (take) sel |= 1u << e;
       }
       const int cnt = __popc(sel);
@@ -4766,22 +4850,26 @@ __global__ __launch_bounds__(256) void k_small_mass(
     const double* __restrict__ part_s, const int* __restrict__ counts,
     const int* __restrict__ well_idx, const double* __restrict__ cdir, int nparts, int sbk,
     int D64, unsigned char* __restrict__ flag) {
-  const int slot = blockIdx.x * blockDim.x + threadIdx.x;
+  // one wave a slot: the parts over the lanes, then a fixed butterfly
+  const int slot = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6), lane = threadIdx.x & 63;
   if (slot >= counts[0]) return;
   const size_t stride = 1 + 2 * (size_t)D64;
   const double* ps = part_s + ((size_t)(slot / sbk) * nparts * sbk + (slot % sbk)) * stride;
-  const double m = sum_strided(ps, nparts, (size_t)sbk * stride, 0.0);
+  double m = 0.0;
+  for (int p = lane; p < nparts; p += 64) m += ps[(size_t)p * sbk * stride];
+  for (int o = 32; o > 0; o >>= 1) m += __shfl_xor(m, o);
   const bool live = cdir[well_idx[slot]] > -INFINITY;
-  flag[slot] = (live && m < kSmallMass) ? 1 : 0;
+  if (lane == 0) flag[slot] = (live && m < kSmallMass) ? 1 : 0;
 }
 
 // The flagged slots in slot order: pos[slot] = index in the list or -1,
-// idx[i] = the component, cnt[1] = the list's length (cnt[0] = 0), so that
+// idx[i] = the component, slots[i] its slot, cnt[1] = the list's length (cnt[0] = 0), so that
 // (idx, cnt) take the place of (ill_idx, counts) for k_stats_ill.
 __global__ __launch_bounds__(1024) void k_small_list(const unsigned char* __restrict__ flag,
                                                      const int* __restrict__ counts,
                                                      const int* __restrict__ well_idx,
                                                      int* __restrict__ pos, int* __restrict__ idx,
+                                                     int* __restrict__ slots,
                                                      int* __restrict__ cnt) {
   __shared__ int wsum[16];
   const int nw = counts[0];
@@ -4808,6 +4896,7 @@ __global__ __launch_bounds__(1024) void k_small_list(const unsigned char* __rest
     if (flag[sl]) {
       pos[sl] = p;
       idx[p] = well_idx[sl];
+      slots[p] = sl;
       ++p;
     } else {
       pos[sl] = -1;
@@ -4825,7 +4914,7 @@ __global__ __launch_bounds__(256) void k_reduce_stats(
     const int* __restrict__ counts, const int* __restrict__ well_idx,
     const int* __restrict__ ill_idx, int nch, int wbk, int nparts, int sbk, int grid_i, int ibk,
     int ipt, int64_t n, int k, int d, int D64, const int* __restrict__ small_pos,
-    const double* __restrict__ part_x, const int* __restrict__ small_cnt,
+    const double* __restrict__ part_x, const int* __restrict__ small_cnt, int dense_listed,
     double* __restrict__ nk, double* __restrict__ s, double* __restrict__ q) {
   const int64_t width = 1 + 2 * (int64_t)d;
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -4853,7 +4942,8 @@ __global__ __launch_bounds__(256) void k_reduce_stats(
       acc = sum_strided(ps, nparts, (size_t)sbk * stride, acc);
     } else {
       const double* p = part_w + ((size_t)(slot / wbk) * nch * wbk + (slot % wbk)) * stride + off;
-      acc = sum_strided(p, nch, (size_t)wbk * stride, acc);
+      const int ech = dense_chunks(dense_points(counts, dense_listed != 0, n), dense_listed != 0, nch);
+      acc = sum_strided(p, ech, (size_t)wbk * stride, acc);
       const double* ps =
           part_s + ((size_t)(slot / sbk) * nparts * sbk + (slot % sbk)) * stride + off;
       acc = sum_strided(ps, nparts, (size_t)sbk * stride, acc);
@@ -5211,8 +5301,7 @@ struct Layout {
   int64_t n;
   int d, k, kpad, D64, m;
   bool wide;                // D64 > 256: 32-point screening tiles
-  int wbk, nch;             // well statistics: components per workgroup (64 for
-                            // k_stats_well, 16 for k_stats_wide at D64 >= 256), chunks
+  int wbk, nch;             // well statistics: components per workgroup, chunks
   int64_t chunk;
   int ibk, ipt, grid_i;     // ill set: components per block, points per tile, grid
   int sbk, lsbk, nb;        // refined pairs: bucket size (log2), buckets
@@ -5250,11 +5339,11 @@ bool make_layout(int64_t n, int d, int k, int m, Layout* L, size_t budget = 0) {
   L->wide = L->D64 > 256;
   const int stride = 1 + 2 * L->D64;
   // chunking depends only on (n, d, k), never on the device
-  L->wbk = L->D64 >= 256 ? 16 : kWB;
-  const int nwb = L->kpad / L->wbk;
+  L->wbk = 16;
+  const int nwb = L->kpad / (L->D64 >= 256 ? 16 : kWB);
   if (L->D64 < 256) {
-    // about 2048 workgroups (four rounds at two per CU) for k_stats_well, and
-    // up to 8192 while the chunks keep 65536 points or more: the blocks'
+    // about 2048 chunks of 64 components (8192 one-wave workgroups) for
+    // k_stats_well, and up to 8192 while the chunks keep 65536 points or more: the blocks'
     // shares of the points differ, and many short rounds let the workgroups
     // of the busy blocks spread over the chip and leave no long tail, while
     // a workgroup's fixed cost (its operands, its partial sums) stays small
@@ -5463,6 +5552,11 @@ CoarseView coarse_view(const Layout& L, void* ws) {
   return v;
 }
 
+// Pairs per bucket, in the region of the screening thresholds, which are not
+// read any more when the pairs are counted (8 bytes a bucket of at least 4
+// components, in 8 bytes a component).
+int64_t* sparse_totals(const Layout& L, void* ws) { return at<int64_t>(ws, L.off_thr); }
+
 // Operands, sample (large n) and the screening itself.  *smax: the most heavy
 // points of the sample with which the pass stays on.
 template <int D64, bool ISO>
@@ -5527,6 +5621,13 @@ int estep_impl(const Layout& L, const float* x, const float* w, const float* mu,
   unsigned long long* bmask = L.bmask_on ? at<unsigned long long>(ws, L.off_bmask) : nullptr;
   unsigned char* lflag = at<unsigned char>(ws, L.off_lflag);
   unsigned char* iflag = at<unsigned char>(ws, L.off_iflag);
+  // per unit of points: sum of log2 Z, first entry in the dense list, entries
+  // (20 bytes a unit of at least 256 points, in 8 bytes per 64 or 32 points)
+  const int gsh = mask_shift(kpad);
+  int64_t* doff = reinterpret_cast<int64_t*>(llpart + L.nunit);
+  int* dcnt = reinterpret_cast<int*>(doff + L.nunit + 1);
+  ulonglong2* dlist = bmask != nullptr ? at<ulonglong2>(ws, L.off_cr) : nullptr;
+  static_assert(kT * sizeof(float) >= sizeof(ulonglong2), "the dense list fits");
 
   bool tm = phase_mark(0, st);
   hipLaunchKernelGGL(k_prep_class, dim3(k), dim3(64), 0, st, w, mu, var, d, cls, cwell, cdir,
@@ -5580,14 +5681,14 @@ int estep_impl(const Layout& L, const float* x, const float* w, const float* mu,
     const CoarseView cv = coarse_view(L, ws);
     hipLaunchKernelGGL(k_refine<D64>, dim3((unsigned)cdiv(n * refine_lanes(D64), 256)), dim3(256),
                        0, st, x, n, d, cv.cand, cv.cidx, dmu, dh, cdir, counts, smax, logz2,
-                       cslot, cr, bmask, iflag, lflag);
+                       cslot, cr, bmask, iflag, lflag, gsh);
   }
   bool launched = false;
   if constexpr (screen_split(D64)) {
     if (L.iso && L.refine) {
       hipLaunchKernelGGL((k_logz<D64, true, true>), dim3((unsigned)L.n_wg_logz), dim3(256), 0, st,
                          x, n, d, vec4, wp, wpb, cw, thr, well_idx, ill_idx, dmu, dh, cdir, counts,
-                         logz2, cslot, cr, bmask, iflag, lflag, hlist, smax);
+                         logz2, cslot, cr, bmask, iflag, lflag, hlist, smax, gsh);
       launched = true;
     }
   }
@@ -5595,11 +5696,11 @@ int estep_impl(const Layout& L, const float* x, const float* w, const float* mu,
     if (L.refine)
       hipLaunchKernelGGL((k_logz<D64, true, false>), dim3((unsigned)L.n_wg_logz), dim3(256), 0, st,
                          x, n, d, vec4, wp, wpb, cw, thr, well_idx, ill_idx, dmu, dh, cdir, counts,
-                         logz2, cslot, cr, bmask, iflag, lflag, hlist, smax);
+                         logz2, cslot, cr, bmask, iflag, lflag, hlist, smax, gsh);
     else
       hipLaunchKernelGGL((k_logz<D64, false, false>), dim3((unsigned)L.n_wg_logz), dim3(256), 0,
                          st, x, n, d, vec4, wp, wpb, cw, thr, well_idx, ill_idx, dmu, dh, cdir,
-                         counts, logz2, cslot, cr, bmask, iflag, lflag, hlist, smax);
+                         counts, logz2, cslot, cr, bmask, iflag, lflag, hlist, smax, gsh);
   }
   tm = phase_mark(2, st) && tm;
   {
@@ -5609,10 +5710,20 @@ int estep_impl(const Layout& L, const float* x, const float* w, const float* mu,
     SPair* slist = at<SPair>(ws, L.off_slist);
     const size_t lds = (size_t)L.nb * sizeof(int);
     hipLaunchKernelGGL(k_sparse_count, dim3((unsigned)L.nunit), dim3(64), lds, st, cslot, n,
-                       L.upts, L.nb, L.lsbk, L.nunit, scnt, logz2, llpart);
-    hipLaunchKernelGGL(k_sparse_scan, dim3(1), dim3(1024), 0, st, scnt, L.nb * L.nunit, soff);
+                       L.upts, L.nb, L.lsbk, L.nunit, scnt, logz2, llpart, bmask, dcnt);
+    int64_t* stot = sparse_totals(L, ws);
+    hipLaunchKernelGGL(k_sparse_total, dim3((unsigned)L.nb), dim3(256), 0, st, scnt, L.nunit,
+                       stot);
+    hipLaunchKernelGGL(k_sparse_offsets, dim3((unsigned)(L.nb + (bmask != nullptr ? 1 : 0))),
+                       dim3(256), 0, st, scnt, L.nb, L.nunit, stot, soff, dcnt, doff,
+                       reinterpret_cast<int64_t*>(counts + kCntDense));
     hipLaunchKernelGGL(k_sparse_scatter, dim3((unsigned)L.nunit), dim3(64), scatter_lds(L.nb), st,
                        cslot, cr, n, L.upts, L.nb, L.lsbk, L.nunit, soff, slist);
+    // the scatter was the last reader of the responsibilities: their region
+    // becomes the dense list
+    if (bmask != nullptr)
+      hipLaunchKernelGGL(k_dense_list, dim3((unsigned)L.nunit), dim3(64), 0, st, bmask, n, L.upts,
+                         doff, dlist);
     hipLaunchKernelGGL(k_stats_sparse<D64>, dim3((unsigned)(L.nb * L.nparts)),
                        dim3(64 * kSparseWaves), 0, st,
                        x, n, d, slist, soff, L.nunit, L.nparts, part_s);
@@ -5628,43 +5739,44 @@ int estep_impl(const Layout& L, const float* x, const float* w, const float* mu,
   if (L.refine) {
     sflag = at<unsigned char>(ws, L.off_sflag);
     spos = at<int>(ws, L.off_spos);
-    hipLaunchKernelGGL(k_small_mass, dim3((unsigned)cdiv(k, 256)), dim3(256), 0, st, part_s,
+    hipLaunchKernelGGL(k_small_mass, dim3((unsigned)cdiv(k, 4)), dim3(256), 0, st, part_s,
                        counts, well_idx, cdir, L.nparts, L.sbk, D64, sflag);
     hipLaunchKernelGGL(k_small_list, dim3(1), dim3(1024), 0, st, sflag, counts, well_idx, spos,
-                       sidx, scnt2);
+                       sidx, cls, scnt2);
   }
   if constexpr (D64 < 256) {
     if (L.iso)
-      hipLaunchKernelGGL((k_stats_well<D64, true>), dim3((unsigned)((kpad / kWB) * L.nch)),
-                         dim3(256), 0, st, x, n, d, vec4, wq, cw, counts, logz2, cslot, bmask,
-                         L.nch, L.chunk, sflag, lflag, part_w);
+      hipLaunchKernelGGL((k_stats_well<D64, true>), dim3((unsigned)((kpad / 16) * L.nch)),
+                         dim3(64), 0, st, x, n, d, vec4, wq, counts, logz2, cslot, dlist, L.nch,
+                         gsh, sflag, lflag, bmask, part_w);
     else
-      hipLaunchKernelGGL((k_stats_well<D64, false>), dim3((unsigned)((kpad / kWB) * L.nch)),
-                         dim3(256), 0, st, x, n, d, vec4, wq, cw, counts, logz2, cslot, bmask,
-                         L.nch, L.chunk, sflag, lflag, part_w);
+      hipLaunchKernelGGL((k_stats_well<D64, false>), dim3((unsigned)((kpad / 16) * L.nch)),
+                         dim3(64), 0, st, x, n, d, vec4, wq, counts, logz2, cslot, dlist, L.nch,
+                         gsh, sflag, lflag, bmask, part_w);
   } else {
     if (L.iso)
       hipLaunchKernelGGL((k_stats_wide<D64, true>), dim3((unsigned)((kpad / 16) * L.nch)),
                          dim3(64 * (D64 / 128)), 0, st, x, n, d, vec4, wq, cwell, well_idx,
-                         counts, logz2, cslot, bmask, L.nch, L.chunk, sflag, lflag, part_w);
+                         counts, logz2, cslot, dlist, L.nch, gsh, sflag, lflag, bmask, part_w);
     else
       hipLaunchKernelGGL((k_stats_wide<D64, false>), dim3((unsigned)((kpad / 16) * L.nch)),
                          dim3(64 * (D64 / 128)), 0, st, x, n, d, vec4, wq, cwell, well_idx,
-                         counts, logz2, cslot, bmask, L.nch, L.chunk, sflag, lflag, part_w);
+                         counts, logz2, cslot, dlist, L.nch, gsh, sflag, lflag, bmask, part_w);
   }
   tm = phase_mark(4, st) && tm;
   hipLaunchKernelGGL(k_stats_ill<D64>, dim3((unsigned)L.grid_i), dim3(256), 0, st, x, n, d, vec4,
                      ill_idx, dmu, dh, cdir, counts, logz2, iflag, nullptr, nullptr, nullptr,
-                     part_i);
+                     nullptr, nullptr, gsh, part_i);
   if (L.refine)
     hipLaunchKernelGGL(k_stats_ill<D64>, dim3((unsigned)L.grid_i), dim3(256), 0, st, x, n, d,
-                       vec4, sidx, dmu, dh, cdir, scnt2, logz2, nullptr, lflag, cslot, spos,
-                       part_x);
+                       vec4, sidx, dmu, dh, cdir, scnt2, logz2, nullptr, lflag, bmask, cslot,
+                       spos, cls, gsh, part_x);
   {
     const int64_t tot = 2 * (int64_t)k * (1 + 2 * (int64_t)d);
     hipLaunchKernelGGL(k_reduce_stats, dim3((unsigned)cdiv(tot, 256)), dim3(256), 0, st, part_w,
                        part_s, part_i, counts, well_idx, ill_idx, L.nch, L.wbk, L.nparts, L.sbk,
-                       L.grid_i, L.ibk, L.ipt, n, k, d, D64, spos, part_x, scnt2, nk, s, q);
+                       L.grid_i, L.ibk, L.ipt, n, k, d, D64, spos, part_x, scnt2,
+                       dlist != nullptr ? 1 : 0, nk, s, q);
   }
   hipLaunchKernelGGL(k_reduce_ll, dim3(1), dim3(1024), 0, st, llpart, (int64_t)L.nunit, loglik,
                      ll_accumulate);
@@ -5783,8 +5895,12 @@ int kmeans_impl(const Layout& L, const float* x, int n_iters, float var_floor, f
                        cslot, cr);
     const size_t lds = (size_t)L.nb * sizeof(int);
     hipLaunchKernelGGL(k_sparse_count, dim3((unsigned)L.nunit), dim3(64), lds, st, cslot, n,
-                       L.upts, L.nb, L.lsbk, L.nunit, scnt, nullptr, nullptr);
-    hipLaunchKernelGGL(k_sparse_scan, dim3(1), dim3(1024), 0, st, scnt, L.nb * L.nunit, soff);
+                       L.upts, L.nb, L.lsbk, L.nunit, scnt, nullptr, nullptr, nullptr, nullptr);
+    int64_t* stot = sparse_totals(L, ws);
+    hipLaunchKernelGGL(k_sparse_total, dim3((unsigned)L.nb), dim3(256), 0, st, scnt, L.nunit,
+                       stot);
+    hipLaunchKernelGGL(k_sparse_offsets, dim3((unsigned)L.nb), dim3(256), 0, st, scnt, L.nb,
+                       L.nunit, stot, soff, nullptr, nullptr, nullptr);
     hipLaunchKernelGGL(k_sparse_scatter, dim3((unsigned)L.nunit), dim3(64), scatter_lds(L.nb), st,
                        cslot, cr, n, L.upts, L.nb, L.lsbk, L.nunit, soff, slist);
     hipLaunchKernelGGL(k_stats_sparse<D64>, dim3((unsigned)(L.nb * L.nparts)),

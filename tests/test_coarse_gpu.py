@@ -1,6 +1,6 @@
 """The one-product screening of the E-step and of the assignment (k_coarse, k_refine,
-k_assign_refine and the points they hand to the two- or three-product passes) against the fp64 checker, at the edges of its tiles and of its rules: workgroups of
-128 and 256 points, blocks of 32 components, widths with and without a remainder, points with
+k_assign_refine and the points they hand to the two- or three-product passes) against the fp64
+checker, at the edges of its tiles and of its rules: workgroups of 128 and 256 points, blocks of 32 components, widths with and without a remainder, points with
 more components in reach than a list or a lane state holds, the sample that switches the pass
 off, and weights near the end of the float range.  The workspace starts as garbage, so a point
 that no kernel wrote would show."""
