@@ -364,13 +364,13 @@ __device__ __forceinline__ int64_t dense_points(const int* __restrict__ counts, 
   return listed ? *reinterpret_cast<const int64_t*>(counts + kCntDense) : n;
 }
 // Chunks they are split into: at most nch, and for a short list no more than
-// keep 256 points a chunk (a chunk's partial sums are written and read again;
+// keep 128 points a chunk (a chunk's partial sums are written and read again;
 // 1024 and 4096 left too few workgroups at n = 1e5: 312 us against 206 with the
 // chunks of the whole range).  The same in the dense passes and
 // k_reduce_stats.
 __device__ __forceinline__ int dense_chunks(int64_t np, bool listed, int nch) {
   if (!listed) return nch;
-  const int64_t c = (np + 255) / 256;
+  const int64_t c = (np + 127) / 128;
   return c < 1 ? 1 : (c > nch ? nch : (int)c);
 }
 __device__ __forceinline__ int64_t heavy_count(const int* __restrict__ counts) {
@@ -425,25 +425,37 @@ __global__ __launch_bounds__(256) void k_prep_scan(const int* __restrict__ cls, 
                                                    int* __restrict__ well_idx,
                                                    int* __restrict__ ill_idx,
                                                    int* __restrict__ counts) {
-  __shared__ int cw[256], ci[256];
-  const int t = threadIdx.x;
+  __shared__ int sw[4], si[4];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int b = (int)((int64_t)k * t / 256), e = (int)((int64_t)k * (t + 1) / 256);
   int nw = 0, ni = 0, wild = 0;
   for (int c = b; c < e; ++c) {
-    nw += (cls[c] & 3) == 0;
-    ni += (cls[c] & 3) == 1;
-    wild |= cls[c] & 4;
+    const int v = cls[c];
+    nw += (v & 3) == 0;
+    ni += (v & 3) == 1;
+    wild |= v & 4;
   }
-  cw[t] = nw;
-  ci[t] = ni;
   wild = __syncthreads_or(wild);
-  if (t == 0) {
-    int aw = 0, ai = 0;
-    for (int i = 0; i < 256; ++i) {
-      const int x = cw[i], y = ci[i];
-      cw[i] = aw; ci[i] = ai;
-      aw += x; ai += y;
+  int iw = nw, ii = ni;                         // inclusive over the wave
+  for (int o = 1; o < 64; o <<= 1) {
+    const int tw = __shfl_up(iw, o), tii = __shfl_up(ii, o);
+    if (lane >= o) {
+      iw += tw;
+      ii += tii;
     }
+  }
+  if (lane == 63) {
+    sw[wave] = iw;
+    si[wave] = ii;
+  }
+  __syncthreads();
+  int pw = iw - nw, pi = ii - ni;
+  for (int w = 0; w < wave; ++w) {
+    pw += sw[w];
+    pi += si[w];
+  }
+  if (t == 0) {
+    const int aw = sw[0] + sw[1] + sw[2] + sw[3], ai = si[0] + si[1] + si[2] + si[3];
     counts[0] = aw;
     counts[1] = ai;
     counts[2] = (aw + kBK - 1) / kBK;
@@ -452,24 +464,35 @@ __global__ __launch_bounds__(256) void k_prep_scan(const int* __restrict__ cls, 
     counts[kCntWild] = wild != 0;
     counts[kCntHeavy] = counts[kCntHeavy + 1] = 0;
   }
-  __syncthreads();
-  int pw = cw[t], pi = ci[t];
   for (int c = b; c < e; ++c) {
     if ((cls[c] & 3) == 0) well_idx[pw++] = c;
     else if ((cls[c] & 3) == 1) ill_idx[pi++] = c;
   }
 }
 
+// Points per screening workgroup: two 32-point MFMA tiles while a 64-point X
+// tile fits in LDS next to the per-point state (D64 <= 256), one tile above.
+__host__ __device__ constexpr int logz_tiles(int D64) { return D64 <= 256 ? 2 : 1; }
+// The screening contraction runs on split bf16 MFMA from a split X tile in LDS
+// while 64 points of it fit beside the post-screening state (D64 <= 128).  Its
+// error, typically about 2^-16.5 of a product over D64/8 accumulation steps, is of
+// the order of the fp32 chain's (2^-24 per step of a running sum of some hundred
+// log2 units over D64 steps), so the refinement rules are the same for both.
+__host__ __device__ constexpr bool screen_b16(int D64) { return D64 <= 128; }
+// D64 > 256 (32-point tiles): split-bf16 screening too, the operands of the
+// points split on the fly from the fp32 tile (logz_group16)
+__host__ __device__ constexpr bool screen_x16(int D64) { return D64 > 256; }
+__host__ __device__ constexpr bool screen_split(int D64) { return screen_b16(D64) || screen_x16(D64); }
+
 // Packed expanded-form operand: wp[(kb*(D64/4) + q)*64 + lane] is the float4 of
 // MFMA steps 4q..4q+3 for lane `lane` of component block kb.
 template <int D64>
-__global__ __launch_bounds__(256) void k_prep_pack_well(
-    const float* __restrict__ mu, const float* __restrict__ var, int d, int kpad,
+__device__ __forceinline__ void pack_well(
+    int64_t t, const float* __restrict__ mu, const float* __restrict__ var, int d, int kpad,
     const double* __restrict__ cwell, const float2* __restrict__ cthr,
     const int* __restrict__ counts, const int* __restrict__ well_idx, float4* __restrict__ wp,
     float* __restrict__ cw, float2* __restrict__ thr) {
   constexpr int QQ = D64 / 4, QH = D64 / 8;
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= (int64_t)kpad * QQ * 2) return;   // kpad/32 blocks * QQ * 64 lanes
   const int lane = (int)(t & 63);
   const int q = (int)((t >> 6) % QQ);
@@ -479,8 +502,10 @@ __global__ __launch_bounds__(256) void k_prep_pack_well(
   const int comp = slot < nw ? well_idx[slot] : -1;
   const bool xpart = q < QH;
   const int qq = xpart ? q : q - QH;
+  // the fp32 operand is read by the fp32 screening alone; the biases and
+  // thresholds below by every one
   float vals[4];
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < 4 && !screen_split(D64); ++i) {
     const int j = 8 * qq + 4 * h + i;
     float v = 0.0f;
     if (comp >= 0 && j < d) {
@@ -489,10 +514,10 @@ __global__ __launch_bounds__(256) void k_prep_pack_well(
     }
     vals[i] = v;
   }
-  wp[t] = make_float4(vals[0], vals[1], vals[2], vals[3]);
+  if constexpr (!screen_split(D64)) wp[t] = make_float4(vals[0], vals[1], vals[2], vals[3]);
   if (q == 0 && h == 0) {
     cw[slot] = comp >= 0 ? (float)cwell[comp] : -INFINITY;
-    thr[slot] = comp >= 0 ? cthr[comp] : make_float2(0.0f, 0.0f);
+    if (thr != nullptr) thr[slot] = comp >= 0 ? cthr[comp] : make_float2(0.0f, 0.0f);
   }
 }
 
@@ -513,11 +538,10 @@ __host__ __device__ constexpr int screen_steps() {
 // split tile) and zeros elsewhere.
 
 template <int D64, bool ISO>
-__global__ __launch_bounds__(256) void k_prep_pack_b16(
-    const float* __restrict__ mu, const float* __restrict__ var, int d, int kpad,
+__device__ __forceinline__ void pack_b16(
+    int64_t t, const float* __restrict__ mu, const float* __restrict__ var, int d, int kpad,
     const int* __restrict__ counts, const int* __restrict__ well_idx, bf16x8* __restrict__ wpb) {
   constexpr int NS16 = screen_steps<D64, ISO>();
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= (int64_t)(kpad / kBK) * NS16 * 64) return;
   const int lane = (int)(t & 63);
   const int s = (int)((t >> 6) % NS16);
@@ -575,14 +599,13 @@ constexpr int wq_steps(int D64) { return D64 / 2 + D64 / 32; }
 constexpr int wq_steps_iso(int D64) { return D64 / 4 + D64 / 16; }
 
 template <int D64, bool ISO>
-__global__ __launch_bounds__(256) void k_prep_pack_w16(
-    const float* __restrict__ w, const float* __restrict__ mu, const float* __restrict__ var,
+__device__ __forceinline__ void pack_w16(
+    int64_t t, const float* __restrict__ w, const float* __restrict__ mu, const float* __restrict__ var,
     int d, int kpad, const int* __restrict__ counts, const int* __restrict__ well_idx,
     float* __restrict__ wq) {
   constexpr int NS = D64 / 4, NGB = D64 / 32, WQS = ISO ? wq_steps_iso(D64) : wq_steps(D64);
   // first bias step
   constexpr int SB = ISO ? NS + NGB : 2 * NS;
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= (int64_t)(kpad / 16) * WQS * 64) return;
   const int lane = (int)(t & 63);
   const int s = (int)((t >> 6) % WQS);
@@ -627,10 +650,9 @@ __global__ __launch_bounds__(256) void k_prep_pack_w16(
 // dmu = mu (fp32), dh = log2(e) / (2 var) (fp64), zero-padded to D64
 // dimensions; the constant is cdir (fp64, from k_prep_class).
 template <int D64>
-__global__ __launch_bounds__(256) void k_prep_pack_direct(
-    const float* __restrict__ mu, const float* __restrict__ var, int d, int k,
+__device__ __forceinline__ void pack_direct(
+    int64_t t, const float* __restrict__ mu, const float* __restrict__ var, int d, int k,
     float* __restrict__ dmu, double* __restrict__ dh) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= (int64_t)k * D64) return;
   const int comp = (int)(t / D64), j = (int)(t % D64);
   float m = 0.0f;
@@ -644,20 +666,6 @@ __global__ __launch_bounds__(256) void k_prep_pack_direct(
 }
 
 // ---------------------------------------------------------------- Step 1: log-normalisers
-// Points per screening workgroup: two 32-point MFMA tiles while a 64-point X
-// tile fits in LDS next to the per-point state (D64 <= 256), one tile above.
-__host__ __device__ constexpr int logz_tiles(int D64) { return D64 <= 256 ? 2 : 1; }
-// The screening contraction runs on split bf16 MFMA from a split X tile in LDS
-// while 64 points of it fit beside the post-screening state (D64 <= 128).  Its
-// error, typically about 2^-16.5 of a product over D64/8 accumulation steps, is of
-// the order of the fp32 chain's (2^-24 per step of a running sum of some hundred
-// log2 units over D64 steps), so the refinement rules are the same for both.
-__host__ __device__ constexpr bool screen_b16(int D64) { return D64 <= 128; }
-// D64 > 256 (32-point tiles): split-bf16 screening too, the operands of the
-// points split on the fly from the fp32 tile (logz_group16)
-__host__ __device__ constexpr bool screen_x16(int D64) { return D64 > 256; }
-__host__ __device__ constexpr bool screen_split(int D64) { return screen_b16(D64) || screen_x16(D64); }
-
 // One software-pipelined step of a screening pass for one wave: when MF, the
 // log-densities of the NT 32-point tiles against component block wpb are
 // formed on MFMA into n0 (and n1), one chain per tile: bias first, then for
@@ -1998,14 +2006,13 @@ __host__ __device__ constexpr int coarse_groups(int D64) {
 // cbias[slot] = c + b, cb2[slot] = 2 b, cidx[slot] = the component; slots past the
 // last component have weights 0 and a bias far below everything.
 template <int D64, bool ISO>
-__global__ __launch_bounds__(256) void k_prep_pack_coarse(
-    const float* __restrict__ mu, const float* __restrict__ var, int d, int kpad,
+__device__ __forceinline__ void pack_coarse(
+    int64_t t, const float* __restrict__ mu, const float* __restrict__ var, int d, int kpad,
     const double* __restrict__ cwell, const double* __restrict__ cdir,
     const int* __restrict__ counts, const int* __restrict__ well_idx,
     const int* __restrict__ ill_idx, bf16x8* __restrict__ wpc, float* __restrict__ cbias,
     float* __restrict__ cb2, int* __restrict__ cidx) {
   constexpr int NS = coarse_steps<D64, ISO>(), NX = D64 / 32;
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= (int64_t)(kpad / 16) * NS * 64) return;
   const int lane = (int)(t & 63), s = (int)((t >> 6) % NS), gr = (int)((t >> 6) / NS);
   const int slot = gr * 16 + (lane & 15), k4 = lane >> 4;
@@ -2054,6 +2061,76 @@ __global__ __launch_bounds__(256) void k_prep_pack_coarse(
     cb2[slot] = __double2float_ru(2.0 * b);
     cidx[slot] = comp;
   }
+}
+
+// Per well slot, the terms of its error bound in the assignment's two-pass
+// screening: (cdir_j, A_j) in log2 units; (-inf, 0) for the padding slots.
+__device__ __forceinline__ void pack_slots(int64_t slot, const double* __restrict__ cwell,
+                                           const double* __restrict__ cdir,
+                                           const int* __restrict__ counts,
+                                           const int* __restrict__ well_idx, int kpad,
+                                           float2* __restrict__ ca) {
+  if (slot >= kpad) return;
+  float2 r = make_float2(-INFINITY, 0.0f);
+  if (slot < counts[0]) {
+    const int comp = well_idx[slot];
+    const double c = cdir[comp], cw = cwell[comp];
+    // rounded up to fp32: the bound only grows
+    r = make_float2(__double2float_ru(c), __double2float_ru(5.0 * (c - cw) + fabs(cw)));
+  }
+  ca[slot] = r;
+}
+
+// Every packed operand of a call in one launch, a range of workgroups each (as
+// five or six launches they took 4 to 5 us each, a sixth of a small call):
+// blocks[i] workgroups for part i, 0 for the parts that the call does not need.
+struct PackArgs {
+  int blocks[6];            // well, b16, w16, direct, coarse, slots
+  const float *w, *mu, *var;
+  int d, k, kpad;
+  const double *cwell, *cdir;
+  const float2* cthr;
+  const int *counts, *well_idx, *ill_idx;
+  float4* wp;
+  float* cw;
+  float2* thr;              // slots: the assignment's (cdir, A) in its place
+  bf16x8* wpb;
+  float* wq;
+  float* dmu;
+  double* dh;
+  bf16x8* wpc;
+  float *cbias, *cb2;
+  int* cidx;
+};
+
+// ISOB, ISOW, ISOC: tied variances in the bf16 screening's, the dense
+// statistics' and the one-product screening's operands.
+template <int D64, bool ISOB, bool ISOW, bool ISOC>
+__global__ __launch_bounds__(256) void k_prep_pack(PackArgs a) {
+  int b = blockIdx.x;
+  auto part = [&](int i, auto&& f) {
+    if (b >= 0 && b < a.blocks[i]) f((int64_t)b * 256 + threadIdx.x);
+    b -= a.blocks[i];
+  };
+  part(0, [&](int64_t t) {
+    pack_well<D64>(t, a.mu, a.var, a.d, a.kpad, a.cwell, a.cthr, a.counts, a.well_idx, a.wp, a.cw,
+                   a.blocks[5] > 0 ? nullptr : a.thr);
+  });
+  part(1, [&](int64_t t) {
+    if constexpr (screen_split(D64))
+      pack_b16<D64, ISOB>(t, a.mu, a.var, a.d, a.kpad, a.counts, a.well_idx, a.wpb);
+  });
+  part(2, [&](int64_t t) {
+    pack_w16<D64, ISOW>(t, a.w, a.mu, a.var, a.d, a.kpad, a.counts, a.well_idx, a.wq);
+  });
+  part(3, [&](int64_t t) { pack_direct<D64>(t, a.mu, a.var, a.d, a.k, a.dmu, a.dh); });
+  part(4, [&](int64_t t) {
+    pack_coarse<D64, ISOC>(t, a.mu, a.var, a.d, a.kpad, a.cwell, a.cdir, a.counts, a.well_idx,
+                           a.ill_idx, a.wpc, a.cbias, a.cb2, a.cidx);
+  });
+  part(5, [&](int64_t t) {
+    pack_slots(t, a.cwell, a.cdir, a.counts, a.well_idx, a.kpad, a.thr);
+  });
 }
 
 // Four values of a row from dimension j on, zero past d: one 16-byte load
@@ -3481,7 +3558,11 @@ __global__ __launch_bounds__(256) void k_sparse_offsets(
   int64_t* out = dense ? doff : off + (size_t)b * nunit;
   int64_t run = 0;
   if (!dense) {
-    for (int c = tid; c < b; c += 256) run += tot[c];
+    // the buckets before: their totals, or (a short table) their entries
+    if (tot != nullptr)
+      for (int c = tid; c < b; c += 256) run += tot[c];
+    else
+      for (int c = tid; c < b * nunit; c += 256) run += cnt[c];
     for (int o = 32; o > 0; o >>= 1) run += __shfl_xor(run, o);
     if (lane == 0) ws[wave] = run;
     __syncthreads();
@@ -4087,25 +4168,6 @@ __host__ __device__ constexpr float split_eps(int D64) {
   return 2.0f * (3.0f * 0x1p-16f + (3.0f * D64 / 8.0f + 8.0f) * 0x1p-24f);
 }
 
-// Per well slot, the terms of its error bound: (cdir_j, A_j) in log2 units;
-// (-inf, 0) for the padding slots.
-__global__ __launch_bounds__(256) void k_assign_slots(const double* __restrict__ cwell,
-                                                      const double* __restrict__ cdir,
-                                                      const int* __restrict__ counts,
-                                                      const int* __restrict__ well_idx, int kpad,
-                                                      float2* __restrict__ ca) {
-  const int slot = blockIdx.x * blockDim.x + threadIdx.x;
-  if (slot >= kpad) return;
-  float2 r = make_float2(-INFINITY, 0.0f);
-  if (slot < counts[0]) {
-    const int comp = well_idx[slot];
-    const double c = cdir[comp], cw = cwell[comp];
-    // rounded up to fp32: the bound only grows
-    r = make_float2(__double2float_ru(c), __double2float_ru(5.0 * (c - cw) + fabs(cw)));
-  }
-  ca[slot] = r;
-}
-
 // Split X tile of the bf16 screening (the [x | x^2] layout of k_logz) from
 // rows row_of(0) .. row_of(63); rows >= n and dimensions >= d are zero.  The whole
 // chunks of every thread are loaded first (one memory round trip), the
@@ -4658,7 +4720,7 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_assign_collect
 // that their loads fly together; every group keeps a top-m list and a log-sum-exp
 // state of its components in ascending order, and the groups' are merged by
 // m block-wide arg-max rounds and fixed-order sums.
-constexpr int kFbBatch = 4;
+constexpr int kFbBatch = 8;
 __global__ __launch_bounds__(256) void k_assign_fallback(
     const float* __restrict__ x, int64_t n, int d, int D64, int k, const float* __restrict__ dmu,
     const double* __restrict__ dh, const double* __restrict__ cdir, int m, float tau,
@@ -5102,40 +5164,69 @@ __global__ __launch_bounds__(256) void k_kpp_update(const float* __restrict__ x,
   for (int q = wave; q < kKppRuns; q += 4) {
     const int64_t r0 = b * kKppBlock + (int64_t)kKppRun * q;
     double rs = 0.0;
-    for (int sub = 0; sub < kKppRun / 4; ++sub) {
-      const int64_t i = r0 + 4 * sub + g;
-      double v = 0.0;
-      if (i < n) {
-        const float* xr = x + i * (int64_t)d;
-        double acc = 0.0;
-        for (int c4 = l16; c4 < nc4; c4 += 16) {
-          float xv[4];
-          if (vec4) {
-            const float4 f = *reinterpret_cast<const float4*>(xr + 4 * c4);
-            xv[0] = f.x; xv[1] = f.y; xv[2] = f.z; xv[3] = f.w;
-          } else {
+    // the run's four groups of rows together: their loads are in flight at once
+    // (one group at a time the pass read 3.1 TB/s of x at n = 1e6, d = 128)
+    constexpr int NSUB = kKppRun / 4;
+    double acc[NSUB], old[NSUB];
+    int64_t row[NSUB];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) xv[e] = 4 * c4 + e < d ? xr[4 * c4 + e] : 0.0f;
-          }
+    for (int sub = 0; sub < NSUB; ++sub) {
+      row[sub] = r0 + 4 * sub + g;
+      acc[sub] = 0.0;
+      old[sub] = !first && l16 == 0 && row[sub] < n ? dist[row[sub]] : 0.0;
+    }
+    auto add = [&](int sub, int c4, const float (&xv)[4]) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            if (4 * c4 + e < d) {
-              const double u = (double)xv[e] - (double)cs[4 * c4 + e];
-              acc = fma(u, u, acc);
-            }
-          }
-        }
-        acc += __shfl_xor(acc, 8);
-        acc += __shfl_xor(acc, 4);
-        acc += __shfl_xor(acc, 2);
-        acc += __shfl_xor(acc, 1);
-        v = acc;
-        if (l16 == 0) {
-          const double old = dist[i];
-          if (!first && !(acc < old)) v = old;
-          dist[i] = v;
+      for (int e = 0; e < 4; ++e) {
+        if (4 * c4 + e < d) {
+          const double u = (double)xv[e] - (double)cs[4 * c4 + e];
+          acc[sub] = fma(u, u, acc[sub]);
         }
       }
+    };
+    if (vec4) {
+      for (int c4 = l16; c4 < nc4; c4 += 32) {
+        float4 f[2][NSUB];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int sub = 0; sub < NSUB; ++sub) {
+            // chunks past the row and rows past the data read row 0's first values
+            const bool ok = c4 + 16 * h < nc4 && row[sub] < n;
+            f[h][sub] = *reinterpret_cast<const float4*>(
+                x + (ok ? row[sub] * (int64_t)d + 4 * (c4 + 16 * h) : 0));
+          }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int sub = 0; sub < NSUB; ++sub) {
+            const float xv[4] = {f[h][sub].x, f[h][sub].y, f[h][sub].z, f[h][sub].w};
+            if (c4 + 16 * h < nc4) add(sub, c4 + 16 * h, xv);
+          }
+      }
+    } else {
+      for (int c4 = l16; c4 < nc4; c4 += 16)
+#pragma unroll
+        for (int sub = 0; sub < NSUB; ++sub) {
+          float xv[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            xv[e] = row[sub] < n && 4 * c4 + e < d ? x[row[sub] * (int64_t)d + 4 * c4 + e] : 0.0f;
+          add(sub, c4, xv);
+        }
+    }
+#pragma unroll
+    for (int sub = 0; sub < NSUB; ++sub) {
+      double v = acc[sub];
+      v += xshfl<8>(v);
+      v += xshfl<4>(v);
+      v += xshfl<2>(v);
+      v += xshfl<1>(v);
+      if (l16 == 0 && row[sub] < n) {
+        if (!first && !(v < old[sub])) v = old[sub];
+        dist[row[sub]] = v;
+      }
+      if (row[sub] >= n) v = 0.0;
       // the run's rows in order (rows past n add 0)
 #pragma unroll
       for (int gg = 0; gg < 4; ++gg) rs += __shfl(v, 16 * gg);
@@ -5176,13 +5267,23 @@ __global__ __launch_bounds__(256) void k_kpp_select(const float* __restrict__ x,
     int64_t pick = -1, blk = -1;
     const double u = uu[t];
     if (t > 0) {
+      // the running sums in order: the total, and what the search compares
       double total = 0.0;
-      for (int q = 0; q < 256; ++q) total += ssum[q];
+      for (int q = 0; q < 256; ++q) {
+        total += ssum[q];
+        ssum[q] = total;
+      }
       if (total > 0.0) {
         const double target = u * total;
-        double run = 0.0;
-        int q = 0;
-        while (q + 1 < 256 && !(run + ssum[q] > target)) run += ssum[q++];
+        // the first stretch whose running sum exceeds the target (the sums do
+        // not decrease), else the last
+        int q = 0, hi = 255;
+        while (q < hi) {
+          const int mid = (q + hi) >> 1;
+          if (ssum[mid] > target) hi = mid;
+          else q = mid + 1;
+        }
+        double run = q > 0 ? ssum[q - 1] : 0.0;
         int64_t b = per * q;
         const int64_t b1 = b + per < nblk ? b + per : nblk;
         while (b + 1 < b1 && !(run + bsum[b] > target)) run += bsum[b++];
@@ -5353,7 +5454,7 @@ bool make_layout(int64_t n, int d, int k, int m, Layout* L, size_t budget = 0) {
       if (more > maxc) maxc = (int)more;
     }
     if (maxc < 8) maxc = 8;
-    int64_t c = cdiv(n, 1024);
+    int64_t c = cdiv(n, 128);
     if (c > maxc) c = maxc;
     if (c >= 8) c = c / 8 * 8;
     L->nch = (int)(c < 1 ? 1 : c);
@@ -5554,23 +5655,68 @@ CoarseView coarse_view(const Layout& L, void* ws) {
 
 // Pairs per bucket, in the region of the screening thresholds, which are not
 // read any more when the pairs are counted (8 bytes a bucket of at least 4
-// components, in 8 bytes a component).
-int64_t* sparse_totals(const Layout& L, void* ws) { return at<int64_t>(ws, L.off_thr); }
+// components, in 8 bytes a component); null for a short table, which
+// k_sparse_offsets adds up by itself.
+int64_t* sparse_totals(const Layout& L, void* ws, const int* scnt, hipStream_t st) {
+  if ((int64_t)L.nb * L.nunit <= 8192) return nullptr;
+  int64_t* tot = at<int64_t>(ws, L.off_thr);
+  hipLaunchKernelGGL(k_sparse_total, dim3((unsigned)L.nb), dim3(256), 0, st, scnt, L.nunit, tot);
+  return tot;
+}
 
-// Operands, sample (large n) and the screening itself.  *smax: the most heavy
-// points of the sample with which the pass stays on.
+inline int pack_blocks(int64_t groups, int steps) { return (int)cdiv(groups * steps * 64, 256); }
+
+// The arguments of k_prep_pack; no parts but the fp32 screening's (whose biases
+// every screening reads) and the direct form's.
+template <int D64>
+PackArgs pack_args(const Layout& L, const float* w, const float* mu, const float* var, void* ws) {
+  const CoarseView cv = coarse_view(L, ws);
+  PackArgs a;
+  a.blocks[0] = (int)cdiv((int64_t)L.kpad * (D64 / 4) * 2, 256);
+  a.blocks[3] = (int)cdiv((int64_t)L.k * D64, 256);
+  a.blocks[1] = a.blocks[2] = a.blocks[4] = a.blocks[5] = 0;
+  a.w = w;
+  a.mu = mu;
+  a.var = var;
+  a.d = L.d;
+  a.k = L.k;
+  a.kpad = L.kpad;
+  a.cwell = at<double>(ws, L.off_cwell);
+  a.cdir = at<double>(ws, L.off_cdir);
+  a.cthr = at<float2>(ws, L.off_cthr);
+  a.counts = at<int>(ws, L.off_counts);
+  a.well_idx = at<int>(ws, L.off_well_idx);
+  a.ill_idx = at<int>(ws, L.off_ill_idx);
+  a.wp = at<float4>(ws, L.off_wp);
+  a.cw = at<float>(ws, L.off_cw);
+  a.thr = at<float2>(ws, L.off_thr);
+  a.wpb = at<bf16x8>(ws, L.off_wpb);
+  a.wq = at<float>(ws, L.off_wq);
+  a.dmu = at<float>(ws, L.off_dmu);
+  a.dh = at<double>(ws, L.off_dh);
+  a.wpc = cv.wpc;
+  a.cbias = cv.cbias;
+  a.cb2 = cv.cb2;
+  a.cidx = cv.cidx;
+  return a;
+}
+
+template <int D64, bool ISOB, bool ISOW, bool ISOC>
+void launch_pack(const PackArgs& a, hipStream_t st) {
+  int64_t nb = 0;
+  for (int i = 0; i < 6; ++i) nb += a.blocks[i];
+  hipLaunchKernelGGL((k_prep_pack<D64, ISOB, ISOW, ISOC>), dim3((unsigned)nb), dim3(256), 0, st, a);
+}
+
+// Sample (large n) and the screening itself.  *smax: the most heavy points of
+// the sample with which the pass stays on.
 template <int D64, bool ISO>
-void launch_coarse(const Layout& L, const float* x, const float* mu, const float* var, void* ws,
-                   float window, hipStream_t st, int* smax) {
+void launch_coarse(const Layout& L, const float* x, void* ws, float window, hipStream_t st,
+                   int* smax) {
   const CoarseView cv = coarse_view(L, ws);
   int* counts = at<int>(ws, L.off_counts);
-  constexpr int NS = coarse_steps<D64, ISO>(), WP = 4 * 16 * coarse_tiles(D64, ISO);
+  constexpr int WP = 4 * 16 * coarse_tiles(D64, ISO);
   constexpr int SP = 16 * (coarse_tiles(D64, ISO) > 2 ? 2 : coarse_tiles(D64, ISO));
-  const int64_t tot = (int64_t)(L.kpad / 16) * NS * 64;
-  hipLaunchKernelGGL((k_prep_pack_coarse<D64, ISO>), dim3((unsigned)cdiv(tot, 256)), dim3(256), 0,
-                     st, mu, var, L.d, L.kpad, at<double>(ws, L.off_cwell),
-                     at<double>(ws, L.off_cdir), counts, at<int>(ws, L.off_well_idx),
-                     at<int>(ws, L.off_ill_idx), cv.wpc, cv.cbias, cv.cb2, cv.cidx);
   *smax = INT_MAX;
   if (L.n < kSplitMax) {
     hipLaunchKernelGGL((k_coarse<D64, ISO, true>), dim3((unsigned)cdiv(L.n, SP)), dim3(256), 0, st,
@@ -5634,49 +5780,25 @@ int estep_impl(const Layout& L, const float* x, const float* w, const float* mu,
                      cthr);
   hipLaunchKernelGGL(k_prep_scan, dim3(1), dim3(256), 0, st, cls, k, well_idx, ill_idx, counts);
   {
-    const int64_t tot = (int64_t)kpad * (D64 / 4) * 2;
-    hipLaunchKernelGGL(k_prep_pack_well<D64>, dim3((unsigned)cdiv(tot, 256)), dim3(256), 0, st,
-                       mu, var, d, kpad, cwell, cthr, counts, well_idx, wp, cw, thr);
-    if constexpr (screen_x16(D64)) {
-      if (L.iso && L.refine) {
-        const int64_t tb = (int64_t)(kpad / kBK) * screen_steps<D64, true>() * 64;
-        hipLaunchKernelGGL((k_prep_pack_b16<D64, true>), dim3((unsigned)cdiv(tb, 256)), dim3(256),
-                           0, st, mu, var, d, kpad, counts, well_idx, wpb);
-      } else {
-        const int64_t tb = (int64_t)(kpad / kBK) * screen_steps<D64, false>() * 64;
-        hipLaunchKernelGGL((k_prep_pack_b16<D64, false>), dim3((unsigned)cdiv(tb, 256)),
-                           dim3(256), 0, st, mu, var, d, kpad, counts, well_idx, wpb);
-      }
-    }
-    if constexpr (screen_b16(D64)) {
-      if (L.iso) {
-        const int64_t tb = (int64_t)(kpad / kBK) * screen_steps<D64, true>() * 64;
-        hipLaunchKernelGGL((k_prep_pack_b16<D64, true>), dim3((unsigned)cdiv(tb, 256)), dim3(256),
-                           0, st, mu, var, d, kpad, counts, well_idx, wpb);
-      } else {
-        const int64_t tb = (int64_t)(kpad / kBK) * screen_steps<D64, false>() * 64;
-        hipLaunchKernelGGL((k_prep_pack_b16<D64, false>), dim3((unsigned)cdiv(tb, 256)),
-                           dim3(256), 0, st, mu, var, d, kpad, counts, well_idx, wpb);
-      }
-    }
-    if (D64 < 256 && L.iso)
-      hipLaunchKernelGGL((k_prep_pack_w16<D64, true>),
-                         dim3((unsigned)cdiv((int64_t)(kpad / 16) * wq_steps_iso(D64) * 64, 256)),
-                         dim3(256), 0, st, w, mu, var, d, kpad, counts, well_idx, wq);
-    else
-      hipLaunchKernelGGL((k_prep_pack_w16<D64, false>),
-                         dim3((unsigned)cdiv((int64_t)(kpad / 16) * wq_steps(D64) * 64, 256)),
-                         dim3(256), 0, st, w, mu, var, d, kpad, counts, well_idx, wq);
-    const int64_t toti = (int64_t)k * D64;
-    hipLaunchKernelGGL(k_prep_pack_direct<D64>, dim3((unsigned)cdiv(toti, 256)), dim3(256), 0,
-                       st, mu, var, d, k, dmu, dh);
+    PackArgs a = pack_args<D64>(L, w, mu, var, ws);
+    const bool isob = L.iso && L.refine && screen_split(D64);
+    a.blocks[1] = screen_split(D64) ? pack_blocks(kpad / kBK, isob ? screen_steps<D64, true>()
+                                                                   : screen_steps<D64, false>())
+                                    : 0;
+    const bool isow = D64 < 256 && L.iso;
+    a.blocks[2] = pack_blocks(kpad / 16, isow ? wq_steps_iso(D64) : wq_steps(D64));
+    a.blocks[4] = pack_blocks(kpad / 16, L.iso ? coarse_steps<D64, true>()
+                                               : coarse_steps<D64, false>());
+    if (L.iso && L.refine) launch_pack<D64, true, (D64 < 256), true>(a, st);
+    else if (L.iso) launch_pack<D64, false, (D64 < 256), true>(a, st);
+    else launch_pack<D64, false, false, false>(a, st);
   }
   tm = phase_mark(1, st) && tm;
   const int64_t* hlist = nullptr;
   int smax = INT_MAX;
   {
-    if (L.iso) launch_coarse<D64, true>(L, x, mu, var, ws, kCoarseWindow, st, &smax);
-    else launch_coarse<D64, false>(L, x, mu, var, ws, kCoarseWindow, st, &smax);
+    if (L.iso) launch_coarse<D64, true>(L, x, ws, kCoarseWindow, st, &smax);
+    else launch_coarse<D64, false>(L, x, ws, kCoarseWindow, st, &smax);
     hlist = coarse_view(L, ws).hlist;
     const CoarseView cv = coarse_view(L, ws);
     hipLaunchKernelGGL(k_refine<D64>, dim3((unsigned)cdiv(n * refine_lanes(D64), 256)), dim3(256),
@@ -5711,9 +5833,7 @@ int estep_impl(const Layout& L, const float* x, const float* w, const float* mu,
     const size_t lds = (size_t)L.nb * sizeof(int);
     hipLaunchKernelGGL(k_sparse_count, dim3((unsigned)L.nunit), dim3(64), lds, st, cslot, n,
                        L.upts, L.nb, L.lsbk, L.nunit, scnt, logz2, llpart, bmask, dcnt);
-    int64_t* stot = sparse_totals(L, ws);
-    hipLaunchKernelGGL(k_sparse_total, dim3((unsigned)L.nb), dim3(256), 0, st, scnt, L.nunit,
-                       stot);
+    int64_t* stot = sparse_totals(L, ws, scnt, st);
     hipLaunchKernelGGL(k_sparse_offsets, dim3((unsigned)(L.nb + (bmask != nullptr ? 1 : 0))),
                        dim3(256), 0, st, scnt, L.nb, L.nunit, stot, soff, dcnt, doff,
                        reinterpret_cast<int64_t*>(counts + kCntDense));
@@ -5812,29 +5932,27 @@ int assign_impl(const Layout& L, const float* x, const float* w, const float* mu
   hipLaunchKernelGGL(k_prep_class, dim3(k), dim3(64), 0, st, w, mu, var, d, cls, cwell, cdir,
                      cthr);
   hipLaunchKernelGGL(k_prep_scan, dim3(1), dim3(256), 0, st, cls, k, well_idx, ill_idx, counts);
+  const bool coarse = m == 1 || tau >= 0x1p-40f;
   {
-    const int64_t tot = (int64_t)kpad * (D64 / 4) * 2;
-    hipLaunchKernelGGL(k_prep_pack_well<D64>, dim3((unsigned)cdiv(tot, 256)), dim3(256), 0, st,
-                       mu, var, d, kpad, cwell, cthr, counts, well_idx, wp, cw, thr);
-    const int64_t toti = (int64_t)k * D64;
-    hipLaunchKernelGGL(k_prep_pack_direct<D64>, dim3((unsigned)cdiv(toti, 256)), dim3(256), 0,
-                       st, mu, var, d, k, dmu, dh);
-    if constexpr (screen_split(D64)) {
-      const int64_t tb = (int64_t)(kpad / kBK) * screen_steps<D64, false>() * 64;
-      hipLaunchKernelGGL((k_prep_pack_b16<D64, false>), dim3((unsigned)cdiv(tb, 256)), dim3(256),
-                         0, st, mu, var, d, kpad, counts, well_idx, wpb);
-      hipLaunchKernelGGL(k_assign_slots, dim3((unsigned)cdiv(kpad, 256)), dim3(256), 0, st,
-                         cwell, cdir, counts, well_idx, kpad, ca);
+    PackArgs a = pack_args<D64>(L, w, mu, var, ws);
+    if (screen_split(D64)) {
+      a.blocks[1] = pack_blocks(kpad / kBK, screen_steps<D64, false>());
+      a.blocks[5] = (int)cdiv(kpad, 256);
     }
+    if (coarse)
+      a.blocks[4] = pack_blocks(kpad / 16, L.iso ? coarse_steps<D64, true>()
+                                                 : coarse_steps<D64, false>());
+    if (L.iso) launch_pack<D64, false, false, true>(a, st);
+    else launch_pack<D64, false, false, false>(a, st);
   }
   // the one-product screening and the exact ranking of its candidates, where
   // the window holds every component that can be assigned; then, for the
   // heavy points (or all), the two-pass screening
   const int64_t* hlist = nullptr;
   int smax = INT_MAX;
-  if (m == 1 || tau >= 0x1p-40f) {
-    if (L.iso) launch_coarse<D64, true>(L, x, mu, var, ws, window, st, &smax);
-    else launch_coarse<D64, false>(L, x, mu, var, ws, window, st, &smax);
+  if (coarse) {
+    if (L.iso) launch_coarse<D64, true>(L, x, ws, window, st, &smax);
+    else launch_coarse<D64, false>(L, x, ws, window, st, &smax);
     const CoarseView cv = coarse_view(L, ws);
     hlist = cv.hlist;
     hipLaunchKernelGGL(k_assign_refine<D64>, dim3((unsigned)cdiv(n * refine_lanes(D64), 256)),
@@ -5896,9 +6014,7 @@ int kmeans_impl(const Layout& L, const float* x, int n_iters, float var_floor, f
     const size_t lds = (size_t)L.nb * sizeof(int);
     hipLaunchKernelGGL(k_sparse_count, dim3((unsigned)L.nunit), dim3(64), lds, st, cslot, n,
                        L.upts, L.nb, L.lsbk, L.nunit, scnt, nullptr, nullptr, nullptr, nullptr);
-    int64_t* stot = sparse_totals(L, ws);
-    hipLaunchKernelGGL(k_sparse_total, dim3((unsigned)L.nb), dim3(256), 0, st, scnt, L.nunit,
-                       stot);
+    int64_t* stot = sparse_totals(L, ws, scnt, st);
     hipLaunchKernelGGL(k_sparse_offsets, dim3((unsigned)L.nb), dim3(256), 0, st, scnt, L.nb,
                        L.nunit, stot, soff, nullptr, nullptr, nullptr);
     hipLaunchKernelGGL(k_sparse_scatter, dim3((unsigned)L.nunit), dim3(64), scatter_lds(L.nb), st,
@@ -6123,10 +6239,9 @@ static int fit_entry(const float* x, int64_t n, int32_t d, int32_t k, int32_t n_
   double* fq = at<double>(ws, L.off_fit_q);
   const int64_t kd = (int64_t)k * d;
   for (int t = 0; t < n_iters; ++t) {
-    hipLaunchKernelGGL(k_zero, dim3((unsigned)cdiv(k, 256)), dim3(256), 0, stream, fnk,
-                       (int64_t)k);
-    hipLaunchKernelGGL(k_zero, dim3((unsigned)cdiv(kd, 256)), dim3(256), 0, stream, fs, kd);
-    hipLaunchKernelGGL(k_zero, dim3((unsigned)cdiv(kd, 256)), dim3(256), 0, stream, fq, kd);
+    // N_k, S and Q lie one after the other
+    const int64_t nz = (int64_t)((L.off_fit_q - L.off_fit_nk) / sizeof(double)) + kd;
+    hipLaunchKernelGGL(k_zero, dim3((unsigned)cdiv(nz, 256)), dim3(256), 0, stream, fnk, nz);
     rc = estep_dispatch(L, x, weights, means, vars, fnk, fs, fq, loglik_hist + t, 0, ws, stream);
     if (rc != GMM_OK) return rc;
     hipLaunchKernelGGL(k_mstep, dim3((unsigned)cdiv(kd, 256)), dim3(256), 0, stream, fnk, fs, fq,
@@ -6207,12 +6322,10 @@ int gmm_fit_iso(const float* x, int64_t n, int32_t d, int32_t k, int32_t n_iters
   float* vfull = at<float>(ws, L.off_iso_var);
   const int64_t kd = (int64_t)k * d;
   for (int t = 0; t < n_iters; ++t) {
-    hipLaunchKernelGGL(k_zero, dim3((unsigned)cdiv(k, 256)), dim3(256), 0, stream, fnk,
-                       (int64_t)k);
-    hipLaunchKernelGGL(k_zero, dim3((unsigned)cdiv(k, 256)), dim3(256), 0, stream, fq,
-                       (int64_t)k);
-    hipLaunchKernelGGL(k_zero, dim3((unsigned)cdiv(kd, 256)), dim3(256), 0, stream, fs, kd);
-    hipLaunchKernelGGL(k_zero, dim3((unsigned)cdiv(kd, 256)), dim3(256), 0, stream, fqd, kd);
+    // N_k, S, the dimensions' Q, (the expanded variances, written next) and Q lie
+    // one after the other
+    const int64_t nz = (int64_t)((L.off_iso_q - L.off_fit_nk) / sizeof(double)) + k;
+    hipLaunchKernelGGL(k_zero, dim3((unsigned)cdiv(nz, 256)), dim3(256), 0, stream, fnk, nz);
     hipLaunchKernelGGL(k_iso_expand, dim3((unsigned)cdiv(kd, 256)), dim3(256), 0, stream, vars,
                        d, k, vfull);
     rc = estep_dispatch(L, x, weights, means, vfull, fnk, fs, fqd, loglik_hist + t, 0, ws,
