@@ -3920,7 +3920,9 @@ __global__ __launch_bounds__(64 * kSparseWaves) void k_stats_sparse(
 // chunks.  Per PT-point iteration wave w forms r for components CW w ..
 // CW w + CW - 1 of the block with the direct form (lane = point), then
 // accumulates the statistics of those components in fp64 (lane = column).
-__host__ __device__ constexpr int ill_pt(int D64) { return D64 <= 256 ? 64 : (D64 <= 512 ? 32 : 16); }
+__host__ __device__ constexpr int ill_pt(int D64) {
+  return D64 <= 128 ? 128 : (D64 <= 256 ? 64 : (D64 <= 512 ? 32 : 16));
+}
 __host__ __device__ constexpr int ill_cw(int D64) { return D64 <= 256 ? 8 : (D64 <= 512 ? 4 : 2); }
 
 __host__ __device__ inline int ill_chunks(int grid, int n_ikb, int64_t n, int pt) {
@@ -4120,6 +4122,281 @@ __global__ __launch_bounds__(256) void k_stats_ill(
     for (int j = 0; j < NJ; ++j) {
       base[1 + lane + 64 * j] = S[c][j];
       base[1 + D64 + lane + 64 * j] = Q[c][j];
+    }
+  }
+}
+
+// The same up to 128 dimensions, on eight waves.  A tile is 128 points by 32
+// components.  Evaluation: a wave has 4 components and a lane 2 points, so a
+// parameter read from LDS (means and weights stay there for the whole launch)
+// serves two pairs and the vector ALU's 3 fp64 instructions a pair and
+// dimension, not LDS, are the bound.  Statistics: r^T [x | x^2] on fp64 MFMA
+// (products of fp32 values are exact in fp64), 4 points a step, a wave one
+// 16-dimension row of tiles (D64 = 128; half of one at 64); steps whose pairs
+// are all zero are skipped.  One by one on the vector ALU an added pair cost
+// about 90 cycles, here 8.  Measured, a launch: n = 1e5, k = 1024, d = 128 (a
+// fit's first six iterations, most components light) 157 -> 129 us; n = 1.18e6,
+// d = 100 (first iteration) 393 -> 199 us.
+typedef double d4v __attribute__((ext_vector_type(4)));
+template <int D64>
+__global__ __launch_bounds__(512, 2) void k_stats_direct(
+    const float* __restrict__ x, int64_t n, int d, int vec4, const int* __restrict__ ill_idx,
+    const float* __restrict__ dmu, const double* __restrict__ dh,
+    const double* __restrict__ cdir, const int* __restrict__ counts,
+    const double* __restrict__ logz2, const unsigned char* __restrict__ iflag,
+    const unsigned char* __restrict__ lflag, const unsigned long long* __restrict__ lmask,
+    const unsigned short* __restrict__ cslot, const int* __restrict__ small_pos,
+    const int* __restrict__ small_slot, int gsh, double* __restrict__ part) {
+  constexpr int P = D64 + 4, STRIDE = 1 + 2 * D64, T = 512, NWV = 8;
+  constexpr int PT = ill_pt(D64), ICB = 4 * ill_cw(D64), CW = ICB / NWV, PL = PT / 64;
+  constexpr int NTL = (D64 / 16) * (ICB / 16) / NWV;    // (dims, components) tiles a wave
+  static_assert(PT == 128 && ICB == 32 && CW == 4 && NTL >= 1, "tile split");
+  constexpr int WPT = 8, WIN = WPT * T;         // points scanned per queue window
+  __shared__ __align__(16) float xs[PT * P];
+  __shared__ __align__(16) float tmu[ICB * D64];
+  __shared__ __align__(16) double th[ICB * D64];        // log2(e) / (2 var)
+  __shared__ float rs[ICB][PT + 1];
+  __shared__ double lzs[PT], cds[ICB];
+  __shared__ int lsx[PT][kT];                   // light: list index of each stored pair, or -1
+  __shared__ unsigned qpt[WIN + PT];            // queued points (offsets from the chunk start)
+  __shared__ unsigned long long nzm[ICB / 16][PL];      // points with r > 0, by 16 components
+  __shared__ int xbad[PT];                      // a value of the point is not finite
+  __shared__ int qsum[NWV];
+  const int n_ill = counts[1];
+  const int n_ikb = (n_ill + ICB - 1) / ICB;
+  if (n_ikb == 0) return;
+  const int nchk = ill_chunks(gridDim.x, n_ikb, n, PT);
+  const int kb = blockIdx.x / nchk, chunk = blockIdx.x % nchk;
+  if (kb >= n_ikb) return;
+  const int64_t chunk_pts = (n + nchk - 1) / nchk;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, i16 = lane & 15, k4 = lane >> 4;
+  const int64_t p0 = (int64_t)chunk * chunk_pts;
+  const int64_t p1 = p0 + chunk_pts < n ? p0 + chunk_pts : n;
+  for (int i = tid; i < ICB * D64; i += T) {
+    const int ki = kb * ICB + i / D64, j = i % D64;
+    const size_t o = ki < n_ill ? (size_t)ill_idx[ki] * D64 + j : 0;
+    tmu[i] = ki < n_ill ? dmu[o] : 0.0f;
+    th[i] = ki < n_ill ? dh[o] : 0.0;
+  }
+  if (tid < ICB) cds[tid] = kb * ICB + tid < n_ill ? cdir[ill_idx[kb * ICB + tid]] : -INFINITY;
+  if (tid < PT) xbad[tid] = 0;
+  if (tid < PL * (ICB / 16)) nzm[tid / PL][tid % PL] = 0ull;
+  d4v S[NTL], Q[NTL];
+#pragma unroll
+  for (int i = 0; i < NTL; ++i) S[i] = Q[i] = d4v{0.0, 0.0, 0.0, 0.0};
+  double NK[CW];
+#pragma unroll
+  for (int c = 0; c < CW; ++c) NK[c] = 0.0;
+  // which points are taken: as in k_stats_ill
+  unsigned long long want = ~0ull;
+  if (small_pos != nullptr && lmask != nullptr) {
+    const int last = (kb + 1) * ICB < n_ill ? (kb + 1) * ICB - 1 : n_ill - 1;
+    const int b0 = small_slot[kb * ICB] >> gsh, b1 = small_slot[last] >> gsh;
+    want = (~0ull << b0) & (~0ull >> (63 - b1));
+  }
+  int qn = 0;
+  for (int64_t wb0 = p0; wb0 < p1; wb0 += WIN) {
+    const int64_t we = wb0 + WIN < p1 ? wb0 + WIN : p1;
+    {
+      const int64_t a = wb0 + WPT * tid;
+      unsigned sel = 0u;
+#pragma unroll
+      for (int e = 0; e < WPT; ++e) {
+        const int64_t pt = a + e;
+        bool take = pt < we;
+        if (take && iflag != nullptr) take = iflag[pt] != 0;
+        if (take && small_pos != nullptr) take = lflag[pt] != 0;
+        if (take && small_pos != nullptr && lmask != nullptr) take = (lmask[pt] & want) != 0ull;
+        if (take) sel |= 1u << e;
+      }
+      const int cnt = __popc(sel);
+      int inc = cnt;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int t2 = __shfl_up(inc, o);
+        if (lane >= o) inc += t2;
+      }
+      if (lane == 63) qsum[wave] = inc;
+      __syncthreads();
+      int pos = qn + inc - cnt, all = 0;
+#pragma unroll
+      for (int w2 = 0; w2 < NWV; ++w2) {
+        if (w2 < wave) pos += qsum[w2];
+        all += qsum[w2];
+      }
+      while (sel) {
+        const int e = __ffs(sel) - 1;
+        sel &= sel - 1;
+        qpt[pos++] = (unsigned)(a + e - p0);
+      }
+      qn += all;
+      __syncthreads();                          // queue complete, qsum free
+    }
+    const int nt = we >= p1 ? (qn + PT - 1) / PT : qn / PT;
+    for (int ti = 0; ti < nt; ++ti) {
+      __syncthreads();                          // the previous tile's reads are done
+      {
+        // gathered tile: queue entries PT ti .. PT ti + PT - 1 (rows past qn are zero)
+        constexpr int Q4 = D64 / 4;
+        for (int idx = tid; idx < PT * Q4; idx += T) {
+          const int r = idx / Q4, c = (idx % Q4) * 4;
+          const int e = PT * ti + r;
+          float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+          if (e < qn && c < d) {
+            const float* xr = x + (p0 + qpt[e]) * d;
+            if (vec4) {
+              v = *reinterpret_cast<const float4*>(xr + c);
+            } else {
+              v.x = xr[c];
+              v.y = c + 1 < d ? xr[c + 1] : 0.f;
+              v.z = c + 2 < d ? xr[c + 2] : 0.f;
+              v.w = c + 3 < d ? xr[c + 3] : 0.f;
+            }
+          }
+          // 0 times infinity would reach the sums of other points' pairs
+          const float t = (v.x - v.x) + (v.y - v.y) + (v.z - v.z) + (v.w - v.w);
+          if (!(t == 0.0f)) {
+            xbad[r] = 1;
+            v = make_float4(0.f, 0.f, 0.f, 0.f);
+          }
+          *reinterpret_cast<float4*>(xs + r * P + c) = v;
+        }
+        if (tid < PT) {
+          const int e = PT * ti + tid;
+          lzs[tid] = e < qn ? logz2[p0 + qpt[e]] : INFINITY;
+          if (small_pos != nullptr) {
+            int v4[kT] = {kNoSlot, kNoSlot, kNoSlot, kNoSlot};
+            if (e < qn) {
+              const ushort4 sl = *reinterpret_cast<const ushort4*>(cslot + (p0 + qpt[e]) * kT);
+              v4[0] = sl.x; v4[1] = sl.y; v4[2] = sl.z; v4[3] = sl.w;
+            }
+#pragma unroll
+            for (int j = 0; j < kT; ++j) lsx[tid][j] = v4[j] != kNoSlot ? small_pos[v4[j]] : -1;
+          }
+        }
+      }
+      __syncthreads();
+      // r of the tile's points (lane, lane + 64) against this wave's components,
+      // the sums in dimension order; r < 2^-150 is 0 in fp32: once every pair of
+      // the wave is past that the sums end
+      double acc[CW][PL], bnd[CW][PL], lz[PL];
+#pragma unroll
+      for (int q = 0; q < PL; ++q) {
+        // a value that is not finite was replaced by 0: such a point holds r = 0 (or
+        // NaN, which adds nothing either)
+        lz[q] = xbad[lane + 64 * q] != 0 ? INFINITY : lzs[lane + 64 * q];
+#pragma unroll
+        for (int c = 0; c < CW; ++c) {
+          acc[c][q] = 0.0;
+          bnd[c][q] = cds[wave * CW + c] - (lz[q] - 150.0);
+        }
+      }
+      for (int j0 = 0; j0 < D64; j0 += 16) {
+#pragma unroll 1
+        for (int j = j0; j < j0 + 16; j += 4) {
+          double xd[PL][4];
+#pragma unroll
+          for (int q = 0; q < PL; ++q) {
+            const float4 v = *reinterpret_cast<const float4*>(xs + (lane + 64 * q) * P + j);
+            xd[q][0] = (double)v.x; xd[q][1] = (double)v.y;
+            xd[q][2] = (double)v.z; xd[q][3] = (double)v.w;
+          }
+#pragma unroll
+          for (int c = 0; c < CW; ++c) {
+            const float4 m4 = *reinterpret_cast<const float4*>(tmu + (wave * CW + c) * D64 + j);
+            const double2* h2 = reinterpret_cast<const double2*>(th + (wave * CW + c) * D64 + j);
+            const double2 ha = h2[0], hb = h2[1];
+            const double m[4] = {(double)m4.x, (double)m4.y, (double)m4.z, (double)m4.w};
+            const double h[4] = {ha.x, ha.y, hb.x, hb.y};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+              for (int q = 0; q < PL; ++q) {
+                const double t = xd[q][e] - m[e];
+                acc[c][q] = fma(t * t, h[e], acc[c][q]);
+              }
+          }
+        }
+        bool more = false;
+#pragma unroll
+        for (int c = 0; c < CW; ++c)
+#pragma unroll
+          for (int q = 0; q < PL; ++q) more |= !(acc[c][q] > bnd[c][q]);
+        if (__ballot(more) == 0ull) break;
+      }
+#pragma unroll
+      for (int q = 0; q < PL; ++q) {
+        bool nz = false;
+#pragma unroll
+        for (int c = 0; c < CW; ++c) {
+          const int kl = wave * CW + c, ki = kb * ICB + kl;
+          bool skip = ki >= n_ill;
+          if (small_pos != nullptr) {
+#pragma unroll
+            for (int j = 0; j < kT; ++j) skip |= lsx[lane + 64 * q][j] == ki;
+          }
+          const double l = acc[c][q] > bnd[c][q] ? -INFINITY : cds[kl] - acc[c][q];
+          float r = exp2_fast((float)(l - lz[q]));
+          if (skip || !(r > 0.0f)) r = 0.0f;
+          rs[kl][lane + 64 * q] = r;
+          nz |= r > 0.0f;
+          NK[c] += (double)r;
+        }
+        const unsigned long long m = __ballot(nz);
+        if (lane == 0 && m != 0ull) atomicOr(&nzm[wave * CW / 16][q], m);
+      }
+      __syncthreads();
+      unsigned long long msk[ICB / 16][PL];
+#pragma unroll
+      for (int cb = 0; cb < ICB / 16; ++cb)
+#pragma unroll
+        for (int q = 0; q < PL; ++q) msk[cb][q] = nzm[cb][q];
+      // statistics: step s contracts points 4 s + k4
+#pragma unroll
+      for (int q = 0; q < PL; ++q) {
+        for (int s = 0; s < 16; ++s) {
+          const int pt = 64 * q + 4 * s + k4;
+#pragma unroll
+          for (int i = 0; i < NTL; ++i) {
+            const int tl = wave * NTL + i, rb = tl / (ICB / 16), cb = tl % (ICB / 16);
+            const unsigned long long mc =
+                NTL % (ICB / 16) == 0 ? msk[i % (ICB / 16)][q] : (cb ? msk[ICB / 16 - 1][q] : msk[0][q]);
+            if ((__builtin_amdgcn_readfirstlane((int)(mc >> (4 * s))) & 15) == 0) continue;
+            const double xv = (double)xs[pt * P + 16 * rb + i16];
+            const double rv = (double)rs[16 * cb + i16][pt];
+            S[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(xv, rv, S[i], 0, 0, 0);
+            Q[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(xv * xv, rv, Q[i], 0, 0, 0);
+          }
+        }
+      }
+      __syncthreads();                          // masks read
+      if (tid < PT) xbad[tid] = 0;
+      if (tid < PL * (ICB / 16)) nzm[tid / PL][tid % PL] = 0ull;
+    }
+    // the entries not taken move to the front of the queue
+    const int used = PT * nt < qn ? PT * nt : qn;
+    const int left = qn - used;
+    __syncthreads();
+    const unsigned keep = tid < left ? qpt[used + tid] : 0u;
+    __syncthreads();
+    if (tid < left) qpt[tid] = keep;
+    qn = left;
+  }
+  double* const out = part + (size_t)blockIdx.x * ICB * STRIDE;
+#pragma unroll
+  for (int c = 0; c < CW; ++c) {
+    double v = NK[c];
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    if (lane == 0) out[(size_t)(wave * CW + c) * STRIDE] = v;
+  }
+  // register v of lane l: dimension 4 v + l / 16, component l % 16
+#pragma unroll
+  for (int i = 0; i < NTL; ++i) {
+    const int tl = wave * NTL + i, rb = tl / (ICB / 16), cb = tl % (ICB / 16);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      double* const o = out + (size_t)(16 * cb + i16) * STRIDE + 1 + 16 * rb + 4 * v + k4;
+      o[0] = S[i][v];
+      o[D64] = Q[i][v];
     }
   }
 }
@@ -5497,8 +5774,8 @@ bool make_layout(int64_t n, int d, int k, int m, Layout* L, size_t budget = 0) {
     if (pp > by_bytes) pp = by_bytes;
     L->nparts = (int)(pp < 1 ? 1 : pp);
   }
-  L->ipt = L->D64 <= 256 ? 64 : (L->D64 <= 512 ? 32 : 16);
-  L->ibk = 4 * (L->D64 <= 256 ? 8 : (L->D64 <= 512 ? 4 : 2));
+  L->ipt = ill_pt(L->D64);
+  L->ibk = 4 * ill_cw(L->D64);
   {
     // at least one workgroup per block of routed components; about 512 in all,
     // but no more chunks than tiles of points
@@ -5708,6 +5985,15 @@ void launch_pack(const PackArgs& a, hipStream_t st) {
   hipLaunchKernelGGL((k_prep_pack<D64, ISOB, ISOW, ISOC>), dim3((unsigned)nb), dim3(256), 0, st, a);
 }
 
+// The pass over the routed and the light components: k_stats_direct where its
+// operands fit LDS.
+constexpr int direct_threads(int D64) { return D64 <= 128 ? 512 : 256; }
+template <int D64>
+constexpr auto direct_kernel() {
+  if constexpr (D64 <= 128) return k_stats_direct<D64>;
+  else return k_stats_ill<D64>;
+}
+
 // Sample (large n) and the screening itself.  *smax: the most heavy points of
 // the sample with which the pass stays on.
 template <int D64, bool ISO>
@@ -5884,12 +6170,12 @@ int estep_impl(const Layout& L, const float* x, const float* w, const float* mu,
                          counts, logz2, cslot, dlist, L.nch, gsh, sflag, lflag, bmask, part_w);
   }
   tm = phase_mark(4, st) && tm;
-  hipLaunchKernelGGL(k_stats_ill<D64>, dim3((unsigned)L.grid_i), dim3(256), 0, st, x, n, d, vec4,
-                     ill_idx, dmu, dh, cdir, counts, logz2, iflag, nullptr, nullptr, nullptr,
+  hipLaunchKernelGGL(direct_kernel<D64>(), dim3((unsigned)L.grid_i), dim3(direct_threads(D64)), 0,
+                     st, x, n, d, vec4, ill_idx, dmu, dh, cdir, counts, logz2, iflag, nullptr, nullptr, nullptr,
                      nullptr, nullptr, gsh, part_i);
   if (L.refine)
-    hipLaunchKernelGGL(k_stats_ill<D64>, dim3((unsigned)L.grid_i), dim3(256), 0, st, x, n, d,
-                       vec4, sidx, dmu, dh, cdir, scnt2, logz2, nullptr, lflag, bmask, cslot,
+    hipLaunchKernelGGL(direct_kernel<D64>(), dim3((unsigned)L.grid_i), dim3(direct_threads(D64)),
+                       0, st, x, n, d, vec4, sidx, dmu, dh, cdir, scnt2, logz2, nullptr, lflag, bmask, cslot,
                        spos, cls, gsh, part_x);
   {
     const int64_t tot = 2 * (int64_t)k * (1 + 2 * (int64_t)d);
