@@ -7,15 +7,17 @@ M-step) over the whole synthetic data set, already resident in HBM.  The
 default workload is the paper-shape large one: N = 1e8 points, D = 128,
 K = 1024 components (51.2 GB of fp32 data), random-point initialisation.
 
-Prints one JSON line on stdout.  `roofline` covers the dominant kernel,
-k_logz (log-densities of every point against every component, their
-log-sum-exp, the exact refinement and log Z), timed over the timed steps with
-the library's phase timer (HIP events recorded on the stream the kernels run
-on).  Its algorithmic work is the log-density contraction over all N x K
-pairs, 4*N*K*D flop per launch ([x | x^2] against [W | P], depth 2D), priced
-against the peak of the MFMA type it runs on (bf16 for D <= 128 and D > 256,
-where the fp32 operands are split in hi/lo bf16 parts and three products are
-summed, fp32 in between).  The E-step as a whole is also reported against the 8*N*K*D
+Prints one JSON line on stdout.  `roofline` covers the dominant phase, the
+screening with its refinement (log-densities of every point against every
+component, the exact log-densities of those that matter and log Z: k_coarse,
+k_refine, and k_logz for the points with many candidates), timed over the timed
+steps with the library's phase timer (HIP events recorded on the stream the
+kernels run on).  Its algorithmic work is the log-density contraction over all
+N x K pairs, 4*N*K*D flop per E-step ([x | x^2] against [W | P], depth 2D),
+priced against the peak of the MFMA type it runs on (bf16, one product with an
+error bound; of the screened calls: bf16 for D <= 128 and D > 256, where the
+fp32 operands are split in hi/lo bf16 parts and three products are summed, fp32
+in between).  The E-step as a whole is also reported against the 8*N*K*D
 flop of the dense algorithm.  `cpu_baseline` times the fp64 CPU checker on a
 bounded slice of the same data and scales it linearly in N (the E-step is
 exactly linear in N).
@@ -165,14 +167,16 @@ def source_digest():
         return hashlib.sha256(f.read()).hexdigest()
 
 
-ESTEP_KERNELS = ("k_prep_", "k_logz", "k_stats_", "k_sparse_", "k_reduce_")
+SCREEN_KERNELS = ("k_coarse", "k_refine", "k_logz")
+ESTEP_KERNELS = SCREEN_KERNELS + ("k_prep_", "k_stats_", "k_sparse_", "k_dense_", "k_small_",
+                                  "k_reduce_")
 
 
 def counter_per_call(csv_path, kernels=ESTEP_KERNELS, skip=0):
     """Sum of a rocprofv3 --pmc counter (KiB) over the dispatches whose kernel name contains one
     of `kernels`, per gmm_estep_accumulate call (a call starts with its k_prep_class dispatch),
-    leaving out the first `skip` calls (the warm-up iterations): per E-step, or per k_logz
-    launch when kernels = ("k_logz",)."""
+    leaving out the first `skip` calls (the warm-up iterations): per E-step, or of its
+    screening phase when kernels = SCREEN_KERNELS."""
     import csv
     with open(csv_path) as f:
         rows = sorted(csv.DictReader(f), key=lambda r: int(r["Dispatch_Id"]))
@@ -196,8 +200,8 @@ def write_traffic(workload, fetch_csv, write_csv, copy_fetch_csv, copy_write_csv
     f_scale, w_scale = COPY_BYTES / f_copy, COPY_BYTES / w_copy
     fetch = counter_per_call(fetch_csv, skip=skip) * 1024.0 * f_scale
     write = counter_per_call(write_csv, skip=skip) * 1024.0 * w_scale
-    lf = counter_per_call(fetch_csv, ("k_logz",), skip) * 1024.0 * f_scale
-    lw = counter_per_call(write_csv, ("k_logz",), skip) * 1024.0 * w_scale
+    lf = counter_per_call(fetch_csv, SCREEN_KERNELS, skip) * 1024.0 * f_scale
+    lw = counter_per_call(write_csv, SCREEN_KERNELS, skip) * 1024.0 * w_scale
     out = {"workload": workload, "bytes_per_call": fetch + write, "fetch_bytes": fetch,
            "write_bytes": write, "logz_bytes_per_launch": lf + lw, "logz_fetch_bytes": lf,
            "logz_write_bytes": lw, "fetch_scale": f_scale, "write_scale": w_scale,
@@ -209,8 +213,8 @@ def write_traffic(workload, fetch_csv, write_csv, copy_fetch_csv, copy_write_csv
 
 
 def measured_traffic(workload, key="logz_bytes_per_launch"):
-    """HBM bytes per k_logz launch (or, with key="bytes_per_call", per E-step) from the
-    committed counter runs (profiles/estep_traffic_<workload>.json), or None when the kernels
+    """HBM bytes of an E-step's screening phase (or, with key="bytes_per_call", of the E-step)
+    from the committed counter runs (profiles/estep_traffic_<workload>.json), or None when the kernels
     have changed since."""
     path = os.path.join(ROOT, "profiles", f"estep_traffic_{workload}.json")
     if not os.path.exists(path):
@@ -258,11 +262,9 @@ def bench_assign(args, w, x, th0, dev):
     kept2 = int((idx[:, 1] >= 0).sum().item())
     flop = 4.0 * w.n * k * d                  # log-densities of every (point, component) pair
     rate = flop / (ms * 1e-3) / 1e12
-    # both passes screen on split-bf16 MFMA (three bf16 products per fp32 product) up to 128
-    # and above 256 padded dimensions, on fp32 MFMA in between
-    split = padded_d(d) <= 128 or padded_d(d) > 256
-    peak = BF16_MFMA_PEAK_TFLOPS if split else FP32_MFMA_PEAK_TFLOPS
-    how = "split-bf16 MFMA, bf16 peak" if split else "fp32 MFMA peak"
+    # every pair is screened on bf16 MFMA (one product); the points with many candidates go
+    # through two more passes, on split-bf16 MFMA (three products) or fp32 MFMA
+    peak = BF16_MFMA_PEAK_TFLOPS
     print(json.dumps({
         "metric": "gmm_assign_topk time (m=2, tau=1/K)", "value": round(ms, 3), "unit": "ms",
         "higher_is_better": False, "n_gpus": 1, "steps": steps, "data": "synthetic",
@@ -270,8 +272,9 @@ def bench_assign(args, w, x, th0, dev):
                                f"N={w.n}, D={d}, K={k}", "n": w.n, "d": d, "k": k, "m": m,
                    "tau": tau},
         "second_rank_kept": kept2,
-        "roofline": {"bound": "mfma", "kernel": "k_assign_theta + k_assign_collect (4*N*K*D flop "
-                     f"of log-densities, {how}; both passes screen every pair)",
+        "roofline": {"bound": "mfma", "kernel": "k_coarse + k_assign_refine (4*N*K*D flop of "
+                     "log-densities, bf16 MFMA peak), k_assign_theta + k_assign_collect for "
+                     "the points with many candidates",
                      "achieved": round(rate, 2), "peak": peak,
                      "unit": "TFLOP/s", "frac": round(rate / peak, 4)}}),
           flush=True)
@@ -488,17 +491,20 @@ def main():
     log(f"  phases (ms per E-step): {phases}")
     flops = 8.0 * w.n * k * d
     dense_rate = flops / (estep_ms * 1e-3) / 1e12
-    # dominant kernel: k_logz, its log-density contraction per launch: [x | x^2] against
+    # dominant phase: the screening, its log-density contraction per E-step: [x | x^2] against
     # [W | P] (depth 2D) for the diagonal model, 4 N K D flop; [x | ||x||^2] against
     # [mu / var | -1/(2 var)] (depth D + 1) for the isotropic one, 2 N K (D + 1) flop
     logz_ms = phases["logz"] or float("nan")
-    # split-bf16 screening (three bf16 products per fp32 product) for D <= 128 and D > 256;
-    # fp32 MFMA in between
-    logz_b16 = padded_d(d) <= 128 or padded_d(d) > 256
+    # one bf16 product per pair and dimension (k_coarse; points with many candidates also go
+    # through k_logz); the screened calls run k_logz alone, split bf16 (three products) for
+    # D <= 128 and D > 256, fp32 MFMA in between
+    split = padded_d(d) <= 128 or padded_d(d) > 256
+    logz_b16 = split or not screened
+    products = 3 if screened and split else 1
     logz_peak = BF16_MFMA_PEAK_TFLOPS if logz_b16 else FP32_MFMA_PEAK_TFLOPS
-    # the isotropic screening runs where the split-bf16 one does; in between the isotropic
-    # calls take the diagonal kernel with tied variances
-    iso_screen = iso and logz_b16
+    # the isotropic operands are used where the split-bf16 screening is; in between the
+    # isotropic calls take the diagonal kernels with tied variances
+    iso_screen = iso and split
     logz_flop = 2.0 * w.n * k * (d + 1) if iso_screen else 4.0 * w.n * k * d
     logz_alg = logz_flop / (logz_ms * 1e-3) / 1e12
     dominant = max(phases, key=lambda p: phases[p] or 0.0)
@@ -513,7 +519,7 @@ def main():
         "higher_is_better": False,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": ("bf16 hi/lo split MFMA (screening log-densities), f32 MFMA (dense statistics), "
+        "dtype": ("bf16 MFMA (screening log-densities), f32 MFMA (dense statistics), "
                   "f64 (exact pairs, sums)") if logz_b16 else
                  "f32 MFMA (log-densities, dense statistics), f64 (exact pairs, sums)",
         "data": "synthetic",
@@ -524,17 +530,18 @@ def main():
                    "precision": ("screened: split-bf16 log-densities for every pair, no fp64 "
                                  "refinement" if screened else "exact")},
         "roofline": {"bound": "mfma",
-                     "kernel": "k_logz (" + ("2*N*K*(D+1)" if iso_screen else "4*N*K*D")
-                               + " flop of log-densities per launch, "
-                               + ("bf16 MFMA peak; 3 bf16 products per fp32 product"
-                                  if logz_b16 else "fp32 MFMA peak") + ")",
+                     "kernel": ("k_logz (" if screened else "k_coarse + k_refine + k_logz (")
+                               + ("2*N*K*(D+1)" if iso_screen else "4*N*K*D")
+                               + " flop of log-densities per E-step, "
+                               + (f"bf16 MFMA peak; {products} bf16 product(s) per pair and "
+                                  "dimension" if logz_b16 else "fp32 MFMA peak") + ")",
                      "achieved": round(logz_alg, 2), "peak": logz_peak, "unit": "TFLOP/s",
                      "frac": round(logz_alg / logz_peak, 4),
-                     # counters were taken on the exact diagonal path's k_logz only
+                     # counters were taken on the exact diagonal path only
                      "traffic": None if (screened or iso) else measured_traffic(w.name),
                      "kernel_ms": logz_ms,
-                     "executed_tflops": round(logz_alg * (3 if logz_b16 else 1), 2),
-                     # k_logz reads X once: its X stream against the HBM peak
+                     "executed_tflops": round(logz_alg * products, 2),
+                     # X once over the phase's time, against the HBM peak
                      "x_stream_gbs": round(4.0 * w.n * d / (logz_ms * 1e-3) / 1e9, 1),
                      "dominant_phase": dominant, "phases_ms": phases,
                      "estep_ms": round(estep_ms, 3),

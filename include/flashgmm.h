@@ -335,12 +335,13 @@ int gmm_estep_accumulate_static(const float* x, int64_t n, int32_t d, int32_t k,
 
 /*
  * Chunking of the dense statistics pass, a tuning control (no part of the
- * method).  That pass splits the points into chunks, one workgroup per
- * (64-component block, chunk); a workgroup queues the chunk's points that
- * need its block, sums their statistics on fp32 MFMA and adds the fp32 sums
- * into fp64 partials every 4096 queued points; the partials are summed in
- * chunk order.  The library picks the chunk count from (n, d, k) (about 8192
- * workgroups); max_chunks > 0 caps it, 0 restores the automatic count.
+ * method).  That pass splits the points that need it into chunks, one
+ * workgroup per (16-component group, chunk); a workgroup queues the chunk's
+ * points that need its group, sums their statistics on fp32 MFMA and adds the
+ * fp32 sums into fp64 partials every 4096 queued points; the partials are
+ * summed in chunk order.  The library picks the largest chunk count from
+ * (n, d, k) and takes fewer chunks when few points need the pass;
+ * max_chunks > 0 caps it, 0 restores the automatic count.
  * Fewer, longer chunks change the results by rounding only (the split of the
  * fp32 runs moves) and never need a larger workspace.  The setting is
  * process-wide and read when a call is made; calls made under different
@@ -355,13 +356,14 @@ int gmm_set_stats_chunk_limit(int32_t max_chunks);
  * gmm_fit) records HIP events on its stream between its phases, waits for the
  * last of them and adds each phase's GPU duration to a process-wide total:
  *   0  parameter preparation (k_prep_*)
- *   1  screening, refinement and log Z of every point (k_logz)
+ *   1  screening, refinement and log Z of every point (k_coarse, k_refine, and
+ *      k_logz for the points with more than 8 candidates)
  *   2  statistics of the stored exact pairs (k_sparse_*, k_stats_sparse)
  *   3  the list of light components (little mass in their stored pairs) and
  *      the dense statistics of the other well-conditioned components
  *      (k_small_mass, k_small_list, k_stats_well / k_stats_wide)
  *   4  routed and light components in the direct form, and the fixed-order
- *      reductions (k_stats_ill, k_reduce_stats, k_reduce_ll)
+ *      reductions (k_stats_direct or k_stats_ill, k_reduce_stats, k_reduce_ll)
  * gmm_timing_enable(on) switches it on (creating the events on the current
  * device at first use) or off, and zeroes the totals.  gmm_timing_read copies
  * the first n_phases totals (ms; phases past GMM_TIMING_PHASES read 0) and the

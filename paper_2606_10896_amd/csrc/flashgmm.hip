@@ -12,19 +12,23 @@
 //               operands: bf16 hi and lo parts for the split-bf16 screening,
 //               fp32 for the fp32 screening and the statistics.
 //   logz        Step 1 of Algorithm 1: log-densities l = [x | x^2] . [W | P]^T + c
-//               on MFMA (three bf16 products per fp32 product, or fp32), an
-//               online log-sum-exp over all components, the pairs that carry
-//               a point's mass recomputed in the direct form in fp64, one fp64
-//               log-normaliser per point and per-workgroup log-likelihood
-//               partials.
-//   stats       Step 2 of Algorithm 1: the same log-densities recomputed on
-//               fp32 MFMA for the (point, 64-component block) pairs that can
-//               hold a responsibility above 2^-64, r = 2^(l - log2 Z) kept in
-//               registers, and the statistic contraction r^T [x | x^2] on fp32
-//               MFMA whose accumulators are added into fp64 partials every 4096
-//               queued points; the few pairs that carry most of a point's
-//               mass are summed exactly in fp64 on the vector ALU (fp32
-//               products are exact in fp64).
+//               of every pair on MFMA from one bf16 product each, with a bound
+//               of their error (k_coarse): it lists every component that can
+//               be within 2^-64 of a point's largest, and where these are at
+//               most 8, the log-normaliser is the fp64 sum of their exact
+//               (direct form) terms (k_refine).  The other points are screened
+//               again in split bf16 (three products) or fp32, with an online
+//               log-sum-exp over all components and the pairs that carry the
+//               point's mass recomputed in fp64 (k_logz).
+//   stats       Step 2 of Algorithm 1: a point's four largest exact pairs are
+//               summed in fp64; for the (point, group of components) pairs in
+//               which another one can hold a responsibility above 2^-64 the
+//               log-densities are recomputed on fp32 MFMA, r = 2^(l - log2 Z)
+//               is kept in registers, and the statistics are contracted,
+//               r^T [x | x^2], on fp32 MFMA whose accumulators are added into
+//               fp64 partials every 4096 queued points.  Components with
+//               little mass and routed ones (below) take the direct form, and
+//               their statistics are contracted in fp64.
 //   reduce      fixed-order fp64 sums of the partials (instead of the paper's
 //               atomics), added into the caller's accumulators.
 //   mstep       closed-form M-step (Eqs. Nk, muk, sig per dimension) in fp64.
@@ -40,12 +44,12 @@
 // component collapsing onto one point, beyond any fp32 accumulation.
 //
 // Results are bitwise reproducible run to run: every sum runs in a fixed
-// order.  The only atomics are LDS integer counters: the exact pairs' counts
-// per bucket (sums of ones, the same in any order) and the counters with
-// which the assignment kernels append candidates to per-point lists; a list
-// is sorted before its terms are summed, and the fallback's list of points
-// only decides which points a workgroup visits, each point's result being
-// its own.
+// order.  The only atomics are integer ones: the exact pairs' counts per bucket
+// (sums of ones, the same in any order), bits set in masks, the counters with
+// which the assignment kernels append candidates to per-point lists, and those
+// that append to lists of points.  A list of candidates is sorted before its
+// terms are summed; a list of points only decides which points a workgroup
+// visits, each point's result being its own.
 
 #include <hip/hip_runtime.h>
 
@@ -95,12 +99,14 @@ constexpr int kRefCap = 1024;
 constexpr int kRefLanes = 4;
 constexpr double kNarrowWindow = 10.0;
 constexpr double kLooseBound = -12.0;
-// Dense statistics are formed only for the (point, 64-component block) pairs
-// that can hold a responsibility above 2^-kDenseWindow that is not among the
-// point's stored exact pairs: a lane state within kDenseWindow of the
-// screening log2 Z marks its arg-max component's block (unless that component
-// is stored), and all of its blocks when the screened mass of its other
-// components exceeds kDenseMass of the point's total.  Every pair left out
+// Dense statistics are formed only for the (point, mask granule) pairs (16 to
+// 64 components, mask_shift) that can hold a responsibility above
+// 2^-kDenseWindow that is not among the point's stored exact pairs.  Where all
+// candidates are listed, those not stored mark their granules; in k_logz a lane
+// state within kDenseWindow of the screening log2 Z marks its arg-max
+// component's granule (unless that component is stored), and all of its
+// granules when the screened mass of its other components exceeds kDenseMass
+// of the point's total.  Every pair left out
 // has r < 2^-kDenseWindow up to the screening error (a few log2 units at
 // most), so a component's N_k moves by less than N 2^-58.
 constexpr float kDenseWindow = 64.0f;
@@ -3304,8 +3310,8 @@ __global__ __launch_bounds__(64 * (DW / 128)) void k_stats_wide(
     first = false;
   };
 
-  // Windows of WIN points: the points that need this group's 64-component
-  // block (every point when dlist is null) are queued in point order, the
+  // Windows of WIN entries: the points that need this group's mask granule
+  // (every point when dlist is null) are queued in point order, the
   // full 16-point tiles of the queue are processed (at the chunk's end also
   // the partial one) and the rest moves to the queue's front.
   const unsigned long long kbit = 1ull << (((16 * g) >> gsh) & 63);
@@ -3976,10 +3982,10 @@ __global__ __launch_bounds__(256) void k_stats_ill(
   // log-density there came within 2^-72 of log2 Z), and the point's stored
   // exact pairs are left out there: the exact-pair pass has summed them.  At
   // every other point each light component is either stored or has
-  // r < 2^-64.  lmask holds the 64-component blocks in which that happened:
-  // a point is taken only for the light components of those blocks (the list is
-  // in slot order, so this workgroup's lie in the blocks from its first one's to
-  // its last one's).
+  // r < 2^-64.  lmask holds the granules (mask_shift) in which that happened:
+  // a point is taken only for the light components of those granules (the list
+  // is in slot order, so this workgroup's lie in the granules from its first
+  // one's to its last one's).
   unsigned long long want = ~0ull;
   if (small_pos != nullptr && lmask != nullptr) {
     const int last = (kb + 1) * ICB < n_ill ? (kb + 1) * ICB - 1 : n_ill - 1;
