@@ -14,10 +14,7 @@ k_refine, and k_logz for the points with many candidates), timed over the timed
 steps with the library's phase timer (HIP events recorded on the stream the
 kernels run on).  Its algorithmic work is the log-density contraction over all
 N x K pairs, 4*N*K*D flop per E-step ([x | x^2] against [W | P], depth 2D),
-priced against the peak of the MFMA type it runs on (bf16, one product with an
-error bound; of the screened calls: bf16 for D <= 128 and D > 256, where the
-fp32 operands are split in hi/lo bf16 parts and three products are summed, fp32
-in between).  The E-step as a whole is also reported against the 8*N*K*D
+priced against the bf16 peak (one product with an error bound).  The E-step as a whole is also reported against the 8*N*K*D
 flop of the dense algorithm.  `cpu_baseline` times the fp64 CPU checker on a
 bounded slice of the same data and scales it linearly in N (the E-step is
 exactly linear in N).
@@ -313,8 +310,8 @@ def main():
                          "variance per component, the *_iso calls)")
     ap.add_argument("--precision", choices=("exact", "screened"), default="exact",
                     help="exact E-step (default, the reported value) or the reduced-precision "
-                         "one (gmm_estep_accumulate_screened: screened log-densities for every "
-                         "pair, looser tolerances)")
+                         "one (gmm_estep_accumulate_screened: screened log-densities for the "
+                         "points with many candidates, looser tolerances)")
     ap.add_argument("--from-init", type=int, default=-1, metavar="ITERS",
                     help="after the timed steps, also time ITERS iterations of one gmm_fit call "
                          "from the initialisation (-1: the workload's own iteration count, "
@@ -496,12 +493,9 @@ def main():
     # [mu / var | -1/(2 var)] (depth D + 1) for the isotropic one, 2 N K (D + 1) flop
     logz_ms = phases["logz"] or float("nan")
     # one bf16 product per pair and dimension (k_coarse; points with many candidates also go
-    # through k_logz); the screened calls run k_logz alone, split bf16 (three products) for
-    # D <= 128 and D > 256, fp32 MFMA in between
+    # through k_logz)
     split = padded_d(d) <= 128 or padded_d(d) > 256
-    logz_b16 = split or not screened
-    products = 3 if screened and split else 1
-    logz_peak = BF16_MFMA_PEAK_TFLOPS if logz_b16 else FP32_MFMA_PEAK_TFLOPS
+    logz_peak = BF16_MFMA_PEAK_TFLOPS
     # the isotropic operands are used where the split-bf16 screening is; in between the
     # isotropic calls take the diagonal kernels with tied variances
     iso_screen = iso and split
@@ -519,28 +513,26 @@ def main():
         "higher_is_better": False,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": ("bf16 MFMA (screening log-densities), f32 MFMA (dense statistics), "
-                  "f64 (exact pairs, sums)") if logz_b16 else
-                 "f32 MFMA (log-densities, dense statistics), f64 (exact pairs, sums)",
+        "dtype": "bf16 MFMA (screening log-densities), f32 MFMA (dense statistics), "
+                 "f64 (exact pairs, sums)",
         "data": "synthetic",
         "config": {"workload": f"{w.name}: {'isotropic' if iso else 'diag'}-GMM EM, N={w.n}, "
                                f"D={d}, K={k}, fp32 points from {w.k_true} seeded diagonal "
                                "Gaussians, random-point init",
                    "n": w.n, "d": d, "k": k, "parallelism": "single GPU",
-                   "precision": ("screened: split-bf16 log-densities for every pair, no fp64 "
-                                 "refinement" if screened else "exact")},
+                   "precision": ("screened: no fp64 refinement of the points with many "
+                                 "candidates" if screened else "exact")},
         "roofline": {"bound": "mfma",
-                     "kernel": ("k_logz (" if screened else "k_coarse + k_refine + k_logz (")
+                     "kernel": "k_coarse + k_refine + k_logz ("
                                + ("2*N*K*(D+1)" if iso_screen else "4*N*K*D")
-                               + " flop of log-densities per E-step, "
-                               + (f"bf16 MFMA peak; {products} bf16 product(s) per pair and "
-                                  "dimension" if logz_b16 else "fp32 MFMA peak") + ")",
+                               + " flop of log-densities per E-step, bf16 MFMA peak; one bf16 "
+                               "product per pair and dimension)",
                      "achieved": round(logz_alg, 2), "peak": logz_peak, "unit": "TFLOP/s",
                      "frac": round(logz_alg / logz_peak, 4),
                      # counters were taken on the exact diagonal path only
                      "traffic": None if (screened or iso) else measured_traffic(w.name),
                      "kernel_ms": logz_ms,
-                     "executed_tflops": round(logz_alg * products, 2),
+                     "executed_tflops": round(logz_alg, 2),
                      # X once over the phase's time, against the HBM peak
                      "x_stream_gbs": round(4.0 * w.n * d / (logz_ms * 1e-3) / 1e9, 1),
                      "dominant_phase": dominant, "phases_ms": phases,

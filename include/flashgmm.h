@@ -125,12 +125,14 @@ int gmm_fit(const float* x, int64_t n, int32_t d, int32_t k, int32_t n_iters, fl
 
 /*
  * Reduced-precision E-step and fit: the calls above with the log-densities
- * left at the precision of the screening pass, i.e. the expanded form
+ * of the points that have more than 8 significant components left at the
+ * precision of their screening pass, i.e. the expanded form
  * (Sec. 3, the two contractions X (mu/var)^T and X^2 (1/var)^T) on split
- * bf16 matrix products, three bf16 products per fp32 product (fp32 above
- * d = 128), with fp32 accumulation.  The exact calls recompute the few
- * pairs that carry a point's mass in the direct form, in fp64; these calls
- * keep the screened values for them too.  Everything else (arguments,
+ * bf16 matrix products, three bf16 products per fp32 product (fp32 for
+ * 128 < d <= 256), with fp32 accumulation.  The exact calls recompute the few
+ * pairs that carry such a point's mass in the direct form, in fp64; these
+ * calls keep the screened values for them (the other points are evaluated as
+ * in the exact calls).  Everything else (arguments,
  * accumulation, workspace, dead and ill-conditioned components, status
  * codes) is as in gmm_estep_accumulate / gmm_fit.
  * Error: a screened log-density is within about 2^-22 log2(e) (S_k + d)
