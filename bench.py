@@ -14,10 +14,10 @@ k_refine, and k_logz for the points with many candidates), timed over the timed
 steps with the library's phase timer (HIP events recorded on the stream the
 kernels run on).  Its algorithmic work is the log-density contraction over all
 N x K pairs, 4*N*K*D flop per E-step ([x | x^2] against [W | P], depth 2D),
-priced against the bf16 peak (one product with an error bound).  The E-step as a whole is also reported against the 8*N*K*D
-flop of the dense algorithm.  `cpu_baseline` times the fp64 CPU checker on a
-bounded slice of the same data and scales it linearly in N (the E-step is
-exactly linear in N).
+priced against the bf16 peak (one product with an error bound).  The E-step as
+a whole is also reported against the 8*N*K*D flop of the dense algorithm.
+`cpu_baseline` times the fp64 CPU checker on a bounded slice of the same data
+and scales it linearly in N (the E-step is exactly linear in N).
 """
 from __future__ import annotations
 
@@ -211,8 +211,8 @@ def write_traffic(workload, fetch_csv, write_csv, copy_fetch_csv, copy_write_csv
 
 def measured_traffic(workload, key="logz_bytes_per_launch"):
     """HBM bytes of an E-step's screening phase (or, with key="bytes_per_call", of the E-step)
-    from the committed counter runs (profiles/estep_traffic_<workload>.json), or None when the kernels
-    have changed since."""
+    from the committed counter runs (profiles/estep_traffic_<workload>.json), or None when the
+    kernels have changed since."""
     path = os.path.join(ROOT, "profiles", f"estep_traffic_{workload}.json")
     if not os.path.exists(path):
         return None
