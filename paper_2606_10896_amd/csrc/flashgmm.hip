@@ -349,8 +349,9 @@ __device__ __forceinline__ double ill_logit_bounded_gr(const float* __restrict__
 // Workspace counters: [0] well components, [1] ill-conditioned components,
 // [2] well 32-blocks, [3] ill 32-blocks, then those of the one-product
 // screening: heavy points of its sample, "wild" parameters (weights near the
-// end of the float range: its error bound does not hold, every point is
-// heavy), and the number of heavy points (64 bits).
+// end of the float range: its error bound does not hold; or no component with a
+// weight above 0: there is nothing to list; every point is heavy), and the
+// number of heavy points (64 bits).
 // Then the entries of the dense list (64 bits, k_sparse_offsets).
 constexpr int kCntSample = 4, kCntWild = 5, kCntHeavy = 6, kCntDense = 8;
 constexpr double kWildWeight = 1e28;
@@ -467,7 +468,7 @@ __global__ __launch_bounds__(256) void k_prep_scan(const int* __restrict__ cls, 
     counts[2] = (aw + kBK - 1) / kBK;
     counts[3] = (ai + kBK - 1) / kBK;
     counts[kCntSample] = 0;
-    counts[kCntWild] = wild != 0;
+    counts[kCntWild] = wild != 0 || aw + ai == 0;
     counts[kCntHeavy] = counts[kCntHeavy + 1] = 0;
   }
   for (int c = b; c < e; ++c) {
@@ -1991,6 +1992,16 @@ __host__ __device__ constexpr int coarse_tiles(int D64, bool iso) {
 }
 // Workgroups per compute unit.
 __host__ __device__ constexpr int coarse_wgs(int D64) { return D64 <= 256 ? 2 : 1; }
+// Bits that hold the index of one of `groups` groups.
+__host__ __device__ constexpr int index_bits(int groups) {
+  int b = 0;
+  while (groups > 1 && ((unsigned)(groups - 1) >> b) != 0u) ++b;
+  return b;
+}
+static_assert(index_bits(0) == 0 && index_bits(1) == 0 && index_bits(2) == 1 &&
+                  index_bits(3) == 2 && index_bits(64) == 6 && index_bits(65) == 7 &&
+                  index_bits((GMM_MAX_K + 15) / 16) == 12,
+              "index bits");
 // Operand pieces (steps) a wave of the SPLIT form reads ahead: a divisor of NS.
 __host__ __device__ constexpr int coarse_ring(int NS) {
   for (int r = 8; r > 3; --r)
@@ -2219,7 +2230,7 @@ __global__ __launch_bounds__(256, SPLIT ? 1 : coarse_wgs(D64)) void k_coarse(
   __shared__ float xlo[SPLIT ? 4 : 1][PTS];     // SPLIT: the waves' bounds, then their counts
   __shared__ int hcnt[4];
   __shared__ unsigned long long hbase;
-  if (!sample && coarse_off(counts, sample_max)) return;
+  if (coarse_off(counts, sample ? INT_MAX : sample_max)) return;    // no component: off too
   const int n_c = counts[0] + counts[1], nkb = (n_c + 16 * GPB - 1) / (16 * GPB);
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int k4 = lane >> 4, col = lane & 15;
@@ -2303,8 +2314,7 @@ __global__ __launch_bounds__(256, SPLIT ? 1 : coarse_wgs(D64)) void k_coarse(
       xr[t][NS - 1] = last;
     }
   }
-  int nbits = 0;                                // index bits: the group of 16
-  while ((GPB * nkb - 1) >> nbits) ++nbits;
+  const int nbits = index_bits(GPB * nkb);      // index bits: the group of 16
   const unsigned imask = (1u << nbits) - 1u;
   unsigned keep = ~imask;
   asm volatile("" : "+v"(keep));                // a vector register: the index is the scalar operand

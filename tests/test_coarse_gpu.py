@@ -186,3 +186,26 @@ def test_weights_near_the_end_of_the_float_range():
     st = gpu_estep(x, wt, mu, var, ws=_dirty_ws(3000, 24, 40))
     check_stats(st, ref, "wild")
     assert st["nk"][11] == 0.0
+
+
+@pytest.mark.parametrize("weight", [0.0, np.nan])
+@pytest.mark.parametrize("n", [300, 65600, (1 << 18) + 5])
+def test_no_component_left(n, weight):
+    """Every weight 0, or NaN as after an iteration on NaN rows: no component, so nothing to
+    screen, at shared and whole workgroups and with the sample.  No point reaches a component:
+    statistics 0, log-likelihood -inf, every rank empty."""
+    import torch
+    import paper_2606_10896_amd as gmm
+    rng = np.random.default_rng(3)
+    d, k, m = 20, 70, 2
+    x, mu = (rng.normal(0.0, 1.0, s).astype(np.float32) for s in ((n, d), (k, d)))
+    wt, var = np.full(k, weight, np.float32), np.ones((k, d), np.float32)
+    st = gpu_estep(x, wt, mu, var, ws=_dirty_ws(n, d, k))
+    assert st["loglik"] == -np.inf
+    for a in ("nk", "s", "q"):
+        assert (st[a] == 0.0).all(), a
+    ws = gmm.workspace(n, d, k, m)
+    ws.fill_(0xEE)
+    torch.cuda.synchronize()
+    idx, resp = gpu_assign(x, wt, mu, var, m, 0.1, ws=ws)
+    assert (idx == -1).all() and (resp == 0.0).all()
