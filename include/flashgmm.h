@@ -24,8 +24,12 @@
  *     return a negative gmm_status (nothing is enqueued then).  A HIP error
  *     reported at launch returns GMM_ERR_DEVICE.  NaN or Inf in the inputs is
  *     not checked; it propagates into the outputs.
- *   - Limits: 1 <= d <= GMM_MAX_D, 1 <= k <= GMM_MAX_K, n >= 1 (n may exceed
- *     2^31), 1 <= m <= GMM_MAX_M.  Shapes beyond them return
+ *   - Limits: 1 <= d <= GMM_MAX_D, 1 <= k <= GMM_MAX_K, 1 <= m <= GMM_MAX_M,
+ *     n >= 1, and at most GMM_MAX_ROWS(d) rows in one call that works on rows
+ *     in device memory (gmm_kmeanspp, which has no such launches, excepted):
+ *     a launch has fewer than 2^32 threads.  More rows are several calls
+ *     (E-steps add up; assignments are independent) or an out-of-core call,
+ *     whose limit is on its chunks.  Shapes beyond them return
  *     GMM_ERR_UNSUPPORTED.
  *   - Results are bitwise deterministic for a given (n, d, k), inputs and
  *     statistics chunk limit (gmm_set_stats_chunk_limit): every sum runs in a
@@ -48,11 +52,12 @@ extern "C" {
 #define GMM_MAX_D 1024
 #define GMM_MAX_K 65535
 #define GMM_MAX_M 8
+#define GMM_MAX_ROWS(d) ((((int64_t)1 << 24) - 1) * ((d) <= 256 ? 64 : 32))
 
 typedef enum {
   GMM_OK = 0,
   GMM_ERR_INVALID_ARG = -1, /* null pointer, non-positive size, bad m/tau */
-  GMM_ERR_UNSUPPORTED = -2, /* d, k or m beyond the library's limits */
+  GMM_ERR_UNSUPPORTED = -2, /* d, k, m or n beyond the library's limits */
   GMM_ERR_WORKSPACE = -3,   /* workspace missing, misaligned or too small */
   GMM_ERR_DEVICE = -4,      /* a HIP call or kernel launch failed */
   GMM_ERR_FILL = -5         /* the caller's fill function reported a failure */

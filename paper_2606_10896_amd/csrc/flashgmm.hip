@@ -2671,9 +2671,10 @@ __device__ __forceinline__ void refine_point(const float* __restrict__ x, int64_
 // E-step outputs of the points whose candidates are listed (see k_logz for what
 // they mean): log2 Z, the kT largest exact responsibilities, the blocks of the
 // other well components above 2^-kDenseWindow, the routed components' flag.
+// Rows row0, row0 + 1, ... (refine_ranges).
 template <int D64>
 __global__ __launch_bounds__(256) void k_refine(
-    const float* __restrict__ x, int64_t n, int d, const unsigned short* __restrict__ cand,
+    const float* __restrict__ x, int64_t row0, int64_t n, int d, const unsigned short* __restrict__ cand,
     const int* __restrict__ cidx, const float* __restrict__ dmu, const double* __restrict__ dh,
     const double* __restrict__ cdir, const int* __restrict__ counts, int sample_max,
     double* __restrict__ logz2, unsigned short* __restrict__ cslot, float* __restrict__ cr,
@@ -2682,7 +2683,7 @@ __global__ __launch_bounds__(256) void k_refine(
   constexpr int G = refine_lanes(D64);
   if (coarse_off(counts, sample_max)) return;
   const int lane = threadIdx.x & 63, g = lane & (G - 1);
-  const int64_t nn = ((int64_t)blockIdx.x * 256 + threadIdx.x) / G;
+  const int64_t nn = row0 + ((int64_t)blockIdx.x * 256 + threadIdx.x) / G;
   uint4 list = make_uint4(~0u, ~0u, ~0u, ~0u);
   if (nn < n) list = *reinterpret_cast<const uint4*>(cand + nn * kCand);
   const bool light = (list.x & 0xFFFFu) != kNoSlot;
@@ -2763,14 +2764,14 @@ __global__ __launch_bounds__(256) void k_refine(
 // component that can be assigned is a candidate.
 template <int D64>
 __global__ __launch_bounds__(256) void k_assign_refine(
-    const float* __restrict__ x, int64_t n, int d, const unsigned short* __restrict__ cand,
+    const float* __restrict__ x, int64_t row0, int64_t n, int d, const unsigned short* __restrict__ cand,
     const int* __restrict__ cidx, const float* __restrict__ dmu, const double* __restrict__ dh,
     const double* __restrict__ cdir, const int* __restrict__ counts, int sample_max, int m,
     float tau, int* __restrict__ idx, float* __restrict__ resp, int* __restrict__ ovf) {
   constexpr int G = refine_lanes(D64);
   if (coarse_off(counts, sample_max)) return;
   const int lane = threadIdx.x & 63, g = lane & (G - 1);
-  const int64_t nn = ((int64_t)blockIdx.x * 256 + threadIdx.x) / G;
+  const int64_t nn = row0 + ((int64_t)blockIdx.x * 256 + threadIdx.x) / G;
   uint4 list = make_uint4(~0u, ~0u, ~0u, ~0u);
   if (nn < n) list = *reinterpret_cast<const uint4*>(cand + nn * kCand);
   const bool light = (list.x & 0xFFFFu) != kNoSlot;
@@ -5705,6 +5706,8 @@ __global__ __launch_bounds__(256) void k_zero(double* __restrict__ p, int64_t cn
 // ---------------------------------------------------------------- host side
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
+// Blocks of 256 threads of one launch: fewer than 2^32 threads.
+constexpr int64_t kMaxBlocks = ((int64_t)1 << 24) - 1;
 
 struct Layout {
   int64_t n;
@@ -6053,6 +6056,18 @@ void launch_coarse(const Layout& L, const float* x, void* ws, float window, hipS
                      cv.hlist);
 }
 
+// Launches of k_refine / k_assign_refine over n rows: f(first row, blocks of 256 threads).
+// They take 8 to 32 threads a row, so that from 2^27 to 2^29 rows on one launch would pass
+// the 2^32 - 1 threads it may have.
+template <int D64, class F>
+void refine_ranges(int64_t n, F&& f) {
+  constexpr int64_t per = 256 / refine_lanes(D64);      // rows a block
+  for (int64_t row0 = 0; row0 < n; row0 += kMaxBlocks * per) {
+    const int64_t blocks = cdiv(n - row0, per);
+    f(row0, (unsigned)(blocks < kMaxBlocks ? blocks : kMaxBlocks));
+  }
+}
+
 template <int D64>
 int estep_impl(const Layout& L, const float* x, const float* w, const float* mu,
                const float* var, double* nk, double* s, double* q, double* loglik,
@@ -6118,9 +6133,11 @@ int estep_impl(const Layout& L, const float* x, const float* w, const float* mu,
     else launch_coarse<D64, false>(L, x, ws, kCoarseWindow, st, &smax);
     hlist = coarse_view(L, ws).hlist;
     const CoarseView cv = coarse_view(L, ws);
-    hipLaunchKernelGGL(k_refine<D64>, dim3((unsigned)cdiv(n * refine_lanes(D64), 256)), dim3(256),
-                       0, st, x, n, d, cv.cand, cv.cidx, dmu, dh, cdir, counts, smax, logz2,
-                       cslot, cr, bmask, iflag, lflag, gsh);
+    refine_ranges<D64>(n, [&](int64_t row0, unsigned blocks) {
+      hipLaunchKernelGGL(k_refine<D64>, dim3(blocks), dim3(256), 0, st, x, row0, n, d, cv.cand,
+                         cv.cidx, dmu, dh, cdir, counts, smax, logz2, cslot, cr, bmask, iflag,
+                         lflag, gsh);
+    });
   }
   bool launched = false;
   if constexpr (screen_split(D64)) {
@@ -6272,9 +6289,10 @@ int assign_impl(const Layout& L, const float* x, const float* w, const float* mu
     else launch_coarse<D64, false>(L, x, ws, window, st, &smax);
     const CoarseView cv = coarse_view(L, ws);
     hlist = cv.hlist;
-    hipLaunchKernelGGL(k_assign_refine<D64>, dim3((unsigned)cdiv(n * refine_lanes(D64), 256)),
-                       dim3(256), 0, st, x, n, d, cv.cand, cv.cidx, dmu, dh, cdir, counts, smax,
-                       m, tau, idx, resp, ovf);
+    refine_ranges<D64>(n, [&](int64_t row0, unsigned blocks) {
+      hipLaunchKernelGGL(k_assign_refine<D64>, dim3(blocks), dim3(256), 0, st, x, row0, n, d,
+                         cv.cand, cv.cidx, dmu, dh, cdir, counts, smax, m, tau, idx, resp, ovf);
+    });
   }
   // up to kFewHeavy points, all of them heavy at most: nothing for the two passes
   if (hlist == nullptr || n > kFewHeavy) {
@@ -6362,7 +6380,11 @@ int estep_dispatch(const Layout& L, const float* x, const float* w, const float*
   }
 }
 
+// The workspace, and that every per-point launch of the call is one that HIP takes (the
+// largest are the heavy points' passes: 256 threads for pts_logz rows).  A launch refused in
+// the middle of a call would leave the later ones to work on memory that nothing wrote.
 int check_ws(const Layout& L, void* ws, size_t ws_bytes) {
+  if (L.n_wg_logz > kMaxBlocks) return GMM_ERR_UNSUPPORTED;
   if (ws == nullptr || (reinterpret_cast<uintptr_t>(ws) & 255) != 0 || ws_bytes < L.total)
     return GMM_ERR_WORKSPACE;
   return GMM_OK;

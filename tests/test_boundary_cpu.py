@@ -273,3 +273,23 @@ def test_static_estep_refuses_shapes_beyond_its_array_before_any_launch():
                                            None) == gmm.GMM_ERR_INVALID_ARG
     assert lib.gmm_estep_accumulate_static(f, 0, 16, 8, f, f, f, f, f, f, f,
                                            None) == gmm.GMM_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("d", [2, 256, 257, 1024])
+def test_rows_beyond_one_launch_are_refused_before_any_launch(d):
+    # fewer than 2^32 threads a launch, 256 of them for 64 rows (32 above 256 dimensions)
+    lib = gmm.load_library()
+    p, ws = _fake(), _fake(0x200000)
+    most = ((1 << 24) - 1) * (64 if d <= 256 else 32)
+    for n, want in ((most, gmm.GMM_ERR_WORKSPACE), (most + 1, gmm.GMM_ERR_UNSUPPORTED)):
+        nb = gmm.workspace_bytes(n, d, 4, 1)
+        nb = nb if n > most else nb - 1
+        for fn in (lib.gmm_estep_accumulate, lib.gmm_estep_accumulate_iso,
+                   lib.gmm_estep_accumulate_screened):
+            e = nb if n > most else 1
+            assert fn(p, n, d, 4, p, p, p, p, p, p, p, ws, e, None) == want
+        for fn in (lib.gmm_fit, lib.gmm_fit_screened, lib.gmm_fit_iso):
+            assert fn(p, n, d, 4, 2, 1e-6, p, p, p, p, ws, 1 if n <= most else nb, None) == want
+        assert lib.gmm_assign_topk(p, n, d, 4, p, p, p, 1, ctypes.c_float(0.1), p, p, ws, nb,
+                                   None) == want
+        assert lib.gmm_kmeans(p, n, d, 4, 1, 1e-6, p, p, p, p, ws, nb, None) == want
