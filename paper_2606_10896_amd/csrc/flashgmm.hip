@@ -62,6 +62,7 @@
 #include <thread>
 #include <vector>
 #include <type_traits>
+#include <utility>
 
 #include "flashgmm.h"
 
@@ -2189,6 +2190,16 @@ __device__ __forceinline__ void top3_high(float& m1, float& m2, float u) {
       : "v"(u));
 }
 
+// f(0), f(1), ... with the index a constant.  (`#pragma unroll` is given up on where the
+// unrolled body passes the compiler's limit, and arrays indexed by what is then a variable
+// live in scratch memory: so it was in k_coarse above 768 dimensions, with two scratch loads
+// an MFMA.  E-step at n = 2e5, k = 1024: d = 960 24.5 ms, 4.0 with constants; d = 1024 25.3
+// and 4.5.)
+template <class F, int... I>
+__device__ __forceinline__ void static_steps(std::integer_sequence<int, I...>, F&& f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+
 typedef float f4v __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ f4v mfma16b(bf16x8 a, bf16x8 b, f4v c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
@@ -2196,9 +2207,9 @@ __device__ __forceinline__ f4v mfma16b(bf16x8 a, bf16x8 b, f4v c) {
 
 // A wave takes 16 NT points (their operands, rounded to bf16, stay in registers
 // for the whole pass: lane l holds point l % 16 of each tile) against every
-// component, 16 at a time; the workgroup's four waves share blocks of 64 (above
-// 128 dimensions 32) components through a double-buffered LDS tile, loaded one block ahead (global
-// to LDS, no registers).  Accumulator register v of lane l is component 16 g +
+// component, 16 at a time; the workgroup's four waves share blocks of 64 components
+// (32 above 128 dimensions, 16 above 512) through a double-buffered LDS tile, loaded one
+// block ahead (global to LDS, no registers).  Accumulator register v of lane l is component 16 g +
 // 4 (l / 16) + v of point l % 16.  A lane state (point, lane group, register) thus
 // covers every 16th component; it keeps its three largest t, whose low mantissa
 // bits carry the group, so that an update is four instructions: mask-and-or, two
@@ -2358,22 +2369,25 @@ __global__ __launch_bounds__(256, SPLIT ? 1 : coarse_wgs(D64)) void k_coarse(
     for (int q = 0; q < RW - 1; ++q) w[q] = wl[64 * q];
     f4v bias[2];
     bias[PAR] = *reinterpret_cast<const f4v*>(bl);
-#pragma unroll
-    for (int q = 0; q < WB; ++q) {
-      const int gi = q / NS, s = q % NS, A = (gi + PAR) & 1;
-      if (q + RW - 1 < WB) w[(q + RW - 1) % RW] = wl[64 * (q + RW - 1)];
-      if (s == NS - 2 && gi + 1 < GPB)
+    // every index of the points' operands, the ring and the accumulators is a
+    // constant: they are registers at any width
+    static_steps(std::make_integer_sequence<int, WB>{}, [&](auto qc) {
+      constexpr int q = decltype(qc)::value, gi = q / NS, s = q % NS, A = (gi + PAR) & 1;
+      if constexpr (q + RW - 1 < WB) w[(q + RW - 1) % RW] = wl[64 * (q + RW - 1)];
+      if constexpr (s == NS - 2 && gi + 1 < GPB)
         bias[(gi + 1 + PAR) & 1] = *reinterpret_cast<const f4v*>(bl + 16 * (gi + 1));
       const int g = GPB * kb + gi;
-#pragma unroll
-      for (int t = 0; t < NT; ++t) {
+      static_steps(std::make_integer_sequence<int, NT>{}, [&](auto tc) {
+        constexpr int t = decltype(tc)::value;
+        constexpr int i0 = (s * NT + t) * NV / NM, i1 = (s * NT + t + 1) * NV / NM;
         acc[A][t] = mfma16b(w[q % RW], xr[t][s], s == 0 ? bias[A] : acc[A][t]);
-#pragma unroll
-        for (int i = (s * NT + t) * NV / NM; i < (s * NT + t + 1) * NV / NM; ++i)
+        static_steps(std::make_integer_sequence<int, i1 - i0>{}, [&](auto ic) {
+          constexpr int i = i0 + decltype(ic)::value;
           take(i & 1, i >> 3, (i >> 1) & 3, acc[1 - A][i >> 3][(i >> 1) & 3], g > 0 ? g - 1 : 0);
+        });
         __builtin_amdgcn_sched_barrier(0);
-      }
-    }
+      });
+    });
   };
   if constexpr (SPLIT) {
     const int ng = GPB * nkb;

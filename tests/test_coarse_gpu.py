@@ -1,9 +1,9 @@
 """The one-product screening of the E-step and of the assignment (k_coarse, k_refine,
 k_assign_refine and the points they hand to the two- or three-product passes) against the fp64
-checker, at the edges of its tiles and of its rules: workgroups of 128 and 256 points, blocks of 32 components, widths with and without a remainder, points with
-more components in reach than a list or a lane state holds, the sample that switches the pass
-off, and weights near the end of the float range.  The workspace starts as garbage, so a point
-that no kernel wrote would show."""
+checker, at the edges of its tiles and of its rules: workgroups of 64 to 256 points, blocks of 16 to 64 components, widths
+with and without a remainder, points with more components in reach than a list or a lane state
+holds, the sample that switches the pass off, and weights near the end of the float range.  The
+workspace starts as garbage, so a point that no kernel wrote would show."""
 import numpy as np
 import pytest
 
@@ -57,6 +57,18 @@ def test_tile_edges(n, d, k):
     x, th0 = g.make(w)
     for t, th in enumerate(oracle.fit(x, *th0, 3, keep_thetas=True)["thetas"]):
         _check(x, th, f"n{n} d{d} k{k} t{t}")
+
+
+@pytest.mark.parametrize("n,d,k", [(65600, 770, 97), (65573, 896, 96), (65601, 960, 33),
+                                   (65536, 1024, 130)])
+def test_blocks_of_the_widest_rows(n, d, k):
+    """Whole workgroups above 768 dimensions through an odd and an even number of blocks of 16
+    components, a last one in part."""
+    w = g.custom(f"cb{n}_{d}_{k}", n, d, max(2, k // 2), k, data_seed=n * 7 + d, init_seed=k)
+    x, th0 = g.make(w)
+    for t, th in enumerate(oracle.fit(x, *th0, 1, keep_thetas=True)["thetas"]):
+        _check(x, th, f"n{n} d{d} k{k} t{t}")
+    _check_assign(x, th, 2, 1.0 / k, f"assign n{n} d{d} k{k}")
 
 
 @pytest.mark.parametrize("n,d,k", [(255, 64, 33), (257, 100, 64), (700, 128, 97),
