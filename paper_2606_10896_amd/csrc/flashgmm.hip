@@ -1938,13 +1938,18 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_logz(
 //             M <= KD (cdir - l) + KA (cdir - cwell), KD = 6, KA = 4 (the x
 //             products alone, for tied variances, whose ||x||^2 step carries
 //             three bf16 pieces of either factor: KD = 3, KA = 2.5); eps =
-//             coarse_eps: two roundings of 2^-8 and the fp32 accumulation.  With
-//             b = eps (KD cdir + KA (cdir - cwell)) per component and
+//             coarse_eps: two roundings of 2^-8 and acc = coarse_acc of the fp32
+//             accumulation, whose running sums hold the bias too: with
+//             b0 = eps (KD cdir + KA (cdir - cwell)) per component,
+//             b = b0 + 1.01 acc (|cwell| + |b0|) + the bias's own rounding, and
 //             t = l~ + b (b is part of the bias),
 //               l <= t / (1 + KD eps),   l >= (t - 2 b) / (1 - KD eps).
 //             Every component with an upper bound above (best lower bound) -
 //             window is a candidate; a point with more than kCand candidates is
-//             heavy and goes to k_logz.
+//             heavy and goes to k_logz.  All of it holds for densities less a
+//             constant: k-means, whose components share cdir, leaves it out
+//             (window 0: the bounds alone decide, and 1.3 log2 units a dimension of
+//             a common constant would be most of the magnitudes they round).
 //   k_refine  the candidates' log-densities in the direct form (fp64), log Z
 //             from them (the rest is below k 2^-window of it), the stored
 //             pairs and the dense blocks of the others.
@@ -1978,10 +1983,13 @@ __host__ __device__ constexpr int coarse_steps() {
 }
 __host__ __device__ constexpr double coarse_kd(bool iso) { return iso ? 3.0 : 6.0; }
 __host__ __device__ constexpr double coarse_ka(bool iso) { return iso ? 2.5 : 4.0; }
-// 2^-7 (1 + 2^-8) for the operands' roundings (two of 2^-8); five roundings of
-// 2^-22 of a running sum per MFMA for the accumulation
+// Five roundings of 2^-22 of a running sum per MFMA for the accumulation
+__host__ __device__ constexpr double coarse_acc(int D64, bool iso) {
+  return (5.0 * (iso ? D64 / 32 : D64 / 16) + 16.0) * 0x1p-22;
+}
+// and 2^-7 (1 + 2^-8) for the operands' roundings (two of 2^-8).
 __host__ __device__ constexpr double coarse_eps(int D64, bool iso) {
-  return 0x1p-7 * (1.0 + 0x1p-8) + (5.0 * (iso ? D64 / 32 : D64 / 16) + 16.0) * 0x1p-22;
+  return 0x1p-7 * (1.0 + 0x1p-8) + coarse_acc(D64, iso);
 }
 // 16-point tiles per wave: the points' operands stay in registers; up to 256
 // dimensions two waves share each SIMD (256 registers each), above one has it
@@ -2022,14 +2030,15 @@ __host__ __device__ constexpr int coarse_groups(int D64) {
 // that meets the three bf16 pieces of ||x||^2 (lane group l / 16 = 0, places 0..2
 // and 3..5, group 1, places 0..2) with the three pieces of -1/2 log2(e) / var.
 // cbias[slot] = c + b, cb2[slot] = 2 b, cidx[slot] = the component; slots past the
-// last component have weights 0 and a bias far below everything.
+// last component have weights 0 and a bias far below everything.  common: without
+// the first component's cdir, which every component has.
 template <int D64, bool ISO>
 __device__ __forceinline__ void pack_coarse(
     int64_t t, const float* __restrict__ mu, const float* __restrict__ var, int d, int kpad,
     const double* __restrict__ cwell, const double* __restrict__ cdir,
     const int* __restrict__ counts, const int* __restrict__ well_idx,
-    const int* __restrict__ ill_idx, bf16x8* __restrict__ wpc, float* __restrict__ cbias,
-    float* __restrict__ cb2, int* __restrict__ cidx) {
+    const int* __restrict__ ill_idx, bool common, bf16x8* __restrict__ wpc,
+    float* __restrict__ cbias, float* __restrict__ cb2, int* __restrict__ cidx) {
   constexpr int NS = coarse_steps<D64, ISO>(), NX = D64 / 32;
   if (t >= (int64_t)(kpad / 16) * NS * 64) return;
   const int lane = (int)(t & 63), s = (int)((t >> 6) % NS), gr = (int)((t >> 6) / NS);
@@ -2069,9 +2078,11 @@ __device__ __forceinline__ void pack_coarse(
     constexpr double kEps = coarse_eps(D64, ISO);
     double bias = -3.0e38, b = 0.0;
     if (comp >= 0) {
-      const double cd = cdir[comp], cwl = cwell[comp];
-      // the second term: fp32 roundings of the bias and of the bounds themselves
-      b = kEps * (coarse_kd(ISO) * cd + coarse_ka(ISO) * (cd - cwl)) +
+      const double c0 = common ? cdir[n_well > 0 ? well_idx[0] : ill_idx[0]] : 0.0;
+      const double cd = cdir[comp] - c0, cwl = cwell[comp] - c0;
+      const double b0 = kEps * (coarse_kd(ISO) * cd + coarse_ka(ISO) * (cd - cwl));
+      // the last term: fp32 roundings of the bias and of the bounds themselves
+      b = b0 + 1.01 * coarse_acc(D64, ISO) * (fabs(cwl) + fabs(b0)) +
           0x1p-20 * (fabs(cd) + fabs(cwl) + 1.0);
       bias = cwl + b;
     }
@@ -2119,6 +2130,7 @@ struct PackArgs {
   bf16x8* wpc;
   float *cbias, *cb2;
   int* cidx;
+  bool common;              // the components share cdir: leave it out of the one-product biases
 };
 
 // ISOB, ISOW, ISOC: tied variances in the bf16 screening's, the dense
@@ -2144,7 +2156,7 @@ __global__ __launch_bounds__(256) void k_prep_pack(PackArgs a) {
   part(3, [&](int64_t t) { pack_direct<D64>(t, a.mu, a.var, a.d, a.k, a.dmu, a.dh); });
   part(4, [&](int64_t t) {
     pack_coarse<D64, ISOC>(t, a.mu, a.var, a.d, a.kpad, a.cwell, a.cdir, a.counts, a.well_idx,
-                           a.ill_idx, a.wpc, a.cbias, a.cb2, a.cidx);
+                           a.ill_idx, a.common, a.wpc, a.cbias, a.cb2, a.cidx);
   });
   part(5, [&](int64_t t) {
     pack_slots(t, a.cwell, a.cdir, a.counts, a.well_idx, a.kpad, a.thr);
@@ -6023,6 +6035,7 @@ PackArgs pack_args(const Layout& L, const float* w, const float* mu, const float
   a.cbias = cv.cbias;
   a.cb2 = cv.cb2;
   a.cidx = cv.cidx;
+  a.common = false;
   return a;
 }
 
@@ -6254,6 +6267,7 @@ int estep_impl(const Layout& L, const float* x, const float* w, const float* mu,
   return tm && phase_collect() ? GMM_OK : GMM_ERR_DEVICE;
 }
 
+// window: kAssignWindow, or 0 for the nearest of centres (equal weights and variances, m = 1).
 template <int D64>
 int assign_impl(const Layout& L, const float* x, const float* w, const float* mu,
                 const float* var, int m, float tau, float window, int* idx, float* resp,
@@ -6290,6 +6304,7 @@ int assign_impl(const Layout& L, const float* x, const float* w, const float* mu
     if (coarse)
       a.blocks[4] = pack_blocks(kpad / 16, L.iso ? coarse_steps<D64, true>()
                                                  : coarse_steps<D64, false>());
+    a.common = window == 0.0f;
     if (L.iso) launch_pack<D64, false, false, true>(a, st);
     else launch_pack<D64, false, false, false>(a, st);
   }

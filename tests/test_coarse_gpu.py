@@ -173,6 +173,33 @@ def test_kmeans_through_the_screening(n, d, k):
     np.testing.assert_allclose(wd.cpu().numpy(), ref["weights"], rtol=1e-3, atol=2.0 / n)
 
 
+@pytest.mark.parametrize("scale", [1e-3, 0.05, 1.0])
+def test_kmeans_of_rows_of_any_scale(scale):
+    """Wide rows whose squared distances (8e-3 between centres at scale 1e-3) are small beside
+    the constant that all centres share, 0.5 d log(2 pi) + log k: the bound that dismisses a
+    centre may not be made of that constant.  Every assignment is the fp64 nearest centre, and
+    no point is left to the passes for points with many candidates (their number is the seventh
+    counter at the workspace's start)."""
+    import torch
+    import paper_2606_10896_amd as gmm
+    rng = np.random.default_rng(17)
+    n, d, k = 4000, 1000, 64
+    c = rng.normal(0.0, 2.0, (k, d))
+    x = (scale * (c[rng.integers(0, k, n)] + rng.normal(0.0, 1.0, (n, d)))).astype(np.float32)
+    mu = (scale * (c + rng.normal(0.0, 0.2, (k, d)))).astype(np.float32)
+    xd, md = (torch.from_numpy(a).cuda() for a in (x, mu))
+    wd, vd = torch.full((k,), 1.0 / k, device="cuda"), torch.ones(k, d, device="cuda")
+    assign, ws = torch.empty(n, dtype=torch.int32, device="cuda"), _dirty_ws_m(n, d, k)
+    gmm.gmm_kmeans(xd, wd, md, vd, 0, assign, ws)
+    torch.cuda.synchronize()
+    m64 = mu.astype(np.float64)
+    near = (x.astype(np.float64) @ m64.T - 0.5 * (m64 ** 2).sum(1)).argmax(1)
+    assert (assign.cpu().numpy() == near).all()
+    heavy = int(ws[:64].view(torch.int32)[6])
+    print(f"  k-means scale {scale}: {heavy} of {n} points with many candidates", flush=True)
+    assert heavy == 0
+
+
 @pytest.mark.parametrize("spread", [0.0, 1.0])
 def test_sample_switches_the_pass(spread):
     """n beyond the sample's threshold: one mixture whose components all overlap (the sample
