@@ -56,3 +56,30 @@ def test_routed_components(n, d, k, routed):
         assert (np.abs(st["q"][c] - q) <= tol * q + floor * top * top).all(), c
     print(f"  routed n{n} d{d} k{k}: {routed} components, "
           f"N_k {r[:, ill].sum():.3f}", flush=True)
+
+
+@pytest.mark.parametrize("d", [16, 128, 200, 300])
+@pytest.mark.parametrize("place", [0, 15, 16, 38])
+def test_one_light_component(d, place):
+    """One component with little mass among heavy ones that overlap everywhere: its statistics are
+    those of the points that the dense pass flags, once for the sixteen components of a group
+    whichever of them is the light one."""
+    rng = np.random.default_rng(100 * d + place)
+    n, k = 4000, 39
+    mu = rng.normal(0.0, 2.0 / np.sqrt(d), (k, d)).astype(np.float32)
+    var = rng.uniform(0.9, 1.1, (k, d)).astype(np.float32)
+    w = np.full(k, 1.0)
+    w[place] = 0.02
+    w = (w / w.sum()).astype(np.float32)
+    x = (mu[rng.integers(0, k, n)] + rng.normal(0.0, 1.0, (n, d))).astype(np.float32)
+    r = _exact(x, w, mu, var)
+    mass = r.sum(0)
+    assert mass[place] < 64.0 < np.delete(mass, place).min()
+    st = gpu_estep(x, w, mu, var)
+    xd = x.astype(np.float64)
+    # log Z keeps the screening error of what is below 2^-20 of it, r is as above
+    tol = 2.0 ** -16
+    c = place
+    assert abs(st["nk"][c] - mass[c]) <= tol * mass[c], (st["nk"][c], mass[c])
+    assert (np.abs(st["s"][c] - r[:, c] @ xd) <= tol * (r[:, c] @ np.abs(xd))).all()
+    assert (np.abs(st["q"][c] - r[:, c] @ (xd * xd)) <= tol * (r[:, c] @ (xd * xd))).all()
