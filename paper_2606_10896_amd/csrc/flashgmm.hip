@@ -5299,11 +5299,14 @@ __global__ __launch_bounds__(1024) void k_small_list(const unsigned char* __rest
   }
 }
 
-// kRedLanes threads share an output, each every kRedLanes-th partial sum, their
-// sums added in order: with one thread an output a call's last launch was a
-// chain of hundreds of dependent batches of loads.  n = 1e4, d = 16, k = 8: 29.5
-// -> 9.4 us; n = 1e6, d = 128, k = 1024: 95 us, bound by the partial sums' bytes.
-constexpr int kRedOut = 32, kRedLanes = 8;
+// LANES threads share an output, each every LANES-th partial sum, their sums added
+// in order.  With one thread an output a call's last launch was a chain of hundreds
+// of dependent batches of loads (n = 1e4, d = 16, k = 8: 29.5 us, 9.4 with eight; n =
+// 1e6, d = 128, k = 1024: 95 us with eight, bound by the partial sums' bytes); with
+// eight a call with many outputs of few partial sums each is threads without one
+// (n = 1000, d = 768, k = 4096: 413 us, 72 with one; the line is reduce_lanes).
+constexpr int kRedLanes = 8;
+template <int LANES>
 __global__ __launch_bounds__(256) void k_reduce_stats(
     const double* __restrict__ part_w, const double* __restrict__ part_s,
     const double* __restrict__ part_i,
@@ -5312,22 +5315,25 @@ __global__ __launch_bounds__(256) void k_reduce_stats(
     int ipt, int64_t n, int k, int d, int D64, const int* __restrict__ small_pos,
     const double* __restrict__ part_x, const int* __restrict__ small_cnt, int dense_listed,
     double* __restrict__ nk, double* __restrict__ s, double* __restrict__ q) {
-  const int64_t width = 1 + 2 * (int64_t)d;
-  __shared__ double sh[kRedLanes][kRedOut];
-  const int g = threadIdx.x / kRedOut, o = threadIdx.x % kRedOut;
-  const int64_t t = (int64_t)blockIdx.x * kRedOut + o;
+  constexpr int OUT = 256 / LANES;
+  const unsigned width = 1 + 2 * (unsigned)d;
+  __shared__ double sh[LANES][OUT];
+  const int g = threadIdx.x / OUT, o = threadIdx.x % OUT;
+  // 2 k width outputs: below 2^29 (32-bit divisions)
+  static_assert(2ull * GMM_MAX_K * (1 + 2 * GMM_MAX_D) < (1ull << 29), "outputs fit 32 bits");
+  const unsigned t = blockIdx.x * OUT + o, tot = (unsigned)k * width;
   auto part = [&](const double* p, int cnt, size_t step, double acc) {
-    return sum_strided(p + (size_t)g * step, cnt > g ? (cnt - g + kRedLanes - 1) / kRedLanes : 0,
-                       step * kRedLanes, acc);
+    return sum_strided(p + (size_t)g * step, cnt > g ? (cnt - g + LANES - 1) / LANES : 0,
+                       step * LANES, acc);
   };
-  const int which = (int)(t / ((int64_t)k * width));
-  const int64_t rem = t % ((int64_t)k * width);
+  const int which = t >= tot ? 1 : 0;
+  const unsigned rem = t >= tot ? t - tot : t;
   const int slot = (int)(rem / width), c = (int)(rem % width);
   const int64_t stride = 1 + 2 * (int64_t)D64;
   const int64_t off = c == 0 ? 0 : (c <= d ? 1 + (c - 1) : 1 + D64 + (c - 1 - d));
   double acc = 0.0;
   int comp = -1;                                // none: the slot is past its list
-  if (t >= 2 * (int64_t)k * width) {
+  if (t >= 2 * tot) {
   } else if (which == 0 && slot < counts[0]) {
     comp = well_idx[slot];
     const int xp = small_pos != nullptr ? small_pos[slot] : -1;
@@ -5361,7 +5367,7 @@ __global__ __launch_bounds__(256) void k_reduce_stats(
   __syncthreads();
   if (g != 0 || comp < 0) return;
 #pragma unroll
-  for (int u = 1; u < kRedLanes; ++u) acc += sh[u][o];
+  for (int u = 1; u < LANES; ++u) acc += sh[u][o];
   if (c == 0) nk[comp] += acc;
   else if (c <= d) s[(int64_t)comp * d + (c - 1)] += acc;
   else q[(int64_t)comp * d + (c - 1 - d)] += acc;
@@ -6092,6 +6098,18 @@ void launch_coarse(const Layout& L, const float* x, void* ws, float window, hipS
                      cv.hlist);
 }
 
+// Threads an output of k_reduce_stats: one where the outputs fill the chip by themselves (2^18:
+// 1024 workgroups) and there are 2048 of them for each partial sum that the longest chain may
+// have.  E-step with eight and with one: n = 1000, d = 768, k = 4096 1446 and 1181 us; n =
+// 8000, d = 384, k = 1024 299 and 277; n = 8000, d = 128, k = 1024 336 and 334; n = 1e5
+// 548.6 and 554.4, where eight it is.
+inline int reduce_lanes(const Layout& L) {
+  const int64_t outs = 2 * (int64_t)L.k * (1 + 2 * (int64_t)L.d);
+  const int64_t nchk = cdiv(L.n, L.ipt) < L.grid_i ? cdiv(L.n, L.ipt) : L.grid_i;
+  const int64_t most = L.nch + L.nparts + nchk;
+  return outs >= (1 << 18) && outs >= 2048 * most ? 1 : kRedLanes;
+}
+
 // Launches of k_refine / k_assign_refine over n rows: f(first row, blocks of 256 threads).
 // They take 8 to 32 threads a row, so that from 2^27 to 2^29 rows on one launch would pass
 // the 2^32 - 1 threads it may have.
@@ -6263,10 +6281,14 @@ int estep_impl(const Layout& L, const float* x, const float* w, const float* mu,
                        spos, cls, gsh, part_x);
   {
     const int64_t tot = 2 * (int64_t)k * (1 + 2 * (int64_t)d);
-    hipLaunchKernelGGL(k_reduce_stats, dim3((unsigned)cdiv(tot, kRedOut)),
-                       dim3(kRedOut * kRedLanes), 0, st, part_w, part_s, part_i, counts, well_idx,
-                       ill_idx, L.nch, L.wbk, L.nparts, L.sbk, L.grid_i, L.ibk, L.ipt, n, k, d,
-                       D64, spos, part_x, scnt2, dlist != nullptr ? 1 : 0, nk, s, q);
+    auto reduce = [&](auto kernel, int lanes) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)cdiv(tot * lanes, 256)), dim3(256), 0, st, part_w,
+                         part_s, part_i, counts, well_idx, ill_idx, L.nch, L.wbk, L.nparts, L.sbk,
+                         L.grid_i, L.ibk, L.ipt, n, k, d, D64, spos, part_x, scnt2,
+                         dlist != nullptr ? 1 : 0, nk, s, q);
+    };
+    if (reduce_lanes(L) == 1) reduce(k_reduce_stats<1>, 1);
+    else reduce(k_reduce_stats<kRedLanes>, kRedLanes);
   }
   hipLaunchKernelGGL(k_reduce_ll, dim3(1), dim3(1024), 0, st, llpart, (int64_t)L.nunit, loglik,
                      ll_accumulate);

@@ -59,6 +59,14 @@ def test_tile_edges(n, d, k):
         _check(x, th, f"n{n} d{d} k{k} t{t}")
 
 
+@pytest.mark.parametrize("n,d,k", [(300, 128, 1024), (300, 127, 1030), (65, 700, 300), (90, 300, 500)])
+def test_many_outputs_of_few_partial_sums(n, d, k):
+    """The reduction with one thread an output, outputs in a last workgroup in part."""
+    w = g.custom(f"cr{n}_{d}_{k}", max(n, k), d, k // 2, k, data_seed=n + d, init_seed=k)
+    x, th0 = g.make(w)
+    _check(x[:n], th0, f"outputs n{n} d{d} k{k}")
+
+
 @pytest.mark.parametrize("n,d,k", [(65600, 770, 97), (65573, 896, 96), (65601, 960, 33),
                                    (65536, 1024, 130)])
 def test_blocks_of_the_widest_rows(n, d, k):
