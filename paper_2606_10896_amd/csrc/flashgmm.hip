@@ -1969,8 +1969,22 @@ constexpr float kCoarseWindow = kDenseWindow;
 // n = 1.18e6, d = 100, k = 1024, 64 % heavy: 8.64 ms with it, 8.2 without).
 constexpr int kSampleWG = 256;
 constexpr int64_t kSampleMin = (int64_t)1 << 18;
-// Heavy points of an assignment up to which they are done over all components.
-constexpr int kFewHeavy = 512;
+// Heavy points of an assignment up to which they are done over all components
+// (k_assign_fallback): their time grows with k D64 a point (9 to 16 TB/s of parameters), that
+// of the two passes is the latency of one workgroup, which grows with k D64 too and is three
+// times longer where they run in fp32 (128 < D64 <= 256).  Whole calls with the passes and
+// without: d = 128, k = 1024 167 and 92 us at 626 heavy points, 152 and 146 at 2218, 155 and
+// 208 at 4119; d = 64, k = 256 81 and 62 at 2132, 86 and 112 at 7858; d = 200, k = 1024 448
+// and 310 at 4386; d = 768, k = 1024 390 and 283 at 986, 390 and 471 at 2297; d = 768, k =
+// 4096 946 and 798 at 518, 934 and 1211 at 1053.
+constexpr int kFbGrid = 512;            // workgroups for them
+inline int few_heavy(int k, int D64) {
+  const int64_t kd = (int64_t)k * D64;
+  int64_t most = 4096;                  // small k D64: the workgroups' own time
+  if (D64 <= 128) most = 1536 + (1 << 26) / kd;
+  else if (D64 > 256) most = 384 + (1 << 29) / kd;
+  return (int)(most < 4096 ? most : 4096);
+}
 // Candidate window of an assignment: what lies below is at most k 2^-40 of the
 // normaliser, and cannot be assigned to a rank j > 1 when tau >= 2^-40.
 constexpr float kAssignWindow = 40.0f;
@@ -4635,7 +4649,7 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_assign_theta(
     const float* __restrict__ x, int64_t n, int d, int vec4, const float4* __restrict__ wp,
     const bf16x8* __restrict__ wpb, const float* __restrict__ cw,
     const float2* __restrict__ ca, const int* __restrict__ counts, int tsel,
-    const int64_t* __restrict__ hlist, int sample_max, float2* __restrict__ theta) {
+    const int64_t* __restrict__ hlist, int sample_max, int few_max, float2* __restrict__ theta) {
   constexpr int P = D64 + 4, NT = logz_tiles(D64), PTS = 32 * NT;
   // SPL: split tile in LDS; SPB: split-bf16 screening (from the split tile or,
   // D64 > 256, from the fp32 tile), whose thresholds need the arg-max slots
@@ -4658,7 +4672,7 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_assign_theta(
   // the points taken: the heavy ones of the one-product screening, or all
   const bool whole = hlist == nullptr || coarse_off(counts, sample_max);
   const int64_t np = whole ? n : heavy_count(counts);
-  if (n0 >= np || (!whole && np <= kFewHeavy)) return;
+  if (n0 >= np || (!whole && np <= few_max)) return;
   auto row_of = [&](int p) -> int64_t {
     if (n0 + p >= np) return n;
     return whole ? n0 + p : hlist[n0 + p];
@@ -4776,7 +4790,7 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_assign_collect
     const double* __restrict__ dh, const int* __restrict__ counts,
     const float2* __restrict__ theta, const float* __restrict__ mu,
     const float* __restrict__ var, const double* __restrict__ cdir, int m, float tau,
-    const int64_t* __restrict__ hlist, int sample_max, int* __restrict__ idx,
+    const int64_t* __restrict__ hlist, int sample_max, int few_max, int* __restrict__ idx,
     float* __restrict__ resp, int* __restrict__ ovf) {
   constexpr int P = D64 + 4, NT = logz_tiles(D64), PTS = 32 * NT;
   constexpr bool SPL = screen_b16(D64);
@@ -4801,7 +4815,7 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_assign_collect
   // the points taken: the heavy ones of the one-product screening, or all
   const bool whole = hlist == nullptr || coarse_off(counts, sample_max);
   const int64_t np = whole ? n : heavy_count(counts);
-  if (n0 >= np || (!whole && np <= kFewHeavy)) return;
+  if (n0 >= np || (!whole && np <= few_max)) return;
   auto row_of = [&](int p) -> int64_t {
     if (n0 + p >= np) return n;
     return whole ? n0 + p : hlist[n0 + p];
@@ -5042,155 +5056,224 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_assign_collect
 
 // Points done exactly over every component in fp64: those whose candidate list
 // overflowed, and the heavy points of the one-product screening when there are
-// at most kFewHeavy of them (one workgroup a point, which takes less time than
-// one workgroup of the two screening passes).  Eight lanes share a component's
+// at most `few_max` of them (few_heavy).  Eight lanes share a component's
 // direct-form sum (coalesced parameter rows: one thread a component took 1.1 ms
 // for 30 points of 128 dimensions at k = 1024), kFbBatch components at a time so
-// that their loads fly together; every group keeps a top-m list and a log-sum-exp
-// state of its components in ascending order, and the groups' are merged by
-// m block-wide arg-max rounds and fixed-order sums.
-constexpr int kFbBatch = 8;
-__global__ __launch_bounds__(256) void k_assign_fallback(
-    const float* __restrict__ x, int64_t n, int d, int D64, int k, const float* __restrict__ dmu,
-    const double* __restrict__ dh, const double* __restrict__ cdir, int m, float tau,
-    const int* __restrict__ ovf, const int* __restrict__ counts,
-    const int64_t* __restrict__ hlist, int sample_max, int* __restrict__ idx,
-    float* __restrict__ resp) {
-  constexpr int G = 8, NGR = 256 / G;
-  __shared__ __align__(16) float xr[GMM_MAX_D];
-  __shared__ int plist[1024];
-  __shared__ int pcnt;
-  __shared__ double wl[2][4];
-  __shared__ int wc[2][4];
-  __shared__ double wz[4];
+// that their loads fly together.  The lanes' sums are added by a transposing
+// reduction that leaves a lane with the sums of its own (component, point)
+// pairs: log-densities, top-m list and log-sum-exp are then one lane's work
+// (each was all eight lanes').  More heavy points than compute units are taken
+// kFbPts at a time, which read the parameters once for all of them (d = 1024, k =
+// 1024: 122 us for 74 points, 260 for 257 one by one, 180 for 515 four by four);
+// the lists of a point's lanes are merged by m block-wide arg-max rounds and
+// fixed-order sums.
+constexpr int kFbBatch = 8, kFbPts = 4, kFbSingle = 256;
+template <int P>
+__device__ __forceinline__ void fallback_points(
+    const float* __restrict__ x, int64_t (&row)[P], int d, int D64, int k,
+    const float* __restrict__ dmu, const double* __restrict__ dh,
+    const double* __restrict__ cdir, int m, float tau, float (*xr)[GMM_MAX_D], double (*wl)[4][kFbPts],
+    int (*wc)[4][kFbPts], double (*wz)[kFbPts], int* __restrict__ idx, float* __restrict__ resp) {
+  constexpr int G = 8, NGR = 256 / G, NV = kFbBatch * P / G;      // pairs of a lane a round
+  static_assert(kFbBatch == G && (P == 1 || P == 4), "reduction below");
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = tid & (G - 1);
   const int grp = tid / G;
-  const int64_t b0 = (int64_t)blockIdx.x * 1024;
-  const bool off = coarse_off(counts, sample_max);
-  // every point of a call that small (the two passes were not launched)
-  const bool each = hlist != nullptr && off && n <= kFewHeavy;
-  const bool few = each || (hlist != nullptr && !off && heavy_count(counts) <= kFewHeavy);
-  if (!few && b0 >= n) return;
-  if (tid == 0) pcnt = 0;
+  const int mp = P == 1 ? 0 : g & (P - 1);                        // the lane's point
+#pragma unroll
+  for (int p = 0; p < P; ++p)
+    for (int j = tid; j < D64; j += 256) xr[p][j] = j < d && row[p] >= 0 ? x[row[p] * d + j] : 0.0f;
   __syncthreads();
-  // the order of the list does not matter: every point's result is its own
-  if (few) {
-    // the light points' lists never overflow; entries blockIdx.x, + gridDim.x, ...
-    const int hc = each ? (int)n : (int)heavy_count(counts);
-    if (tid == 0) pcnt = hc > (int)blockIdx.x ? (hc - 1 - (int)blockIdx.x) / (int)gridDim.x + 1 : 0;
-  } else {
-    for (int i = tid; i < 1024; i += 256)
-      if (b0 + i < n && ovf[b0 + i]) plist[atomicAdd(&pcnt, 1)] = i;
-  }
-  __syncthreads();
-  const int np = pcnt;
-  for (int ip = 0; ip < np; ++ip) {
-    const int64_t i = blockIdx.x + (int64_t)ip * gridDim.x;
-    const int64_t nn = each ? i : (few ? hlist[i] : b0 + plist[ip]);
-    for (int j = tid; j < D64; j += 256) xr[j] = j < d ? x[nn * d + j] : 0.0f;
-    __syncthreads();
-    double tl[GMM_MAX_M];
-    int ti[GMM_MAX_M];
+  double tl[GMM_MAX_M];
+  int ti[GMM_MAX_M];
 #pragma unroll
-    for (int j = 0; j < GMM_MAX_M; ++j) { tl[j] = -INFINITY; ti[j] = INT_MAX; }
-    double mx = -INFINITY, sm = 0.0;            // natural log
-    for (int c0 = grp; c0 < k; c0 += kFbBatch * NGR) {
-      double acc[kFbBatch];
+  for (int j = 0; j < GMM_MAX_M; ++j) { tl[j] = -INFINITY; ti[j] = INT_MAX; }
+  double mx = -INFINITY, sm = 0.0;              // natural log
+  for (int c0 = grp; c0 < k; c0 += kFbBatch * NGR) {
+    double acc[kFbBatch][P];
 #pragma unroll
-      for (int u = 0; u < kFbBatch; ++u) acc[u] = 0.0;
-      for (int c4 = 4 * g; c4 < D64; c4 += 4 * G) {
-        const float4 xv = *reinterpret_cast<const float4*>(xr + c4);
-        float4 mv[kFbBatch];
-        double2 h0[kFbBatch], h1[kFbBatch];
+    for (int u = 0; u < kFbBatch; ++u)
 #pragma unroll
-        for (int u = 0; u < kFbBatch; ++u) {
-          const int comp = c0 + u * NGR < k ? c0 + u * NGR : c0;
-          mv[u] = *reinterpret_cast<const float4*>(dmu + (size_t)comp * D64 + c4);
-          h0[u] = *reinterpret_cast<const double2*>(dh + (size_t)comp * D64 + c4);
-          h1[u] = *reinterpret_cast<const double2*>(dh + (size_t)comp * D64 + c4 + 2);
-        }
+      for (int p = 0; p < P; ++p) acc[u][p] = 0.0;
+    for (int c4 = 4 * g; c4 < D64; c4 += 4 * G) {
+      float4 mv[kFbBatch];
+      double2 h0[kFbBatch], h1[kFbBatch];
+#pragma unroll
+      for (int u = 0; u < kFbBatch; ++u) {
+        const int comp = c0 + u * NGR < k ? c0 + u * NGR : c0;
+        mv[u] = *reinterpret_cast<const float4*>(dmu + (size_t)comp * D64 + c4);
+        h0[u] = *reinterpret_cast<const double2*>(dh + (size_t)comp * D64 + c4);
+        h1[u] = *reinterpret_cast<const double2*>(dh + (size_t)comp * D64 + c4 + 2);
+      }
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        const float4 xv = *reinterpret_cast<const float4*>(xr[p] + c4);
 #pragma unroll
         for (int u = 0; u < kFbBatch; ++u) {
           double t;
-          t = (double)xv.x - (double)mv[u].x; acc[u] = fma(t * t, h0[u].x, acc[u]);
-          t = (double)xv.y - (double)mv[u].y; acc[u] = fma(t * t, h0[u].y, acc[u]);
-          t = (double)xv.z - (double)mv[u].z; acc[u] = fma(t * t, h1[u].x, acc[u]);
-          t = (double)xv.w - (double)mv[u].w; acc[u] = fma(t * t, h1[u].y, acc[u]);
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < kFbBatch; ++u) {
-        const int comp = c0 + u * NGR;
-        const double a = group_sum<G>(acc[u]);
-        if (comp >= k) continue;                // the same for the group's lanes
-        const double l = kLn2 * (cdir[comp] - a);
-        if (!(l > -INFINITY)) continue;
-        if (l > mx) { sm = sm * exp(mx - l) + 1.0; mx = l; }
-        else sm += exp(l - mx);
-        // components arrive in increasing index order: ties keep the earlier
-        if (l > tl[GMM_MAX_M - 1] || ti[GMM_MAX_M - 1] == INT_MAX) {
-#pragma unroll
-          for (int q = GMM_MAX_M - 1; q >= 0; --q) {
-            const bool above = ti[q] == INT_MAX || l > tl[q];
-            const bool above_prev = q > 0 && (ti[q - 1] == INT_MAX || l > tl[q - 1]);
-            if (above_prev) { tl[q] = tl[q - 1]; ti[q] = ti[q - 1]; }
-            else if (above) { tl[q] = l; ti[q] = comp; }
-          }
+          t = (double)xv.x - (double)mv[u].x; acc[u][p] = fma(t * t, h0[u].x, acc[u][p]);
+          t = (double)xv.y - (double)mv[u].y; acc[u][p] = fma(t * t, h0[u].y, acc[u][p]);
+          t = (double)xv.z - (double)mv[u].z; acc[u][p] = fma(t * t, h1[u].x, acc[u][p]);
+          t = (double)xv.w - (double)mv[u].w; acc[u][p] = fma(t * t, h1[u].y, acc[u][p]);
         }
       }
     }
-    // rank j: the largest list head (ties to the lower component), whose group
-    // drops it; the normaliser after the first round
-    double lz = 0.0;
-    for (int j = 0; j < m; ++j) {
-      double bl = tl[0];
-      int bc = ti[0];
-      auto pick = [&](double ol, int oc) {
-        const bool o = oc != INT_MAX && (bc == INT_MAX || ol > bl || (ol == bl && oc < bc));
-        bl = o ? ol : bl;
-        bc = o ? oc : bc;
-      };
-      pick(xshfl<8>(bl), xshfl_i<8>(bc));
-      pick(xshfl<16>(bl), xshfl_i<16>(bc));
-      pick(__shfl_xor(bl, 32), __shfl_xor(bc, 32));
-      if (lane == 0) {
-        wl[j & 1][wave] = bl;
-        wc[j & 1][wave] = bc;
-      }
-      __syncthreads();
-      bl = wl[j & 1][0];
-      bc = wc[j & 1][0];
-      for (int w = 1; w < 4; ++w) pick(wl[j & 1][w], wc[j & 1][w]);
-      if (j == 0) {
-        double z = mx > -INFINITY ? sm * exp(mx - bl) : 0.0;
-        z += xshfl<8>(z);
-        z += xshfl<16>(z);
-        z += __shfl_xor(z, 32);
-        if (lane == 0) wz[wave] = z;
-        __syncthreads();
-        lz = bl + log(((wz[0] + wz[1]) + wz[2]) + wz[3]);
-      }
-      if (bc != INT_MAX && ti[0] == bc) {
+    // lane g keeps the component g of the batch (P = 1), or of point g % 4 the
+    // components 4 (g / 4) .. 4 (g / 4) + 3; the sums' tree is group_sum's
+    double v[NV];
+    const bool b0 = (g & 1) != 0, b1 = (g & 2) != 0, b2 = (g & 4) != 0;
+    auto fold = [&](auto oc, bool b, double lo, double hi) {
+      return (b ? hi : lo) + xshfl<decltype(oc)::value>(b ? lo : hi);
+    };
+    constexpr std::integral_constant<int, 1> o1{};
+    constexpr std::integral_constant<int, 2> o2{};
+    constexpr std::integral_constant<int, 4> o4{};
+    if constexpr (P == 1) {
+      double w[4], y[2];
 #pragma unroll
-        for (int q = 0; q + 1 < GMM_MAX_M; ++q) {
-          tl[q] = tl[q + 1];
-          ti[q] = ti[q + 1];
+      for (int q = 0; q < 4; ++q) w[q] = fold(o1, b0, acc[2 * q][0], acc[2 * q + 1][0]);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) y[q] = fold(o2, b1, w[2 * q], w[2 * q + 1]);
+      v[0] = fold(o4, b2, y[0], y[1]);
+    } else {
+      double w[kFbBatch];
+#pragma unroll
+      for (int u = 0; u < kFbBatch; ++u)
+        w[u] = fold(o2, b1, fold(o1, b0, acc[u][0], acc[u][1]), fold(o1, b0, acc[u][2], acc[u][3]));
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] = fold(o4, b2, w[q], w[q + 4]);
+    }
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+      const int comp = c0 + NGR * (P == 1 ? g : q + (b2 ? 4 : 0));
+      const double l = comp < k ? kLn2 * (cdir[comp] - v[q]) : -INFINITY;
+      if (!(l > -INFINITY)) continue;
+      if (l > mx) { sm = sm * exp(mx - l) + 1.0; mx = l; }
+      else sm += exp(l - mx);
+      // components arrive in increasing index order: ties keep the earlier
+      if (l > tl[GMM_MAX_M - 1] || ti[GMM_MAX_M - 1] == INT_MAX) {
+#pragma unroll
+        for (int e = GMM_MAX_M - 1; e >= 0; --e) {
+          const bool above = ti[e] == INT_MAX || l > tl[e];
+          const bool above_prev = e > 0 && (ti[e - 1] == INT_MAX || l > tl[e - 1]);
+          if (above_prev) { tl[e] = tl[e - 1]; ti[e] = ti[e - 1]; }
+          else if (above) { tl[e] = l; ti[e] = comp; }
         }
-        tl[GMM_MAX_M - 1] = -INFINITY;
-        ti[GMM_MAX_M - 1] = INT_MAX;
       }
-      if (tid == 0) {
-        int oi = -1;
-        float orr = 0.0f;
-        if (bc != INT_MAX) {
-          const double r = exp(bl - lz);
-          if (j == 0 || r > (double)tau) { oi = bc; orr = (float)r; }
-        }
-        idx[nn * m + j] = oi;
-        resp[nn * m + j] = orr;
-      }
+    }
+  }
+  // rank j: the largest list head (ties to the lower component), whose lane
+  // drops it; the normaliser after the first round
+  int64_t mine = row[0];
+#pragma unroll
+  for (int p = 1; p < P; ++p) mine = mp == p ? row[p] : mine;
+  double lz = 0.0;
+  for (int j = 0; j < m; ++j) {
+    double bl = tl[0];
+    int bc = ti[0];
+    auto pick = [&](double ol, int oc) {
+      const bool o = oc != INT_MAX && (bc == INT_MAX || ol > bl || (ol == bl && oc < bc));
+      bl = o ? ol : bl;
+      bc = o ? oc : bc;
+    };
+    if constexpr (P == 1) {
+      pick(xshfl<1>(bl), xshfl_i<1>(bc));
+      pick(xshfl<2>(bl), xshfl_i<2>(bc));
+    }
+    pick(xshfl<4>(bl), xshfl_i<4>(bc));
+    pick(xshfl<8>(bl), xshfl_i<8>(bc));
+    pick(xshfl<16>(bl), xshfl_i<16>(bc));
+    pick(__shfl_xor(bl, 32), __shfl_xor(bc, 32));
+    if (lane < P) {
+      wl[j & 1][wave][lane] = bl;
+      wc[j & 1][wave][lane] = bc;
     }
     __syncthreads();
+    bl = wl[j & 1][0][mp];
+    bc = wc[j & 1][0][mp];
+    for (int w = 1; w < 4; ++w) pick(wl[j & 1][w][mp], wc[j & 1][w][mp]);
+    if (j == 0) {
+      double z = mx > -INFINITY ? sm * exp(mx - bl) : 0.0;
+      if constexpr (P == 1) {
+        z += xshfl<1>(z);
+        z += xshfl<2>(z);
+      }
+      z += xshfl<4>(z);
+      z += xshfl<8>(z);
+      z += xshfl<16>(z);
+      z += __shfl_xor(z, 32);
+      if (lane < P) wz[wave][lane] = z;
+      __syncthreads();
+      lz = bl + log(((wz[0][mp] + wz[1][mp]) + wz[2][mp]) + wz[3][mp]);
+    }
+    if (bc != INT_MAX && ti[0] == bc) {
+#pragma unroll
+      for (int q = 0; q + 1 < GMM_MAX_M; ++q) {
+        tl[q] = tl[q + 1];
+        ti[q] = ti[q + 1];
+      }
+      tl[GMM_MAX_M - 1] = -INFINITY;
+      ti[GMM_MAX_M - 1] = INT_MAX;
+    }
+    if (tid < P && mine >= 0) {
+      int oi = -1;
+      float orr = 0.0f;
+      if (bc != INT_MAX) {
+        const double r = exp(bl - lz);
+        if (j == 0 || r > (double)tau) { oi = bc; orr = (float)r; }
+      }
+      idx[mine * m + j] = oi;
+      resp[mine * m + j] = orr;
+    }
+  }
+}
+
+__global__ __launch_bounds__(256, 2) void k_assign_fallback(
+    const float* __restrict__ x, int64_t n, int d, int D64, int k, const float* __restrict__ dmu,
+    const double* __restrict__ dh, const double* __restrict__ cdir, int m, float tau,
+    const int* __restrict__ ovf, const int* __restrict__ counts,
+    const int64_t* __restrict__ hlist, int sample_max, int few_max, int* __restrict__ idx,
+    float* __restrict__ resp) {
+  __shared__ __align__(16) float xr[kFbPts][GMM_MAX_D];
+  __shared__ int plist[1024];
+  __shared__ int pcnt;
+  __shared__ double wl[2][4][kFbPts];
+  __shared__ int wc[2][4][kFbPts];
+  __shared__ double wz[4][kFbPts];
+  const int tid = threadIdx.x;
+  const bool off = coarse_off(counts, sample_max);
+  // every point of a call that small (the two passes were not launched)
+  const bool each = hlist != nullptr && off && n <= few_max;
+  const bool few = each || (hlist != nullptr && !off && heavy_count(counts) <= few_max);
+  if (few) {
+    // the light points' lists never overflow
+    const int hc = each ? (int)n : (int)heavy_count(counts), grid = (int)gridDim.x;
+    auto row_of = [&](int i) -> int64_t { return i >= hc ? -1 : (each ? i : hlist[i]); };
+    if (hc <= kFbSingle && hc <= grid) {
+      int64_t row[1] = {row_of((int)blockIdx.x)};
+      if (row[0] < 0) return;
+      fallback_points<1>(x, row, d, D64, k, dmu, dh, cdir, m, tau, xr, wl, wc, wz, idx, resp);
+      return;
+    }
+    for (int i = kFbPts * (int)blockIdx.x; i < hc; i += kFbPts * grid) {
+      int64_t row[kFbPts];
+#pragma unroll
+      for (int p = 0; p < kFbPts; ++p) row[p] = row_of(i + p);
+      fallback_points<kFbPts>(x, row, d, D64, k, dmu, dh, cdir, m, tau, xr, wl, wc, wz, idx, resp);
+    }
+    return;
+  }
+  const int64_t b0 = (int64_t)blockIdx.x * 1024;
+  if (b0 >= n) return;
+  if (tid == 0) pcnt = 0;
+  __syncthreads();
+  // the order of the list does not matter: every point's result is its own
+  for (int i = tid; i < 1024; i += 256)
+    if (b0 + i < n && ovf[b0 + i]) plist[atomicAdd(&pcnt, 1)] = i;
+  __syncthreads();
+  const int np = pcnt;
+  for (int ip = 0; ip < np; ++ip) {
+    int64_t row[1] = {b0 + plist[ip]};
+    fallback_points<1>(x, row, d, D64, k, dmu, dh, cdir, m, tau, xr, wl, wc, wz, idx, resp);
   }
 }
 
@@ -6354,23 +6437,24 @@ int assign_impl(const Layout& L, const float* x, const float* w, const float* mu
                          cv.cand, cv.cidx, dmu, dh, cdir, counts, smax, m, tau, idx, resp, ovf);
     });
   }
-  // up to kFewHeavy points, all of them heavy at most: nothing for the two passes
-  if (hlist == nullptr || n > kFewHeavy) {
+  // up to `few` points, all of them heavy at most: nothing for the two passes
+  const int few = few_heavy(k, D64);
+  if (hlist == nullptr || n > few) {
     if (m + 2 <= 4)
       hipLaunchKernelGGL((k_assign_theta<D64, 4>), dim3((unsigned)L.n_wg_logz), dim3(256), 0, st,
-                         x, n, d, vec4, wp, wpb, cw, ca, counts, m + 2, hlist, smax, theta);
+                         x, n, d, vec4, wp, wpb, cw, ca, counts, m + 2, hlist, smax, few, theta);
     else
       hipLaunchKernelGGL((k_assign_theta<D64, kTMax>), dim3((unsigned)L.n_wg_logz), dim3(256), 0,
-                         st, x, n, d, vec4, wp, wpb, cw, ca, counts, m + 2, hlist, smax, theta);
+                         st, x, n, d, vec4, wp, wpb, cw, ca, counts, m + 2, hlist, smax, few, theta);
     hipLaunchKernelGGL(k_assign_collect<D64>, dim3((unsigned)L.n_wg_logz), dim3(256), 0, st, x, n,
                        d, vec4, wp, wpb, cw, ca, well_idx, ill_idx, dmu, dh, counts, theta, mu,
-                       var, cdir, m, tau, hlist, smax, idx, resp, ovf);
+                       var, cdir, m, tau, hlist, smax, few, idx, resp, ovf);
   }
   {
     int64_t wg = cdiv(n, 1024);
-    if (hlist != nullptr && wg < kFewHeavy) wg = n < kFewHeavy ? n : kFewHeavy;
+    if (hlist != nullptr && wg < kFbGrid) wg = n < kFbGrid ? n : kFbGrid;
     hipLaunchKernelGGL(k_assign_fallback, dim3((unsigned)wg), dim3(256), 0, st, x, n, d, D64, k,
-                       dmu, dh, cdir, m, tau, ovf, counts, hlist, smax, idx, resp);
+                       dmu, dh, cdir, m, tau, ovf, counts, hlist, smax, few, idx, resp);
   }
   return launch_status();
 }

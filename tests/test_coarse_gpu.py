@@ -155,6 +155,42 @@ def test_assignment_of_heavy_points(n, d, monkeypatch):
     _check_assign(x, th, 4, 1e-4, f"assign heavy n{n} d{d}", min_checked=0.5)
 
 
+def _heavy(ws):
+    import torch
+    return int(ws[:64].view(torch.int32)[6])
+
+
+@pytest.mark.parametrize("n,d,m,lo,hi", [
+    (1050, 64, 2, 257, 512),          # a workgroup a point
+    (2403, 64, 8, 513, 2048),       # four points a workgroup, a last one in part
+    (2402, 100, 1, 513, 1536),
+    (5001, 200, 3, 1537, 4096),     # more groups of four than workgroups
+    (2501, 400, 2, 513, 2048),
+    (9001, 64, 2, 3300, 9001),      # more than that: the two-pass screening
+    (11003, 200, 2, 4097, 11003)])
+def test_heavy_points_over_all_components(n, d, m, lo, hi, monkeypatch):
+    """Heavy points in fp64 over every component, up to where the two passes take them.  A
+    responsibility is then the fp32 rounding of an fp64 value (that of a light point: below
+    k 2^-40 off); the passes keep a screening error of 2^-21 (S + d)."""
+    import torch
+    import paper_2606_10896_amd as gmm
+    x, th = _reach(d, 23, n)
+    k = th[0].shape[0]
+    s = float((th[1].astype(np.float64) ** 2 / th[2]).sum(1).max())
+    passes = hi == n
+    monkeypatch.setattr(gmmcheck, "TOL_RESP",
+                        max(gmmcheck.TOL_RESP, 2.0 ** -21 * (s + d)) if passes else 1e-6)
+    ws = gmm.workspace(n, d, k, m)
+    ws.fill_(0xEE)
+    torch.cuda.synchronize()
+    ref = oracle.assign_topk(x, *th, m, 1e-4, mr=m + 1)
+    gidx, gresp = gpu_assign(x, *th, m, 1e-4, ws=ws)
+    heavy = _heavy(ws)
+    print(f"  heavy over all n{n} d{d} m{m}: {heavy} heavy, "
+          f"{check_assign(gidx, gresp, ref, m, 1e-4, f'n{n} d{d}', 0.5):.4f}", flush=True)
+    assert lo <= heavy <= hi
+
+
 @pytest.mark.parametrize("n", [300, 3000])
 def test_assignment_with_weights_near_the_end_of_the_float_range(n):
     w = g.custom("cx", 3000, 24, 10, 40, data_seed=8, init_seed=9)
