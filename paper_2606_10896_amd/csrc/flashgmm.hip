@@ -1961,8 +1961,9 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_logz(
 // sample_max are heavy.
 constexpr int kCand = 8;                // candidates held per point
 constexpr float kCoarseWindow = kDenseWindow;
-// Workgroups of the sample, taken when n is at least kSampleMin (below, the
-// pass costs no more than a round of workgroups).  The pass is switched off
+// Workgroups of the sample, taken when n is at least kSampleMin.  Below, it costs what it
+// saves: E-step without and with it, n = 131072, d = 64, k = 256 661 and 639 us with every point
+// heavy, 294 and 302 with few; n = 131072, d = 768, k = 1024 2112 and 2202.  The pass is switched off
 // when more than half of the sample is heavy: it costs about a third of k_logz
 // a point and the candidates' sums another sixth, so that with fewer than about
 // half of the points light it would not pay (the first E-step of a fit at
@@ -1988,8 +1989,20 @@ inline int few_heavy(int k, int D64) {
 // Candidate window of an assignment: what lies below is at most k 2^-40 of the
 // normaliser, and cannot be assigned to a rank j > 1 when tau >= 2^-40.
 constexpr float kAssignWindow = 40.0f;
-// Below this many points the waves of a workgroup share their points (SPLIT).
-constexpr int64_t kSplitMax = 65536;
+// Below this many points the waves of a workgroup share their points (SPLIT).  Both forms take
+// whole rounds: the shared one 8192 points (4096 above 768 dimensions, where a wave has one
+// tile), the plain one 512 workgroups of 128 to 256 points up to 256 dimensions and 256 of 64 to
+// 256 above, which take several times as long.  k_coarse, k = 1024, us plain and shared:
+// d = 64 28 and 21 (n = 32000), 29 and 31 (48000); d = 128 42 and 35, 41 and 48; d = 192 46 and 43
+// (24000), 47 and 50 (28000); d = 256 47 and 47 (16000), 46 and 65 (20000); d = 512 86 and 87
+// (16000), 87 and 124 (20000); d = 768 156 and 159, 155 and 235; d = 1024 122 and 121 (8000), 123
+// and 177 (12000).  Tied variances: d = 384 77 and 77 (24000), d = 768 168 and 157 (24000), 176
+// and 197 (28000); d = 1024 129 and 96 (8000), 130 and 176 (12000).
+constexpr int64_t split_max(int D64, bool iso) {
+  if (D64 <= 128) return 32768;
+  if (D64 == 192 || (iso && D64 > 256 && D64 < 1024)) return 24576;
+  return (iso ? D64 == 1024 : D64 > 768) ? 8192 : 16384;
+}
 // steps of 32 k: [x | x^2], or x and one step for ||x||^2
 template <int D64, bool ISO>
 __host__ __device__ constexpr int coarse_steps() {
@@ -2241,10 +2254,9 @@ __device__ __forceinline__ f4v mfma16b(bf16x8 a, bf16x8 b, f4v c) {
 // bits carry the group, so that an update is four instructions: mask-and-or, two
 // medians, one maximum.  The updates of a group fill the issue slots between
 // the MFMAs of the next one (two accumulator sets).
-// SPLIT (few points): the workgroup's waves share its 32 points instead and take
-// every fourth group each, reading the operand from L2 one group ahead; their
-// states meet in LDS at the end.  With 256 points a workgroup, n below about
-// 65536 would leave compute units without one.
+// SPLIT (few points, split_max): the workgroup's waves share its 32 points (16 above 768
+// dimensions) instead and take every fourth group each, reading the operand from L2 one
+// group ahead; their states meet in LDS at the end.
 template <int D64, bool ISO, bool SPLIT>
 __global__ __launch_bounds__(256, SPLIT ? 1 : coarse_wgs(D64)) void k_coarse(
     const float* __restrict__ x, int64_t n, int d, const bf16x8* __restrict__ wpc,
@@ -6163,7 +6175,7 @@ void launch_coarse(const Layout& L, const float* x, void* ws, float window, hipS
   constexpr int WP = 4 * 16 * coarse_tiles(D64, ISO);
   constexpr int SP = 16 * (coarse_tiles(D64, ISO) > 2 ? 2 : coarse_tiles(D64, ISO));
   *smax = INT_MAX;
-  if (L.n < kSplitMax) {
+  if (L.n < split_max(D64, ISO)) {
     hipLaunchKernelGGL((k_coarse<D64, ISO, true>), dim3((unsigned)cdiv(L.n, SP)), dim3(256), 0, st,
                        x, L.n, L.d, cv.wpc, cv.cbias, cv.cb2, counts, window, (int64_t)1, 0,
                        INT_MAX, cv.cand, cv.hlist);

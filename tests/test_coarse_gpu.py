@@ -25,10 +25,10 @@ def _dirty_ws(n, d, k):
     return ws
 
 
-def _dirty_ws_m(n, d, k):
+def _dirty_ws_m(n, d, k, m=1):
     import torch
     import paper_2606_10896_amd as gmm
-    ws = gmm.workspace(n, d, k, 1)
+    ws = gmm.workspace(n, d, k, m)
     ws.fill_(0xEE)
     torch.cuda.synchronize()
     return ws
@@ -198,6 +198,44 @@ def test_assignment_with_weights_near_the_end_of_the_float_range(n):
     var = var.copy()
     var[7] = 1e-29
     _check_assign(x[:n], (wt, mu, var), 2, 1 / 40, f"assign wild n{n}")
+
+
+@pytest.mark.parametrize("d,n", [(20, 32768), (128, 32768), (190, 24576), (250, 16384),
+                                 (300, 16384), (500, 16384), (640, 16384), (760, 16384),
+                                 (800, 8192), (1000, 8192)])
+def test_shared_and_whole_workgroups_agree(d, n):
+    """One row below the number from which on a workgroup's waves have points of their own, and
+    that number: the same rows but one, listed by either form."""
+    k = 21
+    w = g.custom(f"cs{d}", n, d, 10, k, data_seed=d, init_seed=d + 1)
+    x, th0 = g.make(w)
+    th = oracle.fit(x[:4000], *th0, 2, keep_thetas=True)["thetas"][-1]
+    a, ra = gpu_assign(x[:-1], *th, 2, 0.01, ws=_dirty_ws_m(n - 1, d, k, 2))
+    b, rb = gpu_assign(x, *th, 2, 0.01, ws=_dirty_ws_m(n, d, k, 2))
+    same = a == b[:-1]
+    assert same.mean() > 0.9999
+    # two fp32 roundings of fp64 responsibilities, normalisers k 2^-40 apart at most
+    assert np.abs(ra - rb[:-1])[same].max() <= 1e-6
+    _check(x[-300:], th, f"split d{d}")
+    _check_assign(x[-300:], th, 2, 0.01, f"split assign d{d}")
+
+
+@pytest.mark.parametrize("d,n", [(100, 32768), (190, 24576), (250, 16384), (300, 24576),
+                                 (900, 24576), (1000, 8192)])
+def test_shared_and_whole_workgroups_agree_isotropic(d, n):
+    import torch
+    import paper_2606_10896_amd as gmm
+    k = 37
+    w = g.custom(f"ct{d}", n, d, k, k, data_seed=d, init_seed=d + 1)
+    x, (_, mu, _) = g.make(w)
+    xd, md = torch.from_numpy(x).cuda(), torch.from_numpy(mu).cuda()
+    m64 = mu.astype(np.float64)
+    score = x.astype(np.float64) @ m64.T - 0.5 * (m64 ** 2).sum(1)
+    for rows in (n - 1, n):
+        wd, vd = torch.full((k,), 1.0 / k, device="cuda"), torch.ones(k, d, device="cuda")
+        assign = torch.empty(rows, dtype=torch.int32, device="cuda")
+        gmm.gmm_kmeans(xd[:rows], wd, md.clone(), vd, 0, assign, _dirty_ws_m(rows, d, k))
+        assert (assign.cpu().numpy() == score[:rows].argmax(1)).all(), rows
 
 
 @pytest.mark.parametrize("n,d,k", [(65600, 20, 33), (900, 300, 20)])
