@@ -384,6 +384,17 @@ __device__ __forceinline__ int dense_chunks(int64_t np, bool listed, int nch) {
 __device__ __forceinline__ int64_t heavy_count(const int* __restrict__ counts) {
   return (int64_t)*reinterpret_cast<const unsigned long long*>(counts + kCntHeavy);
 }
+// Points a workgroup of the passes over the heavy points takes: at most the pts it has room
+// for, fewer where the np points leave compute units without one.  A workgroup's screening takes
+// the same time for one point as for pts, but the exact sums after it grow with its points: packed
+// full, the few heavy points of a small call took longer than all of its points had.  n = 1000, k
+// = 1024, at the initialisation, all points / heavy ones packed / spread: k_logz d = 200 200, 221,
+// 189 us; E-step d = 384 593, 696, 610; assignment n = 8000, d = 1024 357, 500, 445.
+__device__ __forceinline__ int heavy_share(int64_t np, int pts, bool whole) {
+  if (whole) return pts;
+  const int64_t wg = gridDim.x < 256 ? gridDim.x : 256, per = (np + wg - 1) / wg;
+  return per < pts ? (int)per : pts;
+}
 
 __global__ __launch_bounds__(64) void k_prep_class(const float* __restrict__ w,
                                                    const float* __restrict__ mu,
@@ -1199,12 +1210,14 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_logz(
   auto& rtl = post.rtl;
   auto& prow = post.prow;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, h = lane >> 5, col = lane & 31;
-  const int64_t n0 = (int64_t)blockIdx.x * PTS;
   // the points taken: the heavy ones of the one-product screening (hlist), or
-  // all of them; np of them in all, point p of this workgroup is row(p)
+  // all of them; n0 .. np - 1 here, point p of this workgroup is row(p)
   const bool whole = hlist == nullptr || coarse_off(counts, sample_max);
-  const int64_t np = whole ? n : heavy_count(counts);
-  if (n0 >= np) return;
+  const int64_t all = whole ? n : heavy_count(counts);
+  const int per = heavy_share(all, PTS, whole);
+  const int64_t n0 = (int64_t)blockIdx.x * per;
+  if (n0 >= all) return;
+  const int64_t np = n0 + per < all ? n0 + per : all;
   auto row_of = [&](int p) -> int64_t {
     if (n0 + p >= np) return n;
     return whole ? n0 + p : hlist[n0 + p];
@@ -4680,11 +4693,13 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_assign_theta(
   float* const lmx = reinterpret_cast<float*>(smem + XB);                  // [PTS][129]
   float2* const lma = reinterpret_cast<float2*>(smem);                     // [PTS][129]
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, h = lane >> 5, col = lane & 31;
-  const int64_t n0 = (int64_t)blockIdx.x * PTS;
   // the points taken: the heavy ones of the one-product screening, or all
   const bool whole = hlist == nullptr || coarse_off(counts, sample_max);
-  const int64_t np = whole ? n : heavy_count(counts);
-  if (n0 >= np || (!whole && np <= few_max)) return;
+  const int64_t all = whole ? n : heavy_count(counts);
+  const int per = heavy_share(all, PTS, whole);
+  const int64_t n0 = (int64_t)blockIdx.x * per;
+  if (n0 >= all || (!whole && all <= few_max)) return;
+  const int64_t np = n0 + per < all ? n0 + per : all;
   auto row_of = [&](int p) -> int64_t {
     if (n0 + p >= np) return n;
     return whole ? n0 + p : hlist[n0 + p];
@@ -4823,11 +4838,13 @@ __global__ __launch_bounds__(256, screen_b16(D64) ? 2 : 1) void k_assign_collect
   bf16x8* const xa = reinterpret_cast<bf16x8*>(smem);
   double* const cl = reinterpret_cast<double*>(smem + (SPL ? 0 : XB));    // [PTS][kACap]
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, h = lane >> 5, col = lane & 31;
-  const int64_t n0 = (int64_t)blockIdx.x * PTS;
   // the points taken: the heavy ones of the one-product screening, or all
   const bool whole = hlist == nullptr || coarse_off(counts, sample_max);
-  const int64_t np = whole ? n : heavy_count(counts);
-  if (n0 >= np || (!whole && np <= few_max)) return;
+  const int64_t all = whole ? n : heavy_count(counts);
+  const int per = heavy_share(all, PTS, whole);
+  const int64_t n0 = (int64_t)blockIdx.x * per;
+  if (n0 >= all || (!whole && all <= few_max)) return;
+  const int64_t np = n0 + per < all ? n0 + per : all;
   auto row_of = [&](int p) -> int64_t {
     if (n0 + p >= np) return n;
     return whole ? n0 + p : hlist[n0 + p];

@@ -191,6 +191,21 @@ def test_heavy_points_over_all_components(n, d, m, lo, hi, monkeypatch):
     assert lo <= heavy <= hi
 
 
+@pytest.mark.parametrize("n,d", [(70, 64), (601, 300), (3001, 200), (40000, 64)])
+def test_heavy_points_spread_over_workgroups(n, d):
+    """From one heavy point a workgroup of the passes over them to as many as it has room for."""
+    x, th = _reach(d, 31, n)
+    _check(x, th, f"spread n{n} d{d}")
+    if n > 10000:                           # more than are done over all components
+        s = float((th[1].astype(np.float64) ** 2 / th[2]).sum(1).max())
+        tol = gmmcheck.TOL_RESP
+        try:
+            gmmcheck.TOL_RESP = max(tol, 2.0 ** -21 * (s + d))
+            _check_assign(x, th, 2, 1e-4, f"spread assign n{n} d{d}", min_checked=0.5)
+        finally:
+            gmmcheck.TOL_RESP = tol
+
+
 @pytest.mark.parametrize("n", [300, 3000])
 def test_assignment_with_weights_near_the_end_of_the_float_range(n):
     w = g.custom("cx", 3000, 24, 10, 40, data_seed=8, init_seed=9)
