@@ -2913,6 +2913,12 @@ __global__ __launch_bounds__(256) void k_assign_refine(
 // Statistic column block c = 4g + e (x part; the x^2 part likewise) row i is
 // dimension 64g + 4i + e, so a lane reads the 4 blocks of a group with one
 // float4 too.
+// The first lane of each sixteen in a vote (the lowest bit of each 16-bit field: f & -f), on the
+// scalar unit, without vector registers.
+__device__ __forceinline__ unsigned long long first_of_16(unsigned long long vote) {
+  const unsigned long long n = ~vote;
+  return vote & (((n & 0x7FFF7FFF7FFF7FFFull) + 0x0001000100010001ull) ^ (n & 0x8000800080008000ull));
+}
 __device__ __forceinline__ f4v mfma16(float a, float b, f4v c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
@@ -2967,6 +2973,7 @@ __global__ __launch_bounds__(64, D64 <= 128 ? 2 : 1) void k_stats_well(
   const int myslot = 16 * grp + i16;
   const bool mylight = sflag != nullptr && myslot < n_well && sflag[myslot] != 0;
   const bool anylight = __ballot(mylight) != 0ull;
+  const bool several = __popcll(__ballot(mylight)) > 4;   // light components (four lanes each)
   float wb[WQS];
 #pragma unroll
   for (int s2 = 0; s2 < WQS; ++s2) wb[s2] = wq[((size_t)grp * WQS + s2) * 64 + lane];
@@ -3172,18 +3179,25 @@ __global__ __launch_bounds__(64, D64 <= 128 ? 2 : 1) void k_stats_well(
       // one lane a point flags it for its sixteen components: as a store and an atomic of
       // every such lane they took half of the pass where nearly every component is light
       // (E-step from the random-point initialisation, d = 128, k = 1024: n = 8000 585 ->
-      // 455 us, 547 before the granules were marked; n = 30000 994 -> 806)
-      if (anylight) {
+      // 455 us, 547 before the granules were marked; n = 30000 994 -> 806).  The lane is chosen
+      // on the scalar unit: shifts of a vote by lane cost registers that the tile loop does not
+      // have (E-step of 1e8 points 1.8 ms).
+      auto flag = [&](int v) {
+        const int64_t nn = pb + pov[v];
+        lflag[nn] = 1;
+        if (lmask != nullptr) atomicOr(lmask + nn, kbit);
+      };
+      if (several) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const unsigned long long hit =
               __ballot(mylight && pov[v] != ~0u && exp2_fast(la[v]) > 0x1p-72f);
-          if (i16 == 0 && ((hit >> (16 * k4)) & 0xFFFFull) != 0ull) {
-            const int64_t nn = pb + pov[v];
-            lflag[nn] = 1;
-            if (lmask != nullptr) atomicOr(lmask + nn, kbit);
-          }
+          if (__builtin_amdgcn_inverse_ballot_w64(first_of_16(hit))) flag(v);
         }
+      } else if (anylight) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (mylight && pov[v] != ~0u && exp2_fast(la[v]) > 0x1p-72f) flag(v);
       }
       // statistics: step v contracts points 4k + v (k = 0..3)
 #pragma unroll
@@ -3290,6 +3304,7 @@ __global__ __launch_bounds__(64 * (DW / 128)) void k_stats_wide(
   // a light component is left out here and recomputed exactly; the points
   // where it comes within 2^-72 of log2 Z are flagged for that
   const bool mylight = sflag != nullptr && myslot < n_well && sflag[myslot] != 0;
+  const bool several = __popcll(__ballot(mylight)) > 4;   // light components (four lanes each)
   float wb[2 * SW];
 #pragma unroll
   for (int s2 = 0; s2 < SW; ++s2) {
@@ -3500,10 +3515,9 @@ __global__ __launch_bounds__(64 * (DW / 128)) void k_stats_wide(
       tot += cst - lzv[v];
       const float e = exp2_fast((float)tot);
       r[v] = (((rbv[v] >> i16) & 1u) || mylight) ? 0.0f : e;
-      // one lane a point flags it for its sixteen components
-      const unsigned long long hit =
-          __ballot(mylight && wave == 0 && e > 0x1p-72f && pov[v] >= 0);
-      if (i16 == 0 && ((hit >> (16 * k4)) & 0xFFFFull) != 0ull) {
+      bool hit = mylight && wave == 0 && e > 0x1p-72f && pov[v] >= 0;
+      if (several) hit = __builtin_amdgcn_inverse_ballot_w64(first_of_16(__ballot(hit)));
+      if (hit) {
         lflag[pov[v]] = 1;
         if (lmask != nullptr) atomicOr(lmask + pov[v], kbit);
       }
