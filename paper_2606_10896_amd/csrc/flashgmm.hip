@@ -391,9 +391,11 @@ __device__ __forceinline__ int64_t heavy_count(const int* __restrict__ counts) {
 // = 1024, at the initialisation, all points / heavy ones packed / spread: k_logz d = 200 200, 221,
 // 189 us; E-step d = 384 593, 696, 610; assignment n = 8000, d = 1024 357, 500, 445.
 __device__ __forceinline__ int heavy_share(int64_t np, int pts, bool whole) {
-  if (whole) return pts;
-  const int64_t wg = gridDim.x < 256 ? gridDim.x : 256, per = (np + wg - 1) / wg;
-  return per < pts ? (int)per : pts;
+  // without a division where there are enough: of a large call's workgroups, one for every pts
+  // points, most only look and leave
+  if (whole || np >= 256 * (int64_t)pts) return pts;
+  const unsigned wg = gridDim.x < 256u ? gridDim.x : 256u, per = ((unsigned)np + wg - 1u) / wg;
+  return per < (unsigned)pts ? (int)per : pts;
 }
 
 __global__ __launch_bounds__(64) void k_prep_class(const float* __restrict__ w,
