@@ -4032,7 +4032,17 @@ __host__ __device__ constexpr int ill_pt(int D64) {
 }
 __host__ __device__ constexpr int ill_cw(int D64) { return D64 <= 256 ? 8 : (D64 <= 512 ? 4 : 2); }
 
+// Chunks of points each of the n_ikb component blocks is split into.  A workgroup of
+// k_stats_direct (tiles of 128 points) has a compute unit to itself: where a chunk would be
+// about a tile, or there is one block and some tiles, one round of 256 workgroups saves the
+// second one's start; else two rounds even the chunks' shares out.  E-step in the course of a
+// fit, 512 workgroups and 256: n = 50000, d = 64, k = 256 264 and 237 us; d = 128, k = 64 262 and
+// 237; n = 250000, d = 64, k = 256 (one block) 328 and 308, k = 1024 (eight) 849 and 905; the
+// pass at n = 1e8, d = 128 (one block) 1.47 and 1.59 ms.
 __host__ __device__ inline int ill_chunks(int grid, int n_ikb, int64_t n, int pt) {
+  if (pt == ill_pt(128) && grid > 256 &&
+      ((n_ikb <= 1 && n <= (1 << 21)) || (n_ikb <= 8 && n <= 512 * pt)))
+    grid = 256;
   int c = grid / (n_ikb > 0 ? n_ikb : 1);
   const int64_t cap = (n + pt - 1) / pt;
   if (c > cap) c = (int)cap;
